@@ -328,6 +328,85 @@ bound_status build_geoms(bound_net *net, hipStream_t st) {
     return BOUND_OK;
 }
 
+// The products of a window pass that bounds every neuron of the convolutional layer k:
+// per layer m = k-1 .. 1 the geometry from its window to the window of layer m-1, and the
+// maps of the windows' positions (map[m]: window on z_m's neurons, map[0]: on the input).
+struct WinPlan {
+    std::vector<GeomSet> gs;     // index m
+    std::vector<WinMap> map;     // index m
+    std::vector<long> elems;     // index m: floats per img of the window of z_m (0: the input)
+};
+
+// Window geometry of target k, or false where whole layers serve better: a layer below is
+// not a convolution, a product's shape is outside the window kernels, or the windows cover
+// so much of the layers that they save less than a third of the multiply-adds (the window
+// epilogues cost more per element; no network between 1 / 2 and 1 / 1 was timed).
+bool window_plan(const bound_net *net, int k, int rpi, WinPlan &wp) {
+    const bound_layer &T = net->layers[k - 1].L;
+    const long lim = 1L << 20;                 // FP32-reciprocal quotients
+    if (T.kind != BOUND_CONV2D || k < 2 || rpi > lim || net->d[k] > lim) return false;
+    wp.gs.assign(k, GeomSet{});
+    wp.map.assign(k, WinMap{});
+    wp.elems.assign(k, 0);
+    int need = T.kh, store = T.kh, S = T.stride, P = T.pad;   // window of z_{k-1}
+    double dense = 0, win = 0;
+    auto put_map = [&](int m) {
+        const bound_layer &L = net->layers[m].L;              // reads layer m's output
+        WinMap &w = wp.map[m];
+        w.H = L.in_h; w.W = L.in_w; w.N = L.in_c; w.DW = store;
+        w.S = S; w.P = P; w.ow = T.out_w; w.dk = (int)net->d[k]; w.rpi = rpi;
+        w.rDW = 1.0f / (float)store;
+        w.rC = 1.0f / (float)T.out_c;
+        w.rOw = 1.0f / (float)T.out_w;
+        w.rrpi = 1.0f / (float)rpi;
+        wp.elems[m] = (long)store * store * L.in_c;
+    };
+    put_map(k - 1);
+    for (int m = k - 1; m >= 1; --m) {
+        const LayerInfo &li = net->layers[m - 1];
+        const bound_layer &L = li.L;
+        if (L.kind != BOUND_CONV2D || L.kh < L.stride) return false;
+        const int s = L.stride, in = store;
+        need = (need - 1) * s + L.kh;
+        int A = (need + s - 1) / s;
+        if (m > 1 || L.in_c > 4) {             // MFMA tiles: 4, 8 or 16 pixels a side
+            A = A <= 4 ? 4 : (A <= 8 ? 8 : 16);
+            if (A * s < need) return false;
+        }
+        store = A * s;
+        P = P * s + L.pad;
+        S *= s;
+        if (store > 512 || S > 512) return false;
+        put_map(m - 1);
+        // phase ph of the window (wy % s) takes the weights packed for the layer's phase
+        // with the same first tap, (p + pad) % s == ph
+        GeomSet &gs = wp.gs[m];
+        gs.n = 0;
+        for (int py = 0; py < s; ++py)
+            for (int px = 0; px < s; ++px) {
+                const Geom *src = nullptr;
+                for (int i = 0; i < li.gT.n; ++i)
+                    if ((li.gT.g[i].oy0 + L.pad) % s == py && (li.gT.g[i].ox0 + L.pad) % s == px)
+                        src = &li.gT.g[i];
+                if (!src) return false;
+                Geom g = *src;
+                g.H = g.W = in;
+                g.OH = g.OW = A;
+                g.pad_y = g.kh - 1;
+                g.pad_x = g.kw - 1;
+                g.DH = g.DW = store;
+                g.oy0 = py;
+                g.ox0 = px;
+                set_recips(g);
+                win += (double)A * A * g.K * g.N;
+                gs.g[gs.n++] = g;
+            }
+        dense += (double)L.out_h * L.out_w * L.out_c * L.kh * L.kw * L.in_c;
+        if (wp.elems[m - 1] > net->max_d || !window_fits(gs, m == 1)) return false;
+    }
+    return wp.elems[k - 1] <= net->max_d && 1.5 * win <= dense;
+}
+
 // Scratch for the split list (nnz entries) and, with beta, its per-row multiplier terms
 // (nnz x rows).  Grows only outside stream capture; old buffers stay until bound_destroy.
 bound_status ensure_split_cap(bound_net *net, long nnz, long rows, hipStream_t st) {
@@ -353,6 +432,72 @@ bound_status ensure_split_cap(bound_net *net, long nnz, long rows, hipStream_t s
         if (!net->alloc(&b, cap)) return fail(BOUND_E_NOMEM, "split multiplier scratch");
         net->bsum = b;
         net->bsum_cap = cap;
+    }
+    return BOUND_OK;
+}
+
+// Start of a pass with the identity spec on z_k.
+IdentityParams identity_params(const bound_net *net, int k, int rpi, long img0) {
+    const LayerInfo &li = net->layers[k - 1];
+    IdentityParams ip{};
+    ip.kind = li.L.kind;
+    ip.W = li.L.weight;
+    ip.bias_k = li.L.bias;
+    ip.ci = li.L.in_c; ip.hi_ = li.L.in_h; ip.wi = li.L.in_w;
+    ip.co = li.L.out_c; ip.ho = li.L.out_h; ip.wo = li.L.out_w;
+    ip.kh = li.L.kh; ip.kw = li.L.kw; ip.stride = li.L.stride; ip.pad = li.L.pad;
+    ip.dk = net->d[k]; ip.din = li.din; ip.rpi = rpi; ip.img0 = img0;
+    ip.s = net->acc_s; ip.mag = net->acc_mag; ip.low = net->acc_low;
+    return ip;
+}
+
+// The backward pass of bound_backward on windows (tables and box are prepared).
+bound_status window_pass(bound_net *net, const bound_pass *P, const bound_out *out, WinPlan &wp, int rpi,
+                         long total, bool slack, long ld, hipStream_t st) {
+    const int k = P->target;
+    const bool both = (P->flags & BOUND_BOTH_SIDES) != 0;
+    const bound_layer &T = net->layers[k - 1].L;
+    for (long img0 = 0; img0 < total; img0 += net->max_rows) {
+        const long n_img = total - img0 < net->max_rows ? total - img0 : net->max_rows;
+        for (auto &w : wp.map) w.img0 = img0;
+        float *cur = net->buf[0], *nxt = net->buf[1];
+        IdentityParams ip = identity_params(net, k, rpi, img0);
+        ip.tab = net->tab + net->relu_off(k - 1);
+        ip.tab_ld = net->n_relu;
+        ip.bias_m = net->bias(k - 1);
+        ip.out = cur;
+        {
+            ProfScope ps(net, st, lbl("init_window_L%d", k));
+            HIPCHK(launch_init_window(ip, wp.map[k - 1], n_img, st));
+        }
+        for (int m = k - 1; m >= 2; --m) {
+            RelaxParams rp{};
+            rp.out = nxt;
+            rp.tab = net->tab + net->relu_off(m - 1);
+            rp.tab_ld = net->n_relu;
+            rp.bias = net->bias(m - 1);
+            rp.chan = net->chan(m - 1);
+            rp.D = wp.elems[m - 1];
+            rp.s = net->acc_s;
+            rp.mag = net->acc_mag;
+            ProfScope ps(net, st, lbl("win_relax_L%d", m));
+            HIPCHK(window_relax(wp.gs[m], cur, n_img, rp, wp.map[m - 1], st));
+            std::swap(cur, nxt);
+        }
+        ConcParams cp{};
+        cp.cen = net->cen;
+        cp.rad = net->rad;
+        cp.D = net->d[0];
+        cp.low = net->acc_low;
+        cp.mag = net->acc_mag;
+        {
+            ProfScope ps(net, st, "win_conc");
+            HIPCHK(window_conc(wp.gs[1], cur, n_img, cp, wp.map[0], st));
+        }
+        ProfScope pf(net, st, "finalize");
+        HIPCHK(launch_finalize(img0, n_img, P->rows, rpi, net->acc_s, net->acc_low, net->acc_mag, net->infeas,
+                               slack, out->lower, both ? out->upper : nullptr, ld, nullptr, nullptr, out->best,
+                               both ? out->best_upper : nullptr, st, T.out_c, T.out_h * T.out_w));
     }
     return BOUND_OK;
 }
@@ -623,6 +768,23 @@ bound_status bound_backward(bound_net *net, const bound_pass *P, const bound_out
     }
     }
 
+    // Full CROWN's pass over a convolutional layer: windows instead of whole layers.  Early
+    // stops, split multipliers, coefficient output and the options (tests and
+    // comparisons of the whole-layer kernels) keep the general path.
+    const bool winok = ident && conc && sl == 0 && !inject && net->options == 0 && !net->tuning;
+    if (winok && k == 1 && net->layers[0].L.kind == BOUND_CONV2D) {
+        IdentityParams ip = identity_params(net, k, rpi, 0);
+        ip.cen = net->cen;
+        ip.rad = net->rad;
+        ProfScope ps(net, st, "conv1_bounds");
+        HIPCHK(launch_conv1_bounds(ip, P->n_inst, slack, out->lower, both ? out->upper : nullptr, ld,
+                                   out->best, both ? out->best_upper : nullptr, st));
+        return BOUND_OK;
+    }
+    WinPlan wp;
+    if (winok && k > 1 && window_plan(net, k, rpi, wp))
+        return window_pass(net, P, out, wp, rpi, total, slack, ld, st);
+
     const long chunk = save ? total : net->max_rows;
     std::vector<long> soff(k + 2, 0);  // offset of saved G_m for m = 1..k
     long lam_off = 0;                  // saved Lambda on z_sl at a linear stop
@@ -673,16 +835,7 @@ bound_status bound_backward(bound_net *net, const bound_pass *P, const bound_out
         float *cur = net->buf[0], *nxt = net->buf[1];
         int m_start;
         if (ident) {
-            const LayerInfo &li = net->layers[k - 1];
-            IdentityParams ip{};
-            ip.kind = li.L.kind;
-            ip.W = li.L.weight;
-            ip.bias_k = li.L.bias;
-            ip.ci = li.L.in_c; ip.hi_ = li.L.in_h; ip.wi = li.L.in_w;
-            ip.co = li.L.out_c; ip.ho = li.L.out_h; ip.wo = li.L.out_w;
-            ip.kh = li.L.kh; ip.kw = li.L.kw; ip.stride = li.L.stride; ip.pad = li.L.pad;
-            ip.dk = dk; ip.din = li.din; ip.rpi = rpi; ip.img0 = img0;
-            ip.s = net->acc_s; ip.mag = net->acc_mag; ip.low = net->acc_low;
+            IdentityParams ip = identity_params(net, k, rpi, img0);
             if (conc_m == k) {
                 ip.cen = sl > 0 ? net->stop_cen : net->cen;
                 ip.rad = sl > 0 ? net->stop_rad : net->rad;

@@ -116,6 +116,22 @@ struct FwdParams {         // z_m = W_m h_{m-1} + b_m for sample rows
     long D;
 };
 
+// Receptive-field windows.  A row that bounds one neuron of a convolutional layer has
+// non-zero coefficients only inside a window of every layer below, so such passes keep
+// [img][window][C] tensors: img r of an instance is the target's neuron r (pixel-major,
+// channel fastest; dk further imgs hold the negated rows), whose window at this layer
+// starts at (oy * S - P, ox * S - P) for its target pixel (oy, ox).
+struct WinMap {
+    int H, W;                // the layer's own extent; window pixels outside it hold 0
+    int N;                   // its channels
+    int DW;                  // pixels per window row
+    int S, P;
+    int ow, dk;              // target layer: pixels per row, width
+    int rpi;                 // imgs per instance
+    long img0;
+    float rDW, rC, rOw, rrpi;   // fl(1 / .) of DW, the target's channels, ow, rpi
+};
+
 // ----- product launchers ---------------------------------------------------------
 // A plan picks the kernel of one product: path 0 = automatic (direct convolution when
 // the geometry fits, else the implicit GEMM with the default tile), 1 = direct
@@ -160,6 +176,13 @@ hipError_t direct_adj(const GeomSet &gs, const float *A, long n_img, const AdjPa
 hipError_t direct_fwd(const GeomSet &gs, const float *A, long n_img, const FwdParams &p,
                       hipStream_t st, int cc, int mode, bool *used);
 int direct_candidates(const GeomSet &gs, int *cc, int *mode, int cap);
+// window.hip: the products of a window pass (direct convolution, DMA-staged); window_fits
+// tells whether the kernels cover a geometry (conc: the concretising step)
+bool window_fits(const GeomSet &gs, bool conc);
+hipError_t window_relax(const GeomSet &gs, const float *A, long n_img, const RelaxParams &p,
+                        const WinMap &w, hipStream_t st);
+hipError_t window_conc(const GeomSet &gs, const float *A, long n_img, const ConcParams &p,
+                       const WinMap &w, hipStream_t st);
 
 // ----- auxiliary kernels (aux.hip) ---------------------------------------------------
 struct LayerShape {        // output shape of a ReLU layer (for index maps)
@@ -257,6 +280,11 @@ struct IdentityParams {
     float *s, *mag, *low;
 };
 hipError_t launch_init_identity(const IdentityParams &p, long n_img, bool conc, hipStream_t st);
+// identity rows of a convolutional target as windows of layer k-1 (w: that layer's map)
+hipError_t launch_init_window(const IdentityParams &p, const WinMap &w, long n_img, hipStream_t st);
+// lower / upper bounds of z_1 = conv(x) over the box (both or lower only)
+hipError_t launch_conv1_bounds(const IdentityParams &p, int n_inst, bool slack, float *lower, float *upper,
+                               long ld, float *best, float *best_upper, hipStream_t st);
 
 // Per first split entry q and row r: sum over the instance's entries on the same neuron
 // of sign * beta (the term the relaxation epilogue subtracts at the split neuron).
@@ -266,7 +294,8 @@ hipError_t launch_beta_sum(int nnz, int rows, const int32_t *off, const int32_t 
 hipError_t launch_finalize(long img0, long n_img, int rows, int rpi, const float *s,
                            const float *low, const float *mag, const int32_t *infeas,
                            bool slack, float *lower, float *upper, long ld, float *offset,
-                           float *offset_mag, float *best, float *best_upper, hipStream_t st);
+                           float *offset_mag, float *best, float *best_upper, hipStream_t st,
+                           int pC = 0, int pHW = 0);   // pC: window pass, the target's channels
 hipError_t launch_adj_init(long n_img, int rows, long d0, const float *gl, const float *g1,
                            const float *cen, const float *rad, const int32_t *infeas,
                            float *gbar, float *sbar, hipStream_t st);

@@ -118,6 +118,7 @@ __device__ inline void lds_dma16(const float *base, int nbytes, float *lds, int 
 struct EpiRelax {
     RelaxParams p;
     static constexpr int NRED = 2;
+    static constexpr bool WIN = false;
     using Pre = Relax;
     struct Row { const Relax *tb; float *out, *save; };
     __device__ Row row(int img) const {
@@ -137,7 +138,7 @@ struct EpiRelax {
     __device__ float *red0() const { return p.s; }
     __device__ float *red1() const { return p.mag; }
     __device__ const DetSums *det() const { return &p.det; }
-    __device__ Pre pre(const Row &rc, int j) const { return ld(rc.tb, j); }
+    __device__ Pre pre(const Row &rc, int dp, int n, int N) const { return ld(rc.tb, dp * N + n); }
     __device__ void pre2(const Row &, Pre &) const {}
     __device__ void post(const Pre &t, const Row &rc, int, int, int j, float bcol, float g,
                          float &r0, float &r1) const {
@@ -163,6 +164,7 @@ struct EpiRelax {
 struct EpiConc {
     ConcParams p;
     static constexpr int NRED = 2;
+    static constexpr bool WIN = false;
     using Pre = float2;
     struct Row { const float *cen, *rad; float *save, *emit; };
     __device__ Row row(int img) const {
@@ -175,7 +177,9 @@ struct EpiConc {
     __device__ float *red0() const { return p.low; }
     __device__ float *red1() const { return p.mag; }
     __device__ const DetSums *det() const { return &p.det; }
-    __device__ Pre pre(const Row &rc, int j) const { return make_float2(ld(rc.cen, j), ld(rc.rad, j)); }
+    __device__ Pre pre(const Row &rc, int dp, int n, int N) const {
+        return make_float2(ld(rc.cen, dp * N + n), ld(rc.rad, dp * N + n));
+    }
     __device__ void pre2(const Row &, Pre &) const {}
     __device__ void post(const Pre &cr, const Row &rc, int dpix, int n, int j, float, float g,
                          float &r0, float &r1) const {
@@ -190,6 +194,7 @@ struct EpiConc {
 struct EpiAdj {
     AdjParams p;
     static constexpr int NRED = 0;
+    static constexpr bool WIN = false;
     struct Pre { Relax t; float g; };
     struct Row { const Relax *tb; const float *gs; float *go; float *gc; float *gb; float sb; };
     __device__ Row row(int img) const {
@@ -205,7 +210,7 @@ struct EpiAdj {
     // G is saved at the unstable neurons only (slot w - 1), a load that depends on the
     // record: pre() fetches the record, pre2() the saved coefficient.  Elsewhere x = y
     // and z = 0, so the sign of G does not matter.
-    __device__ Pre pre(const Row &rc, int j) const { return Pre{ld(rc.tb, j), 0.f}; }
+    __device__ Pre pre(const Row &rc, int dp, int n, int N) const { return Pre{ld(rc.tb, dp * N + n), 0.f}; }
     __device__ void pre2(const Row &rc, Pre &q) const {
         if (q.t.w > 0.f) q.g = ld(rc.gs, (int)q.t.w - 1);
     }
@@ -228,6 +233,7 @@ struct EpiAdj {
 struct EpiFwd {
     FwdParams p;
     static constexpr int NRED = 0;
+    static constexpr bool WIN = false;
     struct Pre {};
     struct Row { float *out; };
     __device__ Row row(int img) const { return Row{p.out + (long)img * p.D}; }
@@ -235,11 +241,92 @@ struct EpiFwd {
     __device__ float *red0() const { return nullptr; }
     __device__ float *red1() const { return nullptr; }
     __device__ const DetSums *det() const { return nullptr; }
-    __device__ Pre pre(const Row &, int) const { return Pre{}; }
+    __device__ Pre pre(const Row &, int, int, int) const { return Pre{}; }
     __device__ void pre2(const Row &, Pre &) const {}
     __device__ void post(const Pre &, const Row &rc, int, int, int j, float bcol, float acc,
                          float &, float &) const {
         st(rc.out, j, acc + bcol);
+    }
+};
+
+// Origin and records of an img's receptive-field window (WinMap): the img's target pixel
+// (oy, ox) puts window pixel (0, 0) at layer pixel (oy * S - P, ox * S - P).
+struct WinOrg { long inst; int y0, x0; };
+__device__ inline WinOrg win_origin(const WinMap &w, int img) {
+    const long gi = w.img0 + img, inst = ldiv_by(gi, w.rpi, w.rrpi);
+    int r = (int)(gi - inst * w.rpi);
+    r = r >= w.dk ? r - w.dk : r;
+    const int pix = qdiv(r, w.rC), oy = qdiv(pix, w.rOw), ox = pix - oy * w.ow;
+    return WinOrg{inst, oy * w.S - w.P, ox * w.S - w.P};
+}
+// Layer pixel of window pixel dp, -1 outside the layer.
+__device__ inline int win_pixel(const WinMap &w, int y0, int x0, int dp) {
+    const int wy = qdiv(dp, w.rDW), y = y0 + wy, x = x0 + dp - wy * w.DW;
+    return (unsigned)y < (unsigned)w.H && (unsigned)x < (unsigned)w.W ? y * w.W + x : -1;
+}
+
+// Lemma 1 on a window: as EpiRelax without split terms and saved coefficients.  Window
+// pixels outside the layer (and columns past N) take a zero record, so their
+// coefficient is 0 and they add nothing to the sums.
+struct EpiRelaxWin {
+    RelaxParams p;
+    WinMap w;
+    static constexpr int NRED = 2;
+    static constexpr bool WIN = true;
+    using Pre = Relax;
+    struct Row { const Relax *tb; float *out; int y0, x0; };
+    __device__ Row row(int img) const {
+        const WinOrg o = win_origin(w, img);
+        return Row{p.tab + o.inst * p.tab_ld, p.out + (long)img * p.D, o.y0, o.x0};
+    }
+    __device__ float colv(int n) const { return p.bias[n % p.chan]; }
+    __device__ float *red0() const { return p.s; }
+    __device__ float *red1() const { return p.mag; }
+    __device__ const DetSums *det() const { return nullptr; }
+    __device__ Pre pre(const Row &rc, int dp, int n, int N) const {
+        const int px = win_pixel(w, rc.y0, rc.x0, dp);
+        return px >= 0 && n < N ? ld(rc.tb, px * N + n) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    __device__ void pre2(const Row &, Pre &) const {}
+    __device__ void post(const Pre &t, const Row &rc, int, int n, int j, float bcol, float g,
+                         float &r0, float &r1) const {
+        const float lam = g >= 0.f ? g * t.x : g * t.y;
+        const float off = g < 0.f ? g * t.z : 0.f;
+        const float bt = lam * bcol;
+        r0 += bt + off;
+        r1 += fabsf(bt) + fabsf(off);
+        asm volatile("" : "+v"(r0), "+v"(r1));   // in order, as in EpiRelax
+        if (n < w.N) st(rc.out, j, lam);
+    }
+};
+
+// Theorem 2 on a window of the input.
+struct EpiConcWin {
+    ConcParams p;
+    WinMap w;
+    static constexpr int NRED = 2;
+    static constexpr bool WIN = true;
+    using Pre = float2;
+    struct Row { const float *cen, *rad; int y0, x0; };
+    __device__ Row row(int img) const {
+        const WinOrg o = win_origin(w, img);
+        return Row{p.cen + o.inst * p.D, p.rad + o.inst * p.D, o.y0, o.x0};
+    }
+    __device__ float colv(int) const { return 0.f; }
+    __device__ float *red0() const { return p.low; }
+    __device__ float *red1() const { return p.mag; }
+    __device__ const DetSums *det() const { return nullptr; }
+    __device__ Pre pre(const Row &rc, int dp, int n, int N) const {
+        const int px = win_pixel(w, rc.y0, rc.x0, dp);
+        return px >= 0 && n < N ? make_float2(ld(rc.cen, px * N + n), ld(rc.rad, px * N + n))
+                                : make_float2(0.f, 0.f);
+    }
+    __device__ void pre2(const Row &, Pre &) const {}
+    __device__ void post(const Pre &cr, const Row &, int, int, int, float, float g, float &r0,
+                         float &r1) const {
+        r0 += g * cr.x - fabsf(g) * cr.y;
+        r1 += fabsf(g) * (fabsf(cr.x) + cr.y);
+        asm volatile("" : "+v"(r0), "+v"(r1));
     }
 };
 
@@ -318,7 +405,7 @@ __device__ inline void tile_epilogue_impl(const Epi &epi, Acc (&acc)[FM][FN], co
 #pragma unroll
             for (int j = 0; j < FN; ++j)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) pre[j][q] = epi.pre(rw, dp[q] * N + ncol[j]);
+                for (int q = 0; q < 4; ++q) pre[j][q] = epi.pre(rw, dp[q], ncol[j], N);
         };
         auto load2 = [&](PreG &pre) {
 #pragma unroll
@@ -385,7 +472,7 @@ __device__ inline void tile_epilogue_impl(const Epi &epi, Acc (&acc)[FM][FN], co
 #pragma unroll
                         for (int j = 0; j < FN; ++j)
                             if (ncol[j] < N) {
-                                typename Epi::Pre pr = epi.pre(rc, dp[q] * N + ncol[j]);
+                                typename Epi::Pre pr = epi.pre(rc, dp[q], ncol[j], N);
                                 epi.pre2(rc, pr);
                                 epi.post(pr, rc, dp[q], ncol[j], dp[q] * N + ncol[j], bcol[j],
                                          acc[i][j][vg * 4 + q], r0, r1);
@@ -425,7 +512,7 @@ __device__ inline void tile_epilogue_impl(const Epi &epi, Acc (&acc)[FM][FN], co
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
                     if (FAST || (img[q] >= 0 && ncol[j] < N)) {
-                        pre[j][q] = epi.pre(rc[q], dp[q] * N + ncol[j]);
+                        pre[j][q] = epi.pre(rc[q], dp[q], ncol[j], N);
                         epi.pre2(rc[q], pre[j][q]);
                     }
 #pragma unroll
@@ -440,6 +527,59 @@ __device__ inline void tile_epilogue_impl(const Epi &epi, Acc (&acc)[FM][FN], co
                 for (int q = 0; q < 4; ++q)
                     reduce_row<MF>(epi, r0[q], r1[q], img[q], dp[q], ncol[0], lane);
             }
+        }
+    }
+}
+
+// Window tiles whose images are smaller than a wave's 64 rows, but hold whole MF-row
+// fragments: fragment i lies in img fimg[i] (wave-uniform; -1 past the batch, where no
+// later fragment exists either).  Rows are resolved and summed per fragment; the next
+// group's records are in flight while a group is finished, as in the FAST path.
+template <class Epi, int MF, int FM, int FN, class Acc, class RowFn>
+__device__ inline void tile_epilogue_frag(const Epi &epi, Acc (&acc)[FM][FN], const int (&ncol)[FN],
+                                          const float (&bcol)[FN], int N, const RowFn &rowfn4,
+                                          int lane, const int (&fimg)[FM]) {
+    constexpr int NGF = Mma<MF>::NACC / 4, NG = FM * NGF;
+    typename Epi::Row rwA, rwB;
+    typename Epi::Pre preA[FN][4], preB[FN][4];
+    int dpA[4], dpB[4];
+    auto load = [&](int g, typename Epi::Row &rw, int (&dp)[4], typename Epi::Pre (&pre)[FN][4]) {
+        int img[4];
+        if (g % NGF == 0) rw = epi.row(fimg[g / NGF]);
+        rowfn4(g / NGF, g % NGF, img, dp);
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) pre[j][q] = epi.pre(rw, dp[q], ncol[j], N);
+    };
+    if (fimg[0] < 0) return;
+    load(0, rwA, dpA, preA);
+    float u0 = 0.f, u1 = 0.f;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        const int i = g / NGF, vg = g % NGF;
+        const bool more = g + 1 < NG && fimg[(g + 1) / NGF < FM ? (g + 1) / NGF : FM - 1] >= 0;
+        if (more) {
+            rwB = rwA;
+            load(g + 1, rwB, dpB, preB);
+        }
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                epi.post(preA[j][q], rwA, dpA[q], ncol[j], dpA[q] * N + ncol[j], bcol[j],
+                         acc[i][j][vg * 4 + q], u0, u1);
+        if (vg == NGF - 1) {
+            reduce_wave(epi, u0, u1, fimg[i], dpA[0], ncol[0], lane);
+            u0 = u1 = 0.f;
+        }
+        if (!more) return;
+        rwA = rwB;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            dpA[q] = dpB[q];
+#pragma unroll
+            for (int j = 0; j < FN; ++j) preA[j][q] = preB[j][q];
         }
     }
 }
