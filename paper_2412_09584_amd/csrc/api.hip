@@ -154,7 +154,8 @@ struct ProfScope {
 // accumulators are scratch until the normal pass that follows tuning) and keep the
 // fastest.
 template <class F>
-bound_status run_product(bound_net *net, hipStream_t st, int key, const GeomSet &gs, F launch) {
+bound_status run_product(bound_net *net, hipStream_t st, int key, const GeomSet &gs, F launch,
+                         bool keep = false) {
     if (!net->tuning) {
         Plan p;
         if (net->options & BOUND_OPT_GEMM_ONLY) {
@@ -165,6 +166,7 @@ bound_status run_product(bound_net *net, hipStream_t st, int key, const GeomSet 
                 p = it->second;
             else if (net->options & BOUND_OPT_DIRECT_DMA)
                 p.cfg = 1;
+            p.keep = keep;
         }
         HIPCHK(launch(p));
         return BOUND_OK;
@@ -771,6 +773,7 @@ bound_status bound_backward(bound_net *net, const bound_pass *P, const bound_out
     // Full CROWN's pass over a convolutional layer: windows instead of whole layers.  Early
     // stops, split multipliers, coefficient output and the options (tests and
     // comparisons of the whole-layer kernels) keep the general path.
+    const bool keep = save;   // see Plan
     const bool winok = ident && conc && sl == 0 && !inject && net->options == 0 && !net->tuning;
     if (winok && k == 1 && net->layers[0].L.kind == BOUND_CONV2D) {
         IdentityParams ip = identity_params(net, k, rpi, 0);
@@ -897,7 +900,7 @@ bound_status bound_backward(bound_net *net, const bound_pass *P, const bound_out
                         if (e != hipSuccess) return e;
                     }
                     return gemm_relax(gs, A, n_img, rp, st, pl);
-                });
+                }, keep);
                 if (bs != BOUND_OK) return bs;
                 if (rp.det.part)
                     HIPCHK(launch_det_reduce(n_img, rp.det.nslot, rp.det.part, rp.s, rp.mag, st));
@@ -936,7 +939,7 @@ bound_status bound_backward(bound_net *net, const bound_pass *P, const bound_out
                         if (e != hipSuccess) return e;
                     }
                     return gemm_conc(gs, A, n_img, cp, st, pl);
-                });
+                }, keep);
                 if (bs != BOUND_OK) return bs;
                 if (cp.det.part)
                     HIPCHK(launch_det_reduce(n_img, cp.det.nslot, cp.det.part, cp.low, cp.mag, st));
@@ -1085,7 +1088,7 @@ bound_status grad_impl(bound_net *net, int64_t pass_id, int32_t n_inst, int32_t 
                     const float *Ap = A;
                     bound_status bs = run_product(net, st, pkey('R', p), gs, [&](const Plan &pl) {
                         return gemm_relax(gs, Ap, n_img, rp, st, pl);
-                    });
+                    }, true);
                     if (bs != BOUND_OK) return bs;
                 }
                 gseg[p] = rp.save;
@@ -1111,7 +1114,7 @@ bound_status grad_impl(bound_net *net, int64_t pass_id, int32_t n_inst, int32_t 
             const float *A = cur;
             bound_status bs = run_product(net, st, pkey('A', m), li.gF, [&](const Plan &pl) {
                 return gemm_adj(li.gF, A, n_img, ap, st, pl);
-            });
+            }, true);
             if (bs != BOUND_OK) return bs;
             if (ap.gout) bs = debug_check(net, st, ap.gout, n_img * net->d[m], lbl("adj_L%d", m));
             if (bs != BOUND_OK) return bs;

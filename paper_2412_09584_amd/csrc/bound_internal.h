@@ -141,6 +141,11 @@ struct Plan {
     int path = 0;
     int cfg = -1;
     int cc = 0;
+    // automatic plans keep the order in which the general kernels add a row's terms: the
+    // saved coefficients' signs pick the branch of the adjoint, and some of them are within
+    // rounding of 0, so a SAVE_FOR_GRAD pass takes only kernels that give bitwise the same
+    // coefficients, and the adjoint, whose gradients move the next step's slopes, the same
+    bool keep = false;
 };
 constexpr int kMaxCandidates = 32;
 
@@ -164,6 +169,15 @@ hipError_t gemm_adj_cfg(const GeomSet &gs, const float *A, long n_img, const Adj
 hipError_t gemm_fwd_cfg(const GeomSet &gs, const float *A, long n_img, const FwdParams &p,
                         hipStream_t st, int cfg);
 int gemm_candidates(const GeomSet &gs, int *cfgs, int cap);
+// dense.hip: wave-per-tile kernels for dense products with few tiles (configurations that
+// follow the GEMM's); dense_auto picks one, or -1 where the LDS-tiled GEMM serves better
+inline bool is_dense(const Geom &g) { return g.H == 1 && g.W == 1 && g.kh == 1 && g.kw == 1; }
+enum { DENSE_W32 = 11, DENSE_W16 = 12, DENSE_W16K4 = 13, DENSE_W16K16 = 14, DENSE_W16O = 15 };
+int dense_auto(const GeomSet &gs, long M, bool keep);
+hipError_t dense_relax(const GeomSet &gs, const float *A, long M, const RelaxParams &p, hipStream_t st, int cfg);
+hipError_t dense_conc(const GeomSet &gs, const float *A, long M, const ConcParams &p, hipStream_t st, int cfg);
+hipError_t dense_adj(const GeomSet &gs, const float *A, long M, const AdjParams &p, hipStream_t st, int cfg);
+hipError_t dense_fwd(const GeomSet &gs, const float *A, long M, const FwdParams &p, hipStream_t st, int cfg);
 // conv.hip: direct convolution (cc = 0: largest chunk that fits; mode 1 or 3: tiles staged
 // by LDS DMA, else through registers; mode 2 or 3: 16x16 MFMA tiles for 32 output
 // channels); *used = false when the geometry does not fit

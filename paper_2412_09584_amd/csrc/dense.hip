@@ -1,0 +1,189 @@
+// Dense products (Linear layers) with few output tiles: one wave per 16x16 or 32x32 tile.
+//
+// The LDS-tiled GEMM of gemm_kernels.h needs hundreds of 128-wide tiles to fill the chip;
+// with fewer, each of its blocks walks all of K in 16-wide chunks behind two barriers and a
+// memory latency each (a product of 64 rows through a 296x296 layer: 75 us).  Here every
+// wave loads its own A and B operands straight from global memory (L2) into registers,
+// several chunks ahead, so there is no barrier and the chain is MFMA latency: 8 cycles per k
+// with 16x16x4 tiles, 32 with 32x32x2.  Where that chain is long and tiles are few, the KS
+// waves of a block split K and add their tiles through LDS in a fixed order.
+//
+// An FP32 MFMA adds its products one fused multiply-add after the other, k ascending over
+// the lane groups (measured: bitwise equal to a chain of fmaf), so a 16x16x4 tile whose
+// groups are fed k = s, 8 + s, s + 1, 9 + s (ORD) repeats the 32x32x2 kernels' sums bitwise
+// at a quarter of their latency.
+//
+// 82 layers of 128 to 296 columns, 64 rows, pass and gradient: 9.84 -> 1.4 ms; adj_L5 of the
+// CNN (K = 4096, 576 rows): 365 -> 79 us.
+#include "device_common.h"
+
+namespace bp {
+namespace {
+
+using namespace dev;
+
+constexpr int BK = 16;
+
+// 16 bytes at 4-byte alignment (rows of a width that is no multiple of 4)
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// (x0 | y0), (x1 | y1), ... of the lower | upper 32 lanes become (x0 | x1), (y0 | y1), ...
+__device__ inline void swap32(f32x4v &v) {
+#pragma unroll
+    for (int i = 0; i < 4; i += 2) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 1]), false, false);
+        v[i] = __uint_as_float(r[0]);
+        v[i + 1] = __uint_as_float(r[1]);
+    }
+}
+
+template <class Epi, int MF, int KS, bool ORD>
+__global__ __launch_bounds__(KS > 4 ? 64 * KS : 256) void k_dense_wave(const Geom g,
+                                                                      const float *__restrict__ A,
+                                                                      const long M, const Epi epi) {
+    using MM = Mma<MF>;
+    using acc_t = typename MM::acc_t;
+    static_assert(!ORD || MF == 16, "the 32x32x2 order on 16x16x4 tiles");
+    constexpr int KPL = MM::KPL, NACC = MM::NACC, Q = KPL / 4;
+    constexpr int D = KPL == 4 ? 8 : 6;          // chunks in flight (16: no faster)
+    __shared__ float red[KS > 1 ? (KS - 1) * 64 * NACC : 1];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int K = g.K, nt = (g.N + MF - 1) / MF;
+    const TileIdx ti = xcd_tile(KS > 1 ? nt : (nt + 3) / 4, 1);
+    const long m0 = ti.x * MF;
+    const int n0 = (KS > 1 ? ti.y : ti.y * 4 + wave) * MF;
+    if (m0 >= M || n0 >= g.N) return;            // whole waves (KS = 1) or blocks
+    const int nch = (K + BK - 1) / BK;
+    const int c0 = KS > 1 ? nch * wave / KS : 0, c1 = KS > 1 ? nch * (wave + 1) / KS : nch;
+    const long row = m0 + MM::idx(lane);
+    const int grp = MM::grp(lane);
+    // this lane's first k inside a chunk; ORD: groups 0 and 2 hold k 0..3 and 4..7, groups 1
+    // and 3 the same of the upper half
+    const int kl = ORD ? (grp & 1) * 8 + (grp >> 1) * 4 : grp * KPL;
+    const float *a = A + (row < M ? row : M - 1) * (long)K + kl;      // rows past M: dropped
+    const float *b = g.Bt + (long)(n0 + MM::idx(lane)) * g.Kp + kl;   // N is padded to 128 rows
+    // The full chunks [c0, cf) of this wave run through D register slots without a branch
+    // around a load, so the loads stay in flight (past the end they repeat the last
+    // chunk); the ragged chunk, if it is this wave's, has registers of its own.
+    const int nf = K / BK, cf = c1 < nf ? c1 : nf;
+    f32x4v ra[D][Q], rb[D][Q], xa[Q], xb[Q];
+    const bool ragged = c1 > nf;
+    if (ragged) {
+#pragma unroll
+        for (int q = 0; q < KPL; ++q) {
+            const int k = nf * BK + q;
+            xb[q >> 2][q & 3] = b[k];
+            xa[q >> 2][q & 3] = k + kl < K ? a[k] : 0.f;
+        }
+    }
+    auto load = [&](int s, int c) {
+        const int k0 = (c < cf ? c : cf - 1) * BK;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            ra[s][q] = *(const f4u *)(a + k0 + 4 * q);
+            rb[s][q] = *(const f32x4v *)(b + k0 + 4 * q);
+        }
+    };
+    acc_t acc[1][1];
+#pragma unroll
+    for (int v = 0; v < NACC; ++v) acc[0][0][v] = 0.f;
+    auto mul = [&](f32x4v (&x)[Q], f32x4v (&y)[Q]) {
+        if constexpr (ORD) {
+            // step t multiplies k = 2t and 2t + 1 (groups 0 and 2) and 8 more: the half
+            // waves swap their odd and even registers
+            swap32(x[0]);
+            swap32(y[0]);
+            constexpr int at[4] = {0, 2, 1, 3};
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[0][0] = MM::mma(x[0][at[t]], y[0][at[t]], acc[0][0]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < KPL; ++k) acc[0][0] = MM::mma(x[k >> 2][k & 3], y[k >> 2][k & 3], acc[0][0]);
+        }
+    };
+    if (c0 < cf) {
+#pragma unroll
+        for (int s = 0; s < D; ++s) {
+            load(s, c0 + s);
+            __builtin_amdgcn_sched_barrier(0);       // in order: the first one is waited for first
+        }
+        int c = c0;
+        for (; c + D <= cf; c += D) {
+#pragma unroll
+            for (int s = 0; s < D; ++s) {
+                mul(ra[s], rb[s]);
+                load(s, c + s + D);
+                __builtin_amdgcn_sched_barrier(0);   // the loads go out here, not after the MFMAs
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < D; ++s)
+            if (c + s < cf) mul(ra[s], rb[s]);
+    }
+    if (ragged) mul(xa, xb);
+    if constexpr (KS > 1) {
+        if (wave > 0) {
+#pragma unroll
+            for (int v = 0; v < NACC; ++v) red[((wave - 1) * NACC + v) * 64 + lane] = acc[0][0][v];
+        }
+        __syncthreads();
+        if (wave > 0) return;
+        for (int w = 0; w < KS - 1; ++w)
+#pragma unroll
+            for (int v = 0; v < NACC; ++v) acc[0][0][v] += red[(w * NACC + v) * 64 + lane];
+    }
+    dense_tile_epilogue<Epi, MF>(epi, acc[0][0], m0, M, n0, g.N, lane);
+}
+
+template <class Epi, int MF, int KS, bool ORD = false>
+hipError_t launch_wave(const Geom &g, const float *A, long M, const Epi &epi, hipStream_t st) {
+    const long nt = (g.N + MF - 1) / MF, tiles = (M + MF - 1) / MF * (KS > 1 ? nt : (nt + 3) / 4);
+    if (tiles > 0x7fffffffL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_dense_wave<Epi, MF, KS, ORD>), dim3((unsigned)tiles), dim3(KS > 1 ? 64 * KS : 256), 0, st,
+                       g, A, M, epi);
+    return hipGetLastError();
+}
+
+template <class Epi>
+hipError_t run(const GeomSet &gs, const float *A, long M, const Epi &epi, hipStream_t st, int cfg) {
+    const Geom &g = gs.g[0];
+    switch (cfg) {
+    case DENSE_W32: return launch_wave<Epi, 32, 1>(g, A, M, epi, st);
+    case DENSE_W16: return launch_wave<Epi, 16, 1>(g, A, M, epi, st);
+    case DENSE_W16O: return launch_wave<Epi, 16, 1, true>(g, A, M, epi, st);
+    case DENSE_W16K4: return launch_wave<Epi, 16, 4>(g, A, M, epi, st);
+    default: return launch_wave<Epi, 16, 16>(g, A, M, epi, st);
+    }
+}
+
+}  // namespace
+
+int dense_auto(const GeomSet &gs, long M, bool keep) {
+    const Geom &g = gs.g[0];
+    if (!is_dense(g) || M <= 0) return -1;
+    const long big = (M + 127) / 128 * ((g.N + 127) / 128);       // tiles of the LDS-tiled GEMM
+    // one tile per CU: below, the wave kernels are faster (160 tiles, K = 512: 95 -> 63 us; 3
+    // tiles, K = 296: 75 -> 12 us), above they re-read A and B too often (384 tiles of K =
+    // 296: 40 -> 50 us)
+    if (big >= 256) return -1;
+    const long small = (M + 15) / 16 * ((g.N + 15) / 16);
+    // the general GEMM's default tiles are 32x32x2 from 32 columns on
+    if (keep) return g.N < 32 ? DENSE_W16 : (small <= 4096 ? DENSE_W16O : DENSE_W32);
+    if (g.K >= 1024 && small <= 512) return DENSE_W16K16;
+    return g.K > 128 && small <= 4096 ? DENSE_W16K4 : DENSE_W16;
+}
+
+hipError_t dense_relax(const GeomSet &gs, const float *A, long M, const RelaxParams &p, hipStream_t st, int cfg) {
+    return run(gs, A, M, EpiRelax{p}, st, cfg);
+}
+hipError_t dense_conc(const GeomSet &gs, const float *A, long M, const ConcParams &p, hipStream_t st, int cfg) {
+    return run(gs, A, M, EpiConc{p}, st, cfg);
+}
+hipError_t dense_adj(const GeomSet &gs, const float *A, long M, const AdjParams &p, hipStream_t st, int cfg) {
+    return run(gs, A, M, EpiAdj{p}, st, cfg);
+}
+hipError_t dense_fwd(const GeomSet &gs, const float *A, long M, const FwdParams &p, hipStream_t st, int cfg) {
+    return run(gs, A, M, EpiFwd{p}, st, cfg);
+}
+
+}  // namespace bp

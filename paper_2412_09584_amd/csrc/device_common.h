@@ -584,6 +584,72 @@ __device__ inline void tile_epilogue_frag(const Epi &epi, Acc (&acc)[FM][FN], co
     }
 }
 
+// Sums over the MF lanes that share output rows, for the NV = 4 or 16 rows v of a lane at
+// once: each step halves the rows a lane carries by exchanging the other half with its
+// partner, so 16 rows over 32 lanes take 16 shuffles instead of 80.  Returns the sum of the
+// lane's row `r`; lanes of one MF group whose index bits past log2(NV) differ hold the same.
+template <int MF, int NV> __device__ inline float sum_rows(float (&v)[NV], int lane, int &r) {
+    r = 0;
+    int n = NV;
+#pragma unroll
+    for (int mk = MF / 2; mk > 0; mk >>= 1) {
+        if (n > 1) {
+            n >>= 1;
+            const bool up = (lane & mk) != 0;
+            r += up ? n : 0;
+#pragma unroll
+            for (int k = 0; k < NV / 2; ++k)
+                if (k < n) {
+                    const float mine = up ? v[k + n] : v[k], other = up ? v[k] : v[k + n];
+                    v[k] = mine + __shfl_xor(other, mk, 64);
+                }
+        } else {
+            v[0] += __shfl_xor(v[0], mk, 64);
+        }
+    }
+    return v[0];
+}
+
+// Epilogue of a wave that holds one MF x MF tile of a dense product (rows m0 .., M rows in
+// all): every row's records are loaded before the first is used, so the tile pays one memory
+// latency (two for the adjoint's dependent loads) instead of one per group of four rows.
+template <class Epi, int MF, class Acc>
+__device__ inline void dense_tile_epilogue(const Epi &epi, const Acc &acc, long m0, long M, int n0,
+                                           int N, int lane) {
+    using MM = Mma<MF>;
+    constexpr int NACC = MM::NACC;
+    const int n = n0 + MM::col(lane);
+    const bool col = n < N;
+    const float bcol = col ? epi.colv(n) : 0.f;
+    typename Epi::Row rc[NACC];
+    typename Epi::Pre pre[NACC];
+#pragma unroll
+    for (int v = 0; v < NACC; ++v) {
+        const long r = m0 + MM::row(v, lane);
+        if (r < M) {
+            rc[v] = epi.row((int)r);
+            if (col) pre[v] = epi.pre(rc[v], 0, n, N);
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < NACC; ++v)
+        if (col && m0 + MM::row(v, lane) < M) epi.pre2(rc[v], pre[v]);
+    float s0[NACC], s1[NACC];
+#pragma unroll
+    for (int v = 0; v < NACC; ++v) {
+        s0[v] = s1[v] = 0.f;
+        if (col && m0 + MM::row(v, lane) < M)
+            epi.post(pre[v], rc[v], 0, n, n, bcol, acc[v], s0[v], s1[v]);
+    }
+    if constexpr (Epi::NRED > 0) {
+        int v;
+        const float a = sum_rows<MF, NACC>(s0, lane, v), b = sum_rows<MF, NACC>(s1, lane, v);
+        const long r = m0 + MM::row(v, lane);
+        // one of the lanes that hold the row's sum
+        if ((lane & (MF / NACC - 1)) == 0 && r < M) put_row_sums(epi, r, 0, n0, a, b);
+    }
+}
+
 // fast: see tile_epilogue_impl (wave-uniform).
 // LEAN: the other tiles take the one-element-at-a-time path (convolution tiles, where
 // they are rare) instead of the batched one (dense products, where every tile is such).

@@ -16,6 +16,9 @@ int gemm_candidates(const GeomSet &gs, int *cfgs, int cap) {
         if (c >= 9 && !dma) continue;
         if (kCfgBN[c] <= 16 * ((N + 15) / 16) || c == default_cfg(N)) cfgs[n++] = c;
     }
+    // the wave-per-tile kernels (they never repeat padding columns past a tile)
+    for (int c = DENSE_W32; c <= DENSE_W16O && n < cap && is_dense(g); ++c)
+        if (c != DENSE_W16K16 || g.K >= 256) cfgs[n++] = c;
     return n;
 }
 
@@ -48,7 +51,7 @@ int plan_candidates(const GeomSet &gs, Plan *out, int cap) {
     return n;
 }
 
-#define BOUND_PRODUCT(NAME, PARAMS, DIRECT, CFG)                                             \
+#define BOUND_PRODUCT(NAME, PARAMS, DIRECT, CFG, DENSE)                                      \
     hipError_t NAME(const GeomSet &gs, const float *A, long n_img, const PARAMS &p,          \
                     hipStream_t st, const Plan &plan) {                                      \
         if (plan.path != 2) {                                                                \
@@ -56,13 +59,17 @@ int plan_candidates(const GeomSet &gs, Plan *out, int cap) {
             const hipError_t e = DIRECT(gs, A, n_img, p, st, plan.path == 1 ? plan.cc : 0,      \
                                         plan.cfg, &used);                                     \
             if (used || e != hipSuccess) return e;                                           \
+            const int d = plan.path == 0 ? dense_auto(gs, n_img, plan.keep) : -1;            \
+            if (d >= 0) return DENSE(gs, A, n_img, p, st, d);                                \
+        } else if (plan.cfg >= DENSE_W32 && is_dense(gs.g[0])) {                             \
+            return DENSE(gs, A, n_img, p, st, plan.cfg);                                     \
         }                                                                                    \
         return CFG(gs, A, n_img, p, st, plan.path == 2 ? plan.cfg : -1);                     \
     }
-BOUND_PRODUCT(gemm_relax, RelaxParams, direct_relax, gemm_relax_cfg)
-BOUND_PRODUCT(gemm_conc, ConcParams, direct_conc, gemm_conc_cfg)
-BOUND_PRODUCT(gemm_adj, AdjParams, direct_adj, gemm_adj_cfg)
-BOUND_PRODUCT(gemm_fwd, FwdParams, direct_fwd, gemm_fwd_cfg)
+BOUND_PRODUCT(gemm_relax, RelaxParams, direct_relax, gemm_relax_cfg, dense_relax)
+BOUND_PRODUCT(gemm_conc, ConcParams, direct_conc, gemm_conc_cfg, dense_conc)
+BOUND_PRODUCT(gemm_adj, AdjParams, direct_adj, gemm_adj_cfg, dense_adj)
+BOUND_PRODUCT(gemm_fwd, FwdParams, direct_fwd, gemm_fwd_cfg, dense_fwd)
 #undef BOUND_PRODUCT
 
 }  // namespace bp
