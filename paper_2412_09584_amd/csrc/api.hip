@@ -250,6 +250,15 @@ std::string lbl(const char *f, int m) {
     return buf;
 }
 
+// The dense layer's packed weights once more, as three bf16 parts (split.hip).
+bool split_weights(bound_net *net, Geom &g, int Np, hipStream_t st) {
+    unsigned short *bs = nullptr;
+    g.Kc = (int)((g.K + 31) / 32);
+    if (!net->alloc(&bs, (long)Np * g.Kc * 96)) return false;
+    g.Bs = bs;
+    return launch_pack_split(g.Bt, Np, g.Kp, g.Kc, bs, st) == hipSuccess;
+}
+
 bound_status build_geoms(bound_net *net, hipStream_t st) {
     for (int i = 0; i < net->n_layers; ++i) {
         LayerInfo &li = net->layers[i];
@@ -266,6 +275,7 @@ bound_status build_geoms(bound_net *net, hipStream_t st) {
                                  0, 0, 1, 1, t.N, t.K, t.Kp, (int)NpT, bt, st));
             t.Bt = bt;
             set_recips(t);
+            if (!split_weights(net, t, (int)NpT, st)) return fail(BOUND_E_NOMEM, "weight packing");
             li.gT.g[0] = t; li.gT.n = 1;
 
             Geom f{};
@@ -279,6 +289,7 @@ bound_status build_geoms(bound_net *net, hipStream_t st) {
                                  (int)NpF, bf, st));
             f.Bt = bf;
             set_recips(f);
+            if (!split_weights(net, f, (int)NpF, st)) return fail(BOUND_E_NOMEM, "weight packing");
             li.gF.g[0] = f; li.gF.n = 1;
         } else {
             // forward convolution (adjoint)
@@ -1191,7 +1202,7 @@ bound_status sample_bounds(bound_net *net, int32_t n_sub, int32_t per_sub, const
                 const float *A = cur;
                 bound_status bs = run_product(net, st, pkey('F', m), li.gF, [&](const Plan &pl) {
                     return gemm_fwd(li.gF, A, n_img, fp, st, pl);
-                });
+                }, true);
                 if (bs != BOUND_OK) return bs;
             }
             const bool last = m == L;
@@ -1305,7 +1316,7 @@ bound_status bound_set_options(bound_net *net, int32_t options) {
 bound_status bound_set_plan(bound_net *net, char product, int32_t layer, int32_t path,
                             int32_t cfg, int32_t cc) {
     if (!net || (product != 'R' && product != 'C' && product != 'A' && product != 'F') ||
-        layer < 1 || layer > net->n_layers || path < 0 || path > 2 || cfg < -1 || cfg > 15 ||
+        layer < 1 || layer > net->n_layers || path < 0 || path > 2 || cfg < -1 || cfg > 17 ||
         cc < 0 || cc > 1024)
         return fail(BOUND_E_ARG, "bound_set_plan: bad arguments");
     Plan p;

@@ -25,6 +25,8 @@ struct Geom {
     float rC, rKW;             // fl(1 / C), fl(1 / kw)
     double rMd;                // 1 / (OH * OW) in FP64 for row indices beyond 2^21
     const float *Bt;
+    const unsigned short *Bs;  // dense layers: Bt in three bf16 parts, [n][Kc][3][32] (split.hip)
+    int Kc;                    // its 32-wide k chunks
 };
 
 // Reciprocals of a geometry's divisors, taken once on the host (the same correctly
@@ -172,12 +174,19 @@ int gemm_candidates(const GeomSet &gs, int *cfgs, int cap);
 // dense.hip: wave-per-tile kernels for dense products with few tiles (configurations that
 // follow the GEMM's); dense_auto picks one, or -1 where the LDS-tiled GEMM serves better
 inline bool is_dense(const Geom &g) { return g.H == 1 && g.W == 1 && g.kh == 1 && g.kw == 1; }
-enum { DENSE_W32 = 11, DENSE_W16 = 12, DENSE_W16K4 = 13, DENSE_W16K16 = 14, DENSE_W16O = 15 };
+enum { DENSE_W32 = 11, DENSE_W16 = 12, DENSE_W16K4 = 13, DENSE_W16K16 = 14, DENSE_W16O = 15, DENSE_SPLIT = 16, DENSE_F32 = 17 };
 int dense_auto(const GeomSet &gs, long M, bool keep);
 hipError_t dense_relax(const GeomSet &gs, const float *A, long M, const RelaxParams &p, hipStream_t st, int cfg);
 hipError_t dense_conc(const GeomSet &gs, const float *A, long M, const ConcParams &p, hipStream_t st, int cfg);
 hipError_t dense_adj(const GeomSet &gs, const float *A, long M, const AdjParams &p, hipStream_t st, int cfg);
 hipError_t dense_fwd(const GeomSet &gs, const float *A, long M, const FwdParams &p, hipStream_t st, int cfg);
+// split.hip: large dense products, on the bf16 matrix cores at FP32 precision (DENSE_SPLIT) or
+// by FP32 MFMAs in the general GEMM's order (DENSE_F32)
+hipError_t tall_relax(const GeomSet &gs, const float *A, long M, const RelaxParams &p, hipStream_t st, bool split);
+hipError_t tall_conc(const GeomSet &gs, const float *A, long M, const ConcParams &p, hipStream_t st, bool split);
+hipError_t tall_adj(const GeomSet &gs, const float *A, long M, const AdjParams &p, hipStream_t st);
+hipError_t tall_fwd(const GeomSet &gs, const float *A, long M, const FwdParams &p, hipStream_t st, bool split);
+hipError_t launch_pack_split(const float *Bt, int Np, int Kp, int Kc, unsigned short *out, hipStream_t st);
 // conv.hip: direct convolution (cc = 0: largest chunk that fits; mode 1 or 3: tiles staged
 // by LDS DMA, else through registers; mode 2 or 3: 16x16 MFMA tiles for 32 output
 // channels); *used = false when the geometry does not fit

@@ -52,7 +52,8 @@ __global__ __launch_bounds__(KS > 4 ? 64 * KS : 256) void k_dense_wave(const Geo
     const TileIdx ti = xcd_tile(KS > 1 ? nt : (nt + 3) / 4, 1);
     const long m0 = ti.x * MF;
     const int n0 = (KS > 1 ? ti.y : ti.y * 4 + wave) * MF;
-    if (m0 >= M || n0 >= g.N) return;            // whole waves (KS = 1) or blocks
+    if (m0 >= M) return;
+    const bool live = n0 < g.N;                  // KS = 1: the block's last waves may have no tile
     const int nch = (K + BK - 1) / BK;
     const int c0 = KS > 1 ? nch * wave / KS : 0, c1 = KS > 1 ? nch * (wave + 1) / KS : nch;
     const long row = m0 + MM::idx(lane);
@@ -62,12 +63,13 @@ __global__ __launch_bounds__(KS > 4 ? 64 * KS : 256) void k_dense_wave(const Geo
     const int kl = ORD ? (grp & 1) * 8 + (grp >> 1) * 4 : grp * KPL;
     const float *a = A + (row < M ? row : M - 1) * (long)K + kl;      // rows past M: dropped
     const float *b = g.Bt + (long)(n0 + MM::idx(lane)) * g.Kp + kl;   // N is padded to 128 rows
+    __shared__ float sums[Epi::NRED > 0 && KS == 1 ? 4 * MF * 2 : 1];
     // The full chunks [c0, cf) of this wave run through D register slots without a branch
     // around a load, so the loads stay in flight (past the end they repeat the last
     // chunk); the ragged chunk, if it is this wave's, has registers of its own.
     const int nf = K / BK, cf = c1 < nf ? c1 : nf;
     f32x4v ra[D][Q], rb[D][Q], xa[Q], xb[Q];
-    const bool ragged = c1 > nf;
+    const bool ragged = live && c1 > nf;
     if (ragged) {
 #pragma unroll
         for (int q = 0; q < KPL; ++q) {
@@ -101,7 +103,7 @@ __global__ __launch_bounds__(KS > 4 ? 64 * KS : 256) void k_dense_wave(const Geo
             for (int k = 0; k < KPL; ++k) acc[0][0] = MM::mma(x[k >> 2][k & 3], y[k >> 2][k & 3], acc[0][0]);
         }
     };
-    if (c0 < cf) {
+    if (live && c0 < cf) {
 #pragma unroll
         for (int s = 0; s < D; ++s) {
             load(s, c0 + s);
@@ -132,7 +134,29 @@ __global__ __launch_bounds__(KS > 4 ? 64 * KS : 256) void k_dense_wave(const Geo
 #pragma unroll
             for (int v = 0; v < NACC; ++v) acc[0][0][v] += red[(w * NACC + v) * 64 + lane];
     }
-    dense_tile_epilogue<Epi, MF>(epi, acc[0][0], m0, M, n0, g.N, lane);
+    float x = 0.f, y = 0.f;
+    int r = 0;
+    bool own = false;
+    if (live) dense_tile_epilogue<Epi, MF>(epi, acc[0][0], m0, M, n0, g.N, lane, x, y, r, own);
+    if constexpr (Epi::NRED > 0 && KS == 1) {
+        // one pair of sums per row and block: fewer roundings of the row's running sum
+        if (own) {
+            sums[(wave * MF + r) * 2] = x;
+            sums[(wave * MF + r) * 2 + 1] = y;
+        }
+        __syncthreads();
+        const int nw = (g.N - (n0 - wave * MF) + MF - 1) / MF < 4 ? (g.N - (n0 - wave * MF) + MF - 1) / MF : 4;
+        if (threadIdx.x < MF && m0 + threadIdx.x < M) {
+            x = y = 0.f;
+            for (int w = 0; w < nw; ++w) {
+                x += sums[(w * MF + threadIdx.x) * 2];
+                y += sums[(w * MF + threadIdx.x) * 2 + 1];
+            }
+            put_row_sums(epi, m0 + threadIdx.x, 0, n0, x, y);
+        }
+    } else if (own && m0 + r < M) {
+        put_row_sums(epi, m0 + r, 0, n0, x, y);
+    }
 }
 
 template <class Epi, int MF, int KS, bool ORD = false>
@@ -165,24 +189,28 @@ int dense_auto(const GeomSet &gs, long M, bool keep) {
     // one tile per CU: below, the wave kernels are faster (160 tiles, K = 512: 95 -> 63 us; 3
     // tiles, K = 296: 75 -> 12 us), above they re-read A and B too often (384 tiles of K =
     // 296: 40 -> 50 us)
-    if (big >= 256) return -1;
+    if (big >= 256) return keep ? (g.N >= 32 ? DENSE_F32 : -1) : DENSE_SPLIT;
     const long small = (M + 15) / 16 * ((g.N + 15) / 16);
     // the general GEMM's default tiles are 32x32x2 from 32 columns on
     if (keep) return g.N < 32 ? DENSE_W16 : (small <= 4096 ? DENSE_W16O : DENSE_W32);
     if (g.K >= 1024 && small <= 512) return DENSE_W16K16;
-    return g.K > 128 && small <= 4096 ? DENSE_W16K4 : DENSE_W16;
+    return g.K > 128 && small <= 1024 ? DENSE_W16K4 : DENSE_W16;
 }
 
 hipError_t dense_relax(const GeomSet &gs, const float *A, long M, const RelaxParams &p, hipStream_t st, int cfg) {
+    if (cfg >= DENSE_SPLIT) return tall_relax(gs, A, M, p, st, cfg == DENSE_SPLIT);
     return run(gs, A, M, EpiRelax{p}, st, cfg);
 }
 hipError_t dense_conc(const GeomSet &gs, const float *A, long M, const ConcParams &p, hipStream_t st, int cfg) {
+    if (cfg >= DENSE_SPLIT) return tall_conc(gs, A, M, p, st, cfg == DENSE_SPLIT);
     return run(gs, A, M, EpiConc{p}, st, cfg);
 }
 hipError_t dense_adj(const GeomSet &gs, const float *A, long M, const AdjParams &p, hipStream_t st, int cfg) {
+    if (cfg >= DENSE_SPLIT) return tall_adj(gs, A, M, p, st);   // gradients keep the FP32 order
     return run(gs, A, M, EpiAdj{p}, st, cfg);
 }
 hipError_t dense_fwd(const GeomSet &gs, const float *A, long M, const FwdParams &p, hipStream_t st, int cfg) {
+    if (cfg >= DENSE_SPLIT) return tall_fwd(gs, A, M, p, st, cfg == DENSE_SPLIT);
     return run(gs, A, M, EpiFwd{p}, st, cfg);
 }
 

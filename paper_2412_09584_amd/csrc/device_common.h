@@ -66,7 +66,9 @@ __device__ inline TileIdx xcd_tile(int ny, int nz) {
 // than (n + 0.5)/d * 2^-23 < 0.5/d, so truncation gives the exact quotient.
 __device__ inline int qdiv(int n, float rd) { return (int)(((float)n + 0.5f) * rd); }
 __device__ inline long ldiv_by(long n, int d, float rd) {
-    return n < (1L << 21) ? (long)qdiv((int)n, rd) : n / d;
+    // past 2^21 an FP64 quotient of the same form: exact for n < 2^50, and a tenth of the
+    // instructions of a 64-bit integer division
+    return n < (1L << 21) ? (long)qdiv((int)n, rd) : (long)(((double)n + 0.5) / (double)d);
 }
 // The same in FP64 with rd = fl64(1 / d): exact for 0 <= n < 2^50 by the argument above
 // with 2^-52 in place of 2^-23.
@@ -126,12 +128,20 @@ struct EpiRelax {
         const long o = (long)img * p.D;
         return Row{p.tab + inst * p.tab_ld, p.out + o, p.save ? p.save + o : nullptr};
     }
+    // whether n rows from img on share their columns' records
+    __device__ bool one_instance(int img, int n) const {
+        return ldiv_by(p.img0 + img, p.rpi, p.rrpi) == ldiv_by(p.img0 + img + n - 1, p.rpi, p.rrpi);
+    }
+    // the img k after r's, of the same instance
+    __device__ Row at(const Row &r, int k) const {
+        return Row{r.tb, r.out + (long)k * p.D, r.save ? r.save + (long)k * p.D : nullptr};
+    }
     // split multipliers' term of row rc at first split entry q: the row within its
     // instance is recovered from the row's output pointer (only on this rare path, so the
     // common path keeps no extra register per row)
     __device__ float split_term(const Row &rc, int q) const {
-        const long gi = p.img0 + (rc.out - p.out) / p.D;
-        const long r = gi - (gi / p.rpi) * p.rpi;
+        const long gi = p.img0 + (long)((double)(rc.out - p.out) / (double)p.D + 0.5);   // exact multiple
+        const long r = gi - ldiv_by(gi, p.rpi, p.rrpi) * p.rpi;
         return p.bsum[(long)q * p.rpi + r];
     }
     __device__ float colv(int n) const { return p.bias[n % p.chan]; }
@@ -173,6 +183,12 @@ struct EpiConc {
         return Row{p.cen + inst * p.D, p.rad + inst * p.D, p.save ? p.save + o : nullptr,
                    p.emit ? p.emit + o : nullptr};
     }
+    __device__ bool one_instance(int img, int n) const {
+        return ldiv_by(p.img0 + img, p.rpi, p.rrpi) == ldiv_by(p.img0 + img + n - 1, p.rpi, p.rrpi);
+    }
+    __device__ Row at(const Row &r, int k) const {
+        return Row{r.cen, r.rad, r.save ? r.save + (long)k * p.D : nullptr, r.emit ? r.emit + (long)k * p.D : nullptr};
+    }
     __device__ float colv(int) const { return 0.f; }
     __device__ float *red0() const { return p.low; }
     __device__ float *red1() const { return p.mag; }
@@ -203,6 +219,8 @@ struct EpiAdj {
         return Row{p.tab + inst * p.tab_ld, p.gsave + o, p.gout ? p.gout + o : nullptr,
                    p.gc + o, p.gbeta ? p.gbeta + (img - inst * p.rpi) : nullptr, p.sbar[img]};
     }
+    __device__ bool one_instance(int, int) const { return false; }   // saved rows differ
+    __device__ Row at(const Row &r, int) const { return r; }
     __device__ float colv(int n) const { return p.bias[n]; }
     __device__ float *red0() const { return nullptr; }
     __device__ float *red1() const { return nullptr; }
@@ -237,6 +255,8 @@ struct EpiFwd {
     struct Pre {};
     struct Row { float *out; };
     __device__ Row row(int img) const { return Row{p.out + (long)img * p.D}; }
+    __device__ bool one_instance(int, int) const { return true; }
+    __device__ Row at(const Row &r, int k) const { return Row{r.out + (long)k * p.D}; }
     __device__ float colv(int n) const { return p.bias[n]; }
     __device__ float *red0() const { return nullptr; }
     __device__ float *red1() const { return nullptr; }
@@ -613,9 +633,11 @@ template <int MF, int NV> __device__ inline float sum_rows(float (&v)[NV], int l
 // Epilogue of a wave that holds one MF x MF tile of a dense product (rows m0 .., M rows in
 // all): every row's records are loaded before the first is used, so the tile pays one memory
 // latency (two for the adjoint's dependent loads) instead of one per group of four rows.
+// The two sums of a row over the tile's columns go to `a` / `b`, of tile row `r` (each held
+// by several lanes; `own` marks one of them).
 template <class Epi, int MF, class Acc>
 __device__ inline void dense_tile_epilogue(const Epi &epi, const Acc &acc, long m0, long M, int n0,
-                                           int N, int lane) {
+                                           int N, int lane, float &a, float &b, int &r, bool &own) {
     using MM = Mma<MF>;
     constexpr int NACC = MM::NACC;
     const int n = n0 + MM::col(lane);
@@ -641,12 +663,13 @@ __device__ inline void dense_tile_epilogue(const Epi &epi, const Acc &acc, long 
         if (col && m0 + MM::row(v, lane) < M)
             epi.post(pre[v], rc[v], 0, n, n, bcol, acc[v], s0[v], s1[v]);
     }
+    own = false;
     if constexpr (Epi::NRED > 0) {
         int v;
-        const float a = sum_rows<MF, NACC>(s0, lane, v), b = sum_rows<MF, NACC>(s1, lane, v);
-        const long r = m0 + MM::row(v, lane);
-        // one of the lanes that hold the row's sum
-        if ((lane & (MF / NACC - 1)) == 0 && r < M) put_row_sums(epi, r, 0, n0, a, b);
+        a = sum_rows<MF, NACC>(s0, lane, v);
+        b = sum_rows<MF, NACC>(s1, lane, v);
+        r = MM::row(v, lane);
+        own = (lane & (MF / NACC - 1)) == 0;
     }
 }
 

@@ -17,7 +17,7 @@ int gemm_candidates(const GeomSet &gs, int *cfgs, int cap) {
         if (kCfgBN[c] <= 16 * ((N + 15) / 16) || c == default_cfg(N)) cfgs[n++] = c;
     }
     // the wave-per-tile kernels (they never repeat padding columns past a tile)
-    for (int c = DENSE_W32; c <= DENSE_W16O && n < cap && is_dense(g); ++c)
+    for (int c = DENSE_W32; c <= DENSE_F32 && n < cap && is_dense(g); ++c)
         if (c != DENSE_W16K16 || g.K >= 256) cfgs[n++] = c;
     return n;
 }

@@ -14,7 +14,7 @@ from oracle import crown as O
 pytestmark = pytest.mark.gpu
 
 WIDTHS = [(5, 7, 3), (33, 31, 130, 17, 4), (64, 129, 16, 65, 10), (30, 300, 258, 2)]
-CFGS = [11, 12, 13, 14, 15]
+CFGS = [11, 12, 13, 14, 15, 16, 17]
 
 
 def _case(dims, n):
@@ -75,7 +75,7 @@ def test_dense_kernels_match_general_gemm_and_oracle(dims, n):
     assert np.abs(ref[1][i] - oga).max() <= 1e-4 * max(np.abs(oga).max(), 1e-30)
 
 
-@pytest.mark.parametrize("n", [1, 50, 700])
+@pytest.mark.parametrize("n", [1, 50, 700, 9000])
 def test_saving_pass_keeps_its_coefficients(n):
     """Automatic plans of a SAVE_FOR_GRAD pass give the general GEMM's coefficients bitwise, so
     the gradient takes the same branch at every neuron, and the adjoint's automatic plans
@@ -84,7 +84,7 @@ def test_saving_pass_keeps_its_coefficients(n):
     from paper_2412_09584_amd import net as N
     dims, R = (40, 100, 530, 70, 17, 36, 6), 3
     net, x_lo, x_hi, C = _case(dims, n)
-    bn = N.BoundNet(net, n, 4096, n * R)
+    bn = N.BoundNet(net, n, max(4096, n * R), n * R)
     lo, hi = bn.crown_bounds(x_lo, x_hi)
     alpha = torch.as_tensor(W.random_alpha(n, bn.n_relu, 25), device="cuda")
     out = []
