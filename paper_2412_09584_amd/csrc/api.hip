@@ -781,18 +781,25 @@ bound_status bound_backward(bound_net *net, const bound_pass *P, const bound_out
     }
     }
 
-    // Full CROWN's pass over a convolutional layer: windows instead of whole layers.  Early
+    // Full CROWN's passes: z_1 straight from the box, a convolutional layer's rows on windows
+    // instead of whole layers.  Early
     // stops, split multipliers, coefficient output and the options (tests and
     // comparisons of the whole-layer kernels) keep the general path.
     const bool keep = save;   // see Plan
     const bool winok = ident && conc && sl == 0 && !inject && net->options == 0 && !net->tuning;
-    if (winok && k == 1 && net->layers[0].L.kind == BOUND_CONV2D) {
+    if (winok && k == 1) {
         IdentityParams ip = identity_params(net, k, rpi, 0);
+        const Geom &wf = net->layers[0].gF.g[0];
         ip.cen = net->cen;
         ip.rad = net->rad;
-        ProfScope ps(net, st, "conv1_bounds");
-        HIPCHK(launch_conv1_bounds(ip, P->n_inst, slack, out->lower, both ? out->upper : nullptr, ld,
-                                   out->best, both ? out->best_upper : nullptr, st));
+        ProfScope ps(net, st, "first_bounds");
+        if (ip.kind == BOUND_CONV2D)
+            HIPCHK(launch_conv1_bounds(ip, P->n_inst, slack, out->lower, both ? out->upper : nullptr, ld,
+                                       out->best, both ? out->best_upper : nullptr, st));
+        else
+            HIPCHK(launch_dense1_bounds(ip, wf.Bt, wf.Kp, P->n_inst, slack, out->lower,
+                                        both ? out->upper : nullptr, ld, out->best,
+                                        both ? out->best_upper : nullptr, st));
         return BOUND_OK;
     }
     WinPlan wp;
@@ -866,7 +873,13 @@ bound_status bound_backward(bound_net *net, const bound_pass *P, const bound_out
                 ip.bsum = inject ? net->bsum : nullptr;
                 {
                     ProfScope ps(net, st, lbl("init_identity_L%d", k));
-                    HIPCHK(launch_init_identity(ip, n_img, false, st));
+                    // Linear targets: eight rows a wave, reading W's rows in internal order (the
+                    // forward product's packed weights); up to 1024 rows a block per row is
+                    // shorter (200 rows: 6 against 13 us)
+                    const Geom &wf = net->layers[k - 1].gF.g[0];
+                    HIPCHK(ip.kind == BOUND_LINEAR && n_img > 1024
+                               ? launch_init_dense(ip, wf.Bt, wf.Kp, n_img, st)
+                               : launch_init_identity(ip, n_img, false, st));
                 }
                 m_start = k - 1;
             }

@@ -303,6 +303,12 @@ struct IdentityParams {
     float *s, *mag, *low;
 };
 hipError_t launch_init_identity(const IdentityParams &p, long n_img, bool conc, hipStream_t st);
+// identity rows of a Linear target (relaxed), W its rows in internal order with stride ldw
+hipError_t launch_init_dense(const IdentityParams &p, const float *W, int ldw, long n_img, hipStream_t st);
+// lower / upper bounds of z_1 = W x + b over the box (both or lower only)
+hipError_t launch_dense1_bounds(const IdentityParams &p, const float *W, int ldw, int n_inst, bool slack,
+                                float *lower, float *upper, long ld, float *best, float *best_upper,
+                                hipStream_t st);
 // identity rows of a convolutional target as windows of layer k-1 (w: that layer's map)
 hipError_t launch_init_window(const IdentityParams &p, const WinMap &w, long n_img, hipStream_t st);
 // lower / upper bounds of z_1 = conv(x) over the box (both or lower only)

@@ -95,3 +95,22 @@ def test_saving_pass_keeps_its_coefficients(n):
         bn.spec_bounds(C, lo, hi, x_lo, x_hi, alpha=alpha, both=False, save=True)
         out.append(bn.grad(torch.ones(n, R, device="cuda"))[0])
     assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("n,dims,rows", [(1, (5, 7, 3, 2), 64), (3, (70, 130, 261, 9, 4), 300), (40, (16, 64, 33, 65, 3), 1500)])
+def test_identity_rows_of_linear_targets(n, dims, rows):
+    """Full CROWN's identity rows and box bounds of Linear layers: rows and columns around the
+    waves' eight rows and 64 columns, instances cut by the workspace's chunks, both the
+    row-per-block and the eight-rows-per-wave kernels, against the FP64 oracle (1e-4)."""
+    from paper_2412_09584_amd import net as N
+    net, x_lo, x_hi, _ = _case(dims, n)
+    bn = N.BoundNet(net, n, rows)
+    lo, hi = (t.double().cpu().numpy() for t in bn.crown_bounds(x_lo, x_hi))
+    one = N.BoundNet(net, n, 1 << 16)
+    olo, ohi = (t.double().cpu().numpy() for t in one.crown_bounds(x_lo, x_hi))
+    for i in range(0, n, 13):
+        ob = O.crown_bounds(net, x_lo[i], x_hi[i])
+        for side, got in ((0, (lo, olo)), (1, (hi, ohi))):
+            want = np.concatenate([b[side] for b in ob])
+            for g in got:
+                assert np.all(np.abs(g[i] - want) <= 1e-4 * np.maximum(np.abs(want), 1.0))
