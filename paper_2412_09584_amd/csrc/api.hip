@@ -59,7 +59,8 @@ struct bound_net {
     int32_t *slot_inv = nullptr;     // slot -> internal neuron index, per bound row
     int32_t *slot_count = nullptr;   // unstable neurons per (bound row, ReLU layer)
     int32_t *srow = nullptr;         // bound row of each instance
-    float *gcbuf = nullptr;          // per-img alpha-gradient contributions of one layer
+    float *gcbuf = nullptr;          // per-img alpha-gradient contributions, of one layer or
+    bool gc_all = false;             // (gc_all) of every layer
     int32_t *infeas = nullptr;
     float *cen = nullptr, *rad = nullptr;
     float *save = nullptr;
@@ -606,6 +607,9 @@ bound_status bound_init(const bound_layer *layers, int32_t n_layers, int32_t max
     for (int i = 0; i < n_layers; ++i)
         net->max_chan = layers[i].out_c > net->max_chan ? layers[i].out_c : net->max_chan;
 
+    // small workspaces keep every layer's contributions, so that one launch sums them all (82
+    // layers, 64 rows: 81 launches of 5 us); large ones, where a layer fills the chip, one's
+    net->gc_all = max_save_rows * net->n_relu <= (1L << 26);
     bool ok = net->alloc(&net->buf[0], max_rows * net->max_d) &&
               net->alloc(&net->buf[1], max_rows * net->max_d) &&
               net->alloc(&net->acc_s, max_rows) && net->alloc(&net->acc_mag, max_rows) &&
@@ -615,7 +619,7 @@ bound_status bound_init(const bound_layer *layers, int32_t n_layers, int32_t max
               net->alloc(&net->slot_inv, (long)max_inst * (net->n_relu > 0 ? net->n_relu : 1)) &&
               net->alloc(&net->slot_count, (long)max_inst * MAX_RELU_LAYERS) &&
               net->alloc(&net->srow, (long)max_inst) &&
-              net->alloc(&net->gcbuf, max_save_rows * (net->max_relu_d > 0 ? net->max_relu_d : 1)) &&
+              net->alloc(&net->gcbuf, max_save_rows * (net->gc_all ? net->n_relu : net->max_relu_d)) &&
               net->alloc(&net->infeas, max_inst) && net->alloc(&net->cen, (long)max_inst * net->d[0]) &&
               net->alloc(&net->rad, (long)max_inst * net->d[0]) &&
               net->alloc(&net->sbar, max_save_rows > 0 ? max_save_rows : 1) &&
@@ -748,13 +752,16 @@ bound_status bound_backward(bound_net *net, const bound_pass *P, const bound_out
     const long d0 = net->d[0];
     {
     ProfScope prof_prep(net, st, "prep");
-    if (used > 0) {
-        HIPCHK(launch_prep_tables(net->ns, used, P->n_inst, net->n_relu, P->lo, P->hi, P->bound_of,
+    // layers below an early stop are not relaxed
+    const int first = smode == BOUND_STOP_RELU ? sl : (smode == BOUND_STOP_LINEAR ? sl - 1 : 0);
+    BoxParams box{(long)P->n_inst * d0, d0, P->n_inst, net->C0, net->HW0, P->x_lo, P->x_hi,
+                  net->cen, net->rad, used > first ? nullptr : net->infeas};
+    if (used > first)
+        HIPCHK(launch_prep_tables(net->ns, first, used, P->n_inst, net->n_relu, P->lo, P->hi, P->bound_of,
                                   P->alpha, net->tab, net->infeas, P->n_bounds, net->slot,
-                                  net->slot_inv, net->slot_count, net->srow, net->max_inst, st));
-    } else {
-        HIPCHK(launch_fill((float *)net->infeas, P->n_inst, 0.f, st));
-    }
+                                  net->slot_inv, net->slot_count, net->srow, net->max_inst, save, box, st));
+    else
+        HIPCHK(launch_prep_box(box, st));
     if (nnz > 0 && used > 0) {
         if (sl > 0)
             HIPCHK(launch_prep_stop_box(P->n_inst, *SL, net->n_relu, P->lo, P->hi, P->bound_of,
@@ -772,12 +779,6 @@ bound_status bound_backward(bound_net *net, const bound_pass *P, const bound_out
         HIPCHK(launch_prep_stop_box(P->n_inst, *SL, net->n_relu, P->lo, P->hi, P->bound_of,
                                     P->n_bounds, smode == BOUND_STOP_RELU, net->stop_cen,
                                     net->stop_rad, st));
-    }
-    if (conc) {
-        HIPCHK(launch_prep_box(P->n_inst, net->C0, net->HW0, P->x_lo, P->x_hi, net->cen, net->rad, st));
-    } else {
-        HIPCHK(launch_fill(net->cen, (long)P->n_inst * d0, 0.f, st));
-        HIPCHK(launch_fill(net->rad, (long)P->n_inst * d0, 0.f, st));
     }
     }
 
@@ -1034,17 +1035,20 @@ bound_status grad_impl(bound_net *net, int64_t pass_id, int32_t n_inst, int32_t 
         if (grad_alpha) HIPCHK(launch_fill(grad_alpha, (long)net->s_n_inst * net->n_relu, 0.f, st));
         if (grad_beta && net->s_nnz > 0) HIPCHK(launch_fill(grad_beta, (long)net->s_nnz * rows, 0.f, st));
     }
-    // alpha part of ReLU layer `layer` (0-based) from the row contributions in gcbuf
-    auto alpha_part = [&](long D, const LayerShape &S, int layer, long aoff) -> hipError_t {
+    // alpha part of the ReLU layers [l0, l0 + nl) (0-based) from the row contributions in
+    // gcbuf; a layer's own start there is gc_of
+    auto gc_of = [&](int layer) {
+        return net->gc_all ? net->gcbuf + net->max_save_rows * net->relu_off(layer + 1) : net->gcbuf;
+    };
+    auto alpha_part = [&](int l0, int nl) -> hipError_t {
         if (as)
-            return launch_alpha_adam(net->s_n_inst, rows, D, S, layer, net->n_relu, net->srow,
-                                     net->slot_count, net->slot_inv, net->slot, net->gcbuf, as->alpha,
-                                     as->m, as->v, net->n_relu, aoff, (int)net->s_nnz, net->sp,
-                                     net->sp + net->sp_cap, net->sp + 2 * net->sp_cap, aa, st);
-        return launch_alpha_grad(net->s_n_inst, rows, D, S, layer, net->n_relu, net->srow,
-                                 net->slot_count, net->slot_inv, net->gcbuf, grad_alpha, net->n_relu,
-                                 aoff, (int)net->s_nnz, net->sp, net->sp + net->sp_cap,
-                                 net->sp + 2 * net->sp_cap, st);
+            return launch_alpha_adam(net->s_n_inst, rows, net->ns, l0, nl, net->max_save_rows, net->n_relu,
+                                     net->srow, net->slot_count, net->slot_inv, net->slot, gc_of(l0), as->alpha,
+                                     as->m, as->v, net->n_relu, (int)net->s_nnz, net->sp, net->sp + net->sp_cap,
+                                     net->sp + 2 * net->sp_cap, aa, st);
+        return launch_alpha_grad(net->s_n_inst, rows, net->ns, l0, nl, net->max_save_rows, net->n_relu, net->srow,
+                                 net->slot_count, net->slot_inv, gc_of(l0), grad_alpha, net->n_relu,
+                                 (int)net->s_nnz, net->sp, net->sp + net->sp_cap, net->sp + 2 * net->sp_cap, st);
     };
     float *cur = net->buf[0], *nxt = net->buf[1];
     int32_t *sp_inst = net->sp, *sp_layer = net->sp + net->sp_cap, *sp_j = net->sp + 2 * net->sp_cap;
@@ -1060,8 +1064,8 @@ bound_status grad_impl(bound_net *net, int64_t pass_id, int32_t n_inst, int32_t 
                                       net->save + net->s_off[sl + 1], net->stop_cen, net->stop_rad,
                                       grad_lower, net->infeas, net->sbar,
                                       net->tab + net->relu_off(sl), net->n_relu,
-                                      sl + 1 < k ? cur : nullptr, net->gcbuf, S.C, S.HW, st));
-        HIPCHK(alpha_part(Ds, S, sl - 1, net->relu_off(sl)));
+                                      sl + 1 < k ? cur : nullptr, gc_of(sl - 1), S.C, S.HW, st));
+        if (!net->gc_all) HIPCHK(alpha_part(sl - 1, 1));
         if (grad_beta && net->s_nnz > 0)
             HIPCHK(launch_beta_grad_stop(net->s_nnz, rows, sl - 1, Ds, sp_inst, sp_layer, sp_j,
                                          net->sp_sign, net->save + net->s_lam_off, net->stop_cen,
@@ -1128,7 +1132,7 @@ bound_status grad_impl(bound_net *net, int64_t pass_id, int32_t n_inst, int32_t 
         ap.tab = net->tab + net->relu_off(m);
         ap.tab_ld = net->n_relu;
         ap.gout = m + 1 < k ? nxt : nullptr;
-        ap.gc = net->gcbuf;
+        ap.gc = gc_of(m - 1);
         ap.gbeta = grad_beta && net->s_nnz > 0 ? grad_beta : nullptr;
         ap.hw = li.L.out_h * li.L.out_w;
         ap.rpi = rows;
@@ -1143,22 +1147,20 @@ bound_status grad_impl(bound_net *net, int64_t pass_id, int32_t n_inst, int32_t 
             if (ap.gout) bs = debug_check(net, st, ap.gout, n_img * net->d[m], lbl("adj_L%d", m));
             if (bs != BOUND_OK) return bs;
         }
-        {
+        if (!net->gc_all) {
             ProfScope ps(net, st, as ? "alpha_adam" : "alpha_grad");
-            HIPCHK(alpha_part(net->d[m], net->ns.l[m - 1], m - 1, net->relu_off(m)));
-        }
-        if (grad_beta && net->s_nnz > 0) {
-            BetaGradLayer bl{};
-            bl.kind = li.L.kind; bl.W = li.L.weight; bl.bias = li.L.bias;
-            bl.ci = li.L.in_c; bl.hi_ = li.L.in_h; bl.wi = li.L.in_w;
-            bl.co = li.L.out_c; bl.ho = li.L.out_h; bl.wo = li.L.out_w;
-            bl.kh = li.L.kh; bl.kw = li.L.kw; bl.stride = li.L.stride; bl.pad = li.L.pad;
-            bl.din = li.din; bl.dout = li.dout;
-            ProfScope ps(net, st, "beta_grad");
-            HIPCHK(launch_beta_grad(net->s_nnz, rows, m - 1, bl, sp_inst, sp_layer, sp_j, sp_dup, net->sp_sign,
-                                    cur, net->sbar, net->infeas, grad_beta, st));
+            HIPCHK(alpha_part(m - 1, 1));
         }
         float *t = cur; cur = nxt; nxt = t;
+    }
+    if (net->gc_all) {
+        const int l0 = smode == BOUND_STOP_LINEAR ? sl - 1 : m0 - 1;
+        ProfScope ps(net, st, as ? "alpha_adam" : "alpha_grad");
+        HIPCHK(alpha_part(l0, k - 1 - l0));
+    }
+    if (grad_beta && net->s_nnz > 0) {
+        ProfScope ps(net, st, "beta_grad");
+        HIPCHK(launch_beta_repeat(net->s_nnz, rows, sp_inst, sp_layer, sp_j, sp_dup, net->sp_sign, grad_beta, st));
     }
     bound_status bs = as ? debug_check(net, st, as->alpha, (long)net->s_n_inst * net->n_relu, "alpha")
                          : debug_check(net, st, grad_alpha, (long)net->s_n_inst * net->n_relu, "grad_alpha");

@@ -67,84 +67,88 @@ __device__ inline Relax relax_of(float l, float u, float a, int k) {
 // Slots of the unstable neurons of one ReLU layer under one bound row: the unstable
 // neurons in internal order get 0, 1, 2, ... (stable: -1).  The adjoint needs a saved
 // coefficient only where the neuron is unstable, so a pass saves G at these slots only.
-// Block (row r, layer m); each thread counts a contiguous segment, then the segment
-// bases come from a scan of the 256 counts.
-__global__ void k_prep_slots(const LayerShape *ls, long n_relu, const float *lo, const float *hi,
-                             const int32_t *bound_of, int n_bounds, int per_inst, int32_t *slot,
-                             int32_t *inv, int32_t *count) {
-    __shared__ int cnt[256];
+// Block (row r, layer m): the bounds are read contiguously (C-major) and leave one bit per
+// neuron, in internal order, in LDS; a scan over the 64-bit words' counts gives every
+// neuron's slot, written contiguously.  64 bound rows of the 3x32x32 CNN's five layers: 31
+// -> 21 us (threads walked strided segments, one thread scanned).
+constexpr int SLOT_TPB = 1024, SLOT_RANGE = 65536;   // most threads; neurons per sweep (8 KB of bits)
+__global__ __launch_bounds__(SLOT_TPB) void k_prep_slots(const LayerShape *ls, long n_relu, const float *lo,
+                                                         const float *hi, const int32_t *bound_of,
+                                                         int n_bounds, int per_inst, int layer0,
+                                                         int32_t *slot, int32_t *inv, int32_t *count) {
+    __shared__ unsigned long long bits[SLOT_RANGE / 64];
+    __shared__ int base[SLOT_RANGE / 64], wtot[SLOT_TPB / 64];
     const long r = blockIdx.x;
-    const LayerShape L = ls[blockIdx.y];
+    const int nt = blockDim.x;
+    const int layer = layer0 + (int)blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const LayerShape L = ls[layer];
     const long b = per_inst ? bound_row(bound_of, r, n_bounds) : r;
     const float *lr = lo + b * n_relu + L.off, *hr = hi + b * n_relu + L.off;
-    const long seg = (L.d + 255) / 256, j0 = threadIdx.x * seg;
-    const long j1 = j0 + seg < L.d ? j0 + seg : L.d;
-    // unstable flags of n <= 64 neurons from internal index (channel cc, pixel pp) on,
-    // which advances; eight neurons' loads are issued at a time
-    auto flags = [&](int n, int &cc, long &pp) -> uint64_t {
-        uint64_t f = 0;
-        for (int u0 = 0; u0 < n; u0 += 8) {
-            float a[8], h[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const bool ok = u0 + u < n;
-                const long jn = ok ? (long)cc * L.HW + pp : 0;   // index 0 stands in past the end
-                a[u] = lr[jn];
-                h[u] = hr[jn];
-                if (ok && ++cc == L.C) { cc = 0; ++pp; }
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (u0 + u < n && !(a[u] >= 0.f) && !(h[u] <= 0.f)) f |= 1ull << (u0 + u);
-        }
-        return f;
-    };
-    const int cs = j0 < L.d ? (int)(j0 % L.C) : 0;
-    const long ps = j0 < L.d ? j0 / L.C : 0;
-    int c = 0;
-    {
-        int cc = cs;
-        long pp = ps;
-        for (long ja = j0; ja < j1; ja += 64)
-            c += __popcll(flags(j1 - ja < 64 ? (int)(j1 - ja) : 64, cc, pp));
-    }
-    cnt[threadIdx.x] = c;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int run = 0;
-        for (int t = 0; t < 256; ++t) {
-            const int v = cnt[t];
-            cnt[t] = run;
-            run += v;
-        }
-        count[r * MAX_RELU_LAYERS + blockIdx.y] = run;
-    }
-    __syncthreads();
-    int k = cnt[threadIdx.x];
     int32_t *out = slot + r * n_relu + L.off;
     int32_t *back = inv + r * n_relu + L.off;     // slot -> internal index
-    int cc = cs;
-    long pp = ps;
-    for (long ja = j0; ja < j1; ja += 64) {
-        const int n = j1 - ja < 64 ? (int)(j1 - ja) : 64;
-        const uint64_t f = flags(n, cc, pp);
-        for (int u = 0; u < n; ++u) {
-            const bool un = (f >> u) & 1;
-            if (un) back[k] = (int32_t)(ja + u);
-            out[ja + u] = un ? k++ : -1;
+    int run = 0;                                  // unstable neurons of the sweeps before
+    for (long j0 = 0; j0 < L.d; j0 += SLOT_RANGE) {
+        const int n = (int)(L.d - j0 < SLOT_RANGE ? L.d - j0 : SLOT_RANGE), nw = (n + 63) / 64;
+        for (int w = tid; w < nw; w += nt) bits[w] = 0;
+        __syncthreads();
+        for (long e = tid; e < L.d; e += nt) {
+            if (lr[e] >= 0.f || hr[e] <= 0.f) continue;
+            const unsigned c = (unsigned)e / (unsigned)L.HW, p = (unsigned)e - c * (unsigned)L.HW;
+            const long j = (long)p * L.C + c - j0;
+            if (j >= 0 && j < n) atomicOr(&bits[j >> 6], 1ull << (j & 63));
         }
+        __syncthreads();
+        // exclusive scan of the words' counts: a contiguous run of words per thread
+        const int per = (nw + nt - 1) / nt, w0 = tid * per;
+        int c = 0;
+        for (int w = w0; w < w0 + per && w < nw; ++w) c += __popcll(bits[w]);
+        int incl = c;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int o = __shfl_up(incl, d, 64);
+            if (lane >= d) incl += o;
+        }
+        if (lane == 63) wtot[wv] = incl;
+        __syncthreads();
+        int before = run + incl - c, total = 0;
+        for (int w = 0; w < nt / 64; ++w) {
+            if (w < wv) before += wtot[w];
+            total += wtot[w];
+        }
+        for (int w = w0; w < w0 + per && w < nw; ++w) {
+            base[w] = before;
+            before += __popcll(bits[w]);
+        }
+        __syncthreads();
+        for (int j = tid; j < n; j += nt) {
+            const unsigned long long w = bits[j >> 6];
+            const int bit = j & 63;
+            int k = -1;
+            if ((w >> bit) & 1) {
+                k = base[j >> 6] + __popcll(w & ((1ull << bit) - 1));
+                back[k] = (int32_t)(j0 + j);
+            }
+            out[j0 + j] = k;
+        }
+        run += total;
+        __syncthreads();
     }
+    if (tid == 0) count[r * MAX_RELU_LAYERS + layer] = run;
 }
 
 // alpha-gradient of ReLU layer L: the adjoint product left each img's contributions
 // [G >= 0] G Lambda_bar at the compact slots of its unstable neurons (gc, row stride D);
 // one block per instance walks its slots, sums the instance's rows and stores the
 // result at the neuron's C-major index.  Slots of split neurons (w = 0) are skipped.
-__global__ void k_alpha_grad(int rows, long D, const LayerShape L, int layer, long n_relu,
+__global__ void k_alpha_grad(int rows, const LayerShape *ls, int layer0, long gc_rows, long n_relu,
                              const int32_t *srow, const int32_t *count, const int32_t *inv,
-                             const float *gc, float *galpha, long ga_ld, long ga_off) {
+                             const float *gc, float *galpha, long ga_ld) {
     const long inst = blockIdx.x;
     const long r = srow[inst];
+    const int layer = layer0 + (int)blockIdx.y;
+    const LayerShape L = ls[layer];
+    const long D = L.d, ga_off = L.off;
+    gc += gc_rows * (L.off - ls[layer0].off);
     const int cnt = count[r * MAX_RELU_LAYERS + layer];
     const int32_t *iv = inv + r * n_relu + L.off;
     const float *g = gc + inst * rows * D;
@@ -171,13 +175,14 @@ __global__ void k_alpha_grad(int rows, long D, const LayerShape L, int layer, lo
 
 // The alpha-gradient of a split neuron is 0 (its relaxation has no alpha): one thread per
 // split entry of the layer.
-__global__ void k_alpha_split_zero(int nnz, int layer, const LayerShape L, const int32_t *sp_inst,
+__global__ void k_alpha_split_zero(int nnz, int layer0, int layers, const LayerShape *ls, const int32_t *sp_inst,
                                    const int32_t *sp_layer, const int32_t *sp_j, float *galpha,
-                                   long ga_ld, long ga_off) {
+                                   long ga_ld) {
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= nnz || sp_layer[q] != layer) return;
+    if (q >= nnz || sp_layer[q] < layer0 || sp_layer[q] >= layer0 + layers) return;
+    const LayerShape L = ls[sp_layer[q]];
     const int j = sp_j[q], c = j % L.C, p = j / L.C;
-    galpha[(long)sp_inst[q] * ga_ld + ga_off + (long)c * L.HW + p] = 0.f;
+    galpha[(long)sp_inst[q] * ga_ld + L.off + (long)c * L.HW + p] = 0.f;
 }
 
 __global__ void k_count_nonfinite(const float *p, long n, int32_t *cnt) {
@@ -202,6 +207,31 @@ __global__ void k_fill4(float4 *p, long n4, float v) {
     if (i < n4) p[i] = make_float4(v, v, v, v);
 }
 
+// Centre and radius of input element e (internal order); without a box 0, as the
+// coefficient form needs; infeas is cleared along where no tables are built.
+__device__ inline void prep_box(const BoxParams &b, long e) {
+    if (b.infeas && e < b.n_inst) b.infeas[e] = 0;
+    if (e >= b.total) return;
+    if (!b.x_lo) {
+        b.cen[e] = b.rad[e] = 0.f;
+        return;
+    }
+    // 32-bit quotients whenever the launch has fewer than 2^31 elements
+    long inst, j;
+    if (b.total < 0x7fffffffL) {
+        inst = (unsigned)e / (unsigned)b.d0;
+        j = (unsigned)e - (unsigned)inst * (unsigned)b.d0;
+    } else {
+        inst = e / b.d0;
+        j = e - inst * b.d0;
+    }
+    const unsigned p = (unsigned)j / (unsigned)b.C0, c = (unsigned)j - p * (unsigned)b.C0;
+    const long jn = (long)c * b.HW0 + p;
+    const float lo = b.x_lo[inst * b.d0 + jn], hi = b.x_hi[inst * b.d0 + jn];
+    b.cen[e] = 0.5f * (lo + hi);
+    b.rad[e] = 0.5f * (hi - lo);
+}
+
 // Relaxation records of one instance: a block covers a tile of one ReLU layer -- P
 // pixels x all C channels of a convolutional layer (C <= PREP_TILE), or PREP_TILE
 // consecutive neurons of a dense one -- and moves the bounds and alpha, stored C-major,
@@ -210,18 +240,25 @@ __global__ void k_fill4(float4 *p, long n4, float v) {
 // take one pixel's channels per block with direct (strided) reads.
 constexpr int PREP_SH = PREP_TILE + PREP_TILE / 8;  // room for one pad per pixel when C >= 8
 
+template <bool SAVE>
 __global__ __launch_bounds__(256) void k_prep_tables(const LayerShape *ls, const int32_t *tile0,
                                                      int used, long n_relu,
                                                      const float *lo, const float *hi,
                                                      const int32_t *bound_of, const float *alpha,
                                                      Relax *tab, int32_t *infeas, int n_bounds,
                                                      const int32_t *slot, int per_inst,
-                                                     int32_t *srow, int tiles) {
+                                                     int32_t *srow, int tiles, int tile_first,
+                                                     long n_tab, const BoxParams bx) {
     __shared__ float sh[3 * PREP_SH];
+    // the blocks past the tables' form the input boxes' centres and radii
+    if (blockIdx.x >= n_tab) {
+        prep_box(bx, ((long)blockIdx.x - n_tab) * 256 + threadIdx.x);
+        return;
+    }
     // consecutive blocks take consecutive tiles of one instance, so the blocks in flight
     // write one contiguous stretch of the record table (and share one bounds row)
     const long inst = blockIdx.x / (unsigned)tiles;
-    const int t0 = (int)(blockIdx.x - inst * tiles);
+    const int t0 = tile_first + (int)(blockIdx.x - inst * tiles);
     if (t0 >= tile0[used]) return;
     // the tile's layer: the last m < used with tile0[m] <= t0
     int m = 0, mb = used - 1;
@@ -233,13 +270,14 @@ __global__ __launch_bounds__(256) void k_prep_tables(const LayerShape *ls, const
     const int t = t0 - tile0[m];
     const LayerShape L = ls[m];
     const long b = bound_row(bound_of, inst, n_bounds);
-    if (t0 == 0 && threadIdx.x == 0) {
+    if (t0 == tile_first && threadIdx.x == 0) {
         infeas[inst] = 0;
         srow[inst] = per_inst ? (int32_t)inst : (int32_t)b;
     }
     const float *lr = lo + b * n_relu + L.off, *hr = hi + b * n_relu + L.off;
     const float *ar = alpha ? alpha + inst * n_relu + L.off : nullptr;
-    const int32_t *kr = slot + (per_inst ? inst : b) * n_relu + L.off;
+    // without slots (a pass that saves nothing) an unstable record carries w = 1
+    const int32_t *kr = SAVE ? slot + (per_inst ? inst : b) * n_relu + L.off : nullptr;
     Relax *tr = tab + inst * n_relu + L.off;
     auto record = [&](long j, float l, float u, float a, int32_t k) {
         if (!ar) a = u >= -l ? 1.f : 0.f;
@@ -252,7 +290,7 @@ __global__ __launch_bounds__(256) void k_prep_tables(const LayerShape *ls, const
         const long j0 = (long)t * PREP_TILE;
         for (int e = threadIdx.x; e < PREP_TILE; e += 256) {
             const long j = j0 + e;
-            if (j < L.d) record(j, lr[j], hr[j], ar ? ar[j] : 0.f, kr[j]);
+            if (j < L.d) record(j, lr[j], hr[j], ar ? ar[j] : 0.f, SAVE ? kr[j] : 0);
         }
         return;
     }
@@ -261,7 +299,8 @@ __global__ __launch_bounds__(256) void k_prep_tables(const LayerShape *ls, const
         const int p = t / nch, c0 = (t - p * nch) * PREP_TILE;
         for (int e = threadIdx.x; e < PREP_TILE && c0 + e < L.C; e += 256) {
             const long jn = (long)(c0 + e) * L.HW + p;
-            record((long)p * L.C + c0 + e, lr[jn], hr[jn], ar ? ar[jn] : 0.f, kr[(long)p * L.C + c0 + e]);
+            record((long)p * L.C + c0 + e, lr[jn], hr[jn], ar ? ar[jn] : 0.f,
+                   SAVE ? kr[(long)p * L.C + c0 + e] : 0);
         }
         return;
     }
@@ -270,6 +309,7 @@ __global__ __launch_bounds__(256) void k_prep_tables(const LayerShape *ls, const
     const int CS = C >= 8 ? C + 1 : C;                // LDS pixel stride, odd when padded
     const float rP = 1.0f / (float)P, rC = 1.0f / (float)C;
     constexpr int PER = PREP_TILE / 256;
+    const float *av = ar ? ar : lr;                   // record() ignores it without alpha
     // C-major reads: e -> (c, pixel p0 + q), contiguous in q; all of a thread's loads are
     // issued before the first LDS store
     float vl[PER], vh[PER], va[PER];
@@ -279,14 +319,12 @@ __global__ __launch_bounds__(256) void k_prep_tables(const LayerShape *ls, const
         const int e = threadIdx.x + k * 256;
         // e / P through one FP32 multiply by fl(1 / P): exact for e < 2^21
         const int c = (int)(((float)e + 0.5f) * rP), q = e - c * P;
-        vs[k] = -1;
-        if (e < C * P && q < np) {
-            const long jn = (long)c * L.HW + p0 + q;
-            vs[k] = q * CS + c;
-            vl[k] = lr[jn];
-            vh[k] = hr[jn];
-            va[k] = ar ? ar[jn] : 0.f;
-        }
+        vs[k] = e < C * P && q < np ? q * CS + c : -1;
+        // clamped rather than guarded, so that no branch stands between the loads
+        const long jn = (long)(c < C ? c : C - 1) * L.HW + p0 + (q < np ? q : np - 1);
+        vl[k] = lr[jn];
+        vh[k] = hr[jn];
+        va[k] = av[jn];
     }
 #pragma unroll
     for (int k = 0; k < PER; ++k)
@@ -301,7 +339,7 @@ __global__ __launch_bounds__(256) void k_prep_tables(const LayerShape *ls, const
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int e = threadIdx.x + k * 256;
-        ks[k] = e < np * C ? kr[(long)p0 * C + e] : 0;
+        ks[k] = SAVE ? kr[(long)p0 * C + (e < np * C ? e : np * C - 1)] : 0;
     }
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
@@ -313,18 +351,33 @@ __global__ __launch_bounds__(256) void k_prep_tables(const LayerShape *ls, const
     }
 }
 
+// One wave per instance, a lane per split entry; lists of up to 64 entries compare their
+// neurons through the lanes' registers instead of reading the list once per entry.
 __global__ void k_prep_splits(const LayerShape *ls, int used, long T, int n_inst, long n_relu,
                               const float *lo, const float *hi, const int32_t *bound_of,
                               const int32_t *off, const int32_t *idx, const int8_t *sign,
                               Relax *tab, int32_t *infeas, int32_t *sp_inst, int32_t *sp_layer,
                               int32_t *sp_j, int32_t *sp_dup, int n_bounds, int stop_m,
                               int stop_relu, float *stop_cen, float *stop_rad) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (i >= n_inst) return;
     const long b = bound_row(bound_of, i, n_bounds);
     const int q0 = off[i], q1 = off[i + 1];
-    for (int q = q0; q < q1; ++q) {
-        const long g = idx[q];
+    const bool small = q1 - q0 <= 64;
+    const int myi = small && q0 + lane < q1 ? idx[q0 + lane] : -1;
+    const int mys = small && q0 + lane < q1 ? sign[q0 + lane] : 0;
+    for (int q = q0 + lane; q - lane < q1; q += 64) {       // whole wave: lanes past q1 only lend registers
+        const long g = small ? myi : (q < q1 ? idx[q] : -1);
+        int first = q, pos = 0, neg = 0;
+        for (int q2 = q0; q2 < q1; ++q2) {
+            const int gi = small ? __shfl(myi, q2 - q0, 64) : idx[q2];
+            const int sg = small ? __shfl(mys, q2 - q0, 64) : sign[q2];
+            if (gi != g) continue;
+            if (q2 < first) first = q2;
+            pos |= sg > 0;
+            neg |= sg <= 0;
+        }
+        if (q >= q1) continue;
         sp_inst[q] = i;
         sp_layer[q] = -1;
         sp_j[q] = 0;
@@ -334,13 +387,8 @@ __global__ void k_prep_splits(const LayerShape *ls, int used, long T, int n_inst
         const LayerShape L = ls[m];
         const long jn = g - L.off;
         float l = lo[b * n_relu + g], u = hi[b * n_relu + g];
-        int first = q;
-        for (int q2 = q0; q2 < q1; ++q2) {
-            if (idx[q2] != g) continue;
-            if (q2 < first) first = q2;
-            if (sign[q2] > 0) l = fmaxf(l, 0.f);
-            else u = fminf(u, 0.f);
-        }
+        if (pos) l = fmaxf(l, 0.f);
+        if (neg) u = fminf(u, 0.f);
         if (l > u) infeas[i] = 1;
         const long j = to_internal(jn, L.C, L.HW);
         // a split neuron's record carries w = -(q + 1), q its first entry in the
@@ -350,7 +398,7 @@ __global__ void k_prep_splits(const LayerShape *ls, int used, long T, int n_inst
         const float zs = sign[first] < 0 ? -0.0f : 0.0f;
         tab[(long)i * n_relu + L.off + j] = l >= 0.f ? make_float4(1.f, 1.f, zs, wq)
                                                      : make_float4(0.f, 0.f, zs, wq);
-        sp_dup[q] = first != q;   // a repeated entry: k_beta_grad computes it
+        sp_dup[q] = first != q;   // a repeated entry: k_beta_repeat copies its gradient
         if (m == stop_m && stop_cen) {  // the early-stop node's box sees the clamp too
             const float a = stop_relu ? fmaxf(l, 0.f) : l, c = stop_relu ? fmaxf(u, 0.f) : u;
             stop_cen[(long)i * L.d + j] = 0.5f * (a + c);
@@ -380,52 +428,39 @@ __global__ void k_prep_stop_box(long total, LayerShape L, long n_relu, const flo
     rad[e] = 0.5f * (u - l);
 }
 
-// I: the index type, 32-bit unsigned whenever the launch has fewer than 2^31 elements
-// (cheaper quotients), else long.
-template <class I>
-__global__ void k_prep_box(long total, long d0, int C0, int HW0, const float *x_lo,
-                           const float *x_hi, float *cen, float *rad) {
-    const I e = (I)blockIdx.x * (I)blockDim.x + (I)threadIdx.x;
-    if ((long)e >= total) return;
-    const I inst = e / (I)d0, j = e - inst * (I)d0;
-    const long jn = (long)(j % (I)C0) * HW0 + (long)(j / (I)C0);
-    const float a = x_lo[inst * d0 + jn], b = x_hi[inst * d0 + jn];
-    cen[e] = 0.5f * (a + b);
-    rad[e] = 0.5f * (b - a);
+__global__ void k_prep_box(const BoxParams bx) {
+    prep_box(bx, (long)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
-__global__ void k_init_spec(long img0, long n_img, int rows, int rpi, const float *spec, long dk,
-                            int Ck, int HWk, float *lam) {
-    const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n_img * dk) return;
-    const long li = e / dk, j = e - li * dk;
-    const long gimg = img0 + li;
-    const long inst = gimg / rpi;
-    const int rr = (int)(gimg - inst * rpi);
-    const float sg = rr < rows ? 1.f : -1.f;
-    const int r = rr < rows ? rr : rr - rows;
-    lam[e] = sg * spec[(inst * rows + r) * dk + to_cmajor(j, Ck, HWk)];
-}
-
-__global__ void k_init_spec_acc(long img0, long n_img, int rows, int rpi, const float *spec,
-                                long dk, int HWk, const float *bias_k, float *s, float *mag,
-                                float *low) {
-    const long li = blockIdx.x;
+// Spec rows: coefficients in internal order and the target's bias terms; TPI threads an img
+// (a wave, or a block where the target is wide).
+template <int TPI>
+__global__ __launch_bounds__(256) void k_init_spec(long img0, long n_img, int rows, int rpi, const float *spec,
+                                                   long dk, int Ck, int HWk, const float *bias_k, float *lam,
+                                                   float *s, float *mag, float *low) {
+    const long li = (long)blockIdx.x * (256 / TPI) + threadIdx.x / TPI;
+    const int t0 = threadIdx.x & (TPI - 1);
     if (li >= n_img) return;
     const long gimg = img0 + li;
     const long inst = gimg / rpi;
     const int rr = (int)(gimg - inst * rpi);
     const float sg = rr < rows ? 1.f : -1.f;
-    const int r = rr < rows ? rr : rr - rows;
-    const float *row = spec + (inst * rows + r) * dk;
+    const float *row = spec + (inst * rows + (rr < rows ? rr : rr - rows)) * dk;
     float a = 0.f, b = 0.f;
-    for (long jn = threadIdx.x; jn < dk; jn += blockDim.x) {
-        const float t = row[jn] * bias_k[jn / HWk];
+    for (long j = t0; j < dk; j += TPI) {
+        const unsigned p = (unsigned)j / (unsigned)Ck, c = (unsigned)j - p * (unsigned)Ck;
+        const float w = row[(long)c * HWk + p], t = w * bias_k[c];
+        lam[li * dk + j] = sg * w;
         a += t;
         b += fabsf(t);
     }
-    block_sum2(a, b);
-    if (threadIdx.x == 0) {
+    if (TPI == 256) {
+        block_sum2(a, b);
+    } else {
+        a = wave_sum(a);
+        b = wave_sum(b);
+    }
+    if (t0 == 0) {
         s[li] = sg * a;
         mag[li] = b;
         low[li] = 0.f;
@@ -806,52 +841,21 @@ __global__ void k_adj_init4(long n_img, int rows, long d0, const float *gl, cons
         make_float4(one(g.x, c.x, r.x), one(g.y, c.y, r.y), one(g.z, c.z, r.z), one(g.w, c.w, r.w));
 }
 
-__global__ void k_beta_grad(int nnz, int rows, int layer, const BetaGradLayer L,
-                            const int32_t *sp_inst, const int32_t *sp_layer, const int32_t *sp_j,
-                            const int32_t *sp_dup, const int8_t *sign, const float *gbar_m,
-                            const float *sbar, float *gbeta) {
-    // one wave per split entry, its rows in turn: most entries leave at once
-    const long q = ((long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int lane = threadIdx.x & 63;
-    if (q >= nnz) return;
-    // first entries of a neuron get their gradient in the adjoint product's epilogue
-    if (sp_layer[q] != layer || !sp_dup[q]) return;
-    for (int r = 0; r < rows; ++r) {
-        const long img = (long)sp_inst[q] * rows + r;
-        const float *gb = gbar_m + img * L.din;
-        const long j = sp_j[q];
-        float acc = 0.f;
-        int bidx;
-        if (L.kind == 0) {
-            const int hwin = L.hi_ * L.wi;
-            const float *wrow = L.W + j * L.din;
-            for (long k = lane; k < L.din; k += 64) {
-                const long pix = k / L.ci;
-                const int c = (int)(k - pix * L.ci);
-                acc += gb[k] * wrow[(long)c * hwin + pix];
-            }
-            bidx = (int)j;
-        } else {
-            const long pix = j / L.co;
-            const int co = (int)(j - pix * L.co);
-            const int oy = (int)(pix / L.wo), ox = (int)(pix - (long)oy * L.wo);
-            const int taps = L.kh * L.kw * L.ci;
-            for (int t = lane; t < taps; t += 64) {
-                const int ci = t % L.ci, kk = t / L.ci;
-                const int ky = kk / L.kw, kx = kk - ky * L.kw;
-                const int y = oy * L.stride - L.pad + ky, x = ox * L.stride - L.pad + kx;
-                if (y < 0 || y >= L.hi_ || x < 0 || x >= L.wi) continue;
-                acc += gb[((long)y * L.wi + x) * L.ci + ci] *
-                       L.W[(((long)co * L.ci + ci) * L.kh + ky) * L.kw + kx];
-            }
-            bidx = co;
+// beta-gradient of repeated split entries: their neuron's first entry holds -sign *
+// Lambda_bar already (the adjoint's epilogue wrote it), so a repeat takes it with the two
+// signs' product.  One thread per entry and row; most leave at once.
+__global__ void k_beta_repeat(int nnz, int rows, const int32_t *sp_inst, const int32_t *sp_layer,
+                              const int32_t *sp_j, const int32_t *sp_dup, const int8_t *sign, float *gbeta) {
+    const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= (long)nnz * rows) return;
+    const int q = (int)(e / rows), r = (int)(e - (long)q * rows);
+    if (sp_layer[q] < 0 || !sp_dup[q]) return;
+    for (int f = q - 1; f >= 0 && sp_inst[f] == sp_inst[q]; --f)
+        if (!sp_dup[f] && sp_layer[f] == sp_layer[q] && sp_j[f] == sp_j[q]) {
+            const float g = gbeta[(long)f * rows + r];
+            gbeta[e] = (sign[f] < 0) == (sign[q] < 0) ? g : -g;
+            return;
         }
-        acc = wave_sum(acc);
-        if (lane == 0) {
-            const float lam_bar = acc + sbar[img] * L.bias[bidx];
-            gbeta[q * rows + r] = -(float)sign[q] * lam_bar;
-        }
-    }
 }
 
 // lower/mag[img] += sum_j lam c - |lam| r, sum_j |lam| (|c| + r) over one row of internal-order
@@ -994,28 +998,33 @@ __global__ void k_adam(long n, float *p, const float *g, float *m, float *v, con
 // Split neurons keep the slot they have as unstable neurons but take no alpha: their
 // slots' row contributions are cleared, so the fused step below sees a zero gradient
 // there, as the dense gradient has.  One thread per (split entry, row).
-__global__ void k_split_gc_zero(int nnz, int rows, int layer, long D, long n_relu, long off,
-                                const int32_t *sp_inst, const int32_t *sp_layer,
+__global__ void k_split_gc_zero(int nnz, int rows, int layer0, int layers, const LayerShape *ls, long gc_rows,
+                                long n_relu, const int32_t *sp_inst, const int32_t *sp_layer,
                                 const int32_t *sp_j, const int32_t *srow, const int32_t *slot,
                                 float *gc) {
     const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= (long)nnz * rows) return;
     const int q = (int)(t / rows), r = (int)(t - (long)q * rows);
-    if (sp_layer[q] != layer) return;
+    if (sp_layer[q] < layer0 || sp_layer[q] >= layer0 + layers) return;
+    const LayerShape L = ls[sp_layer[q]];
     const long inst = sp_inst[q];
-    const int s = slot[(long)srow[inst] * n_relu + off + sp_j[q]];
-    if (s >= 0) gc[(inst * rows + r) * D + s] = 0.f;
+    const int s = slot[(long)srow[inst] * n_relu + L.off + sp_j[q]];
+    if (s >= 0) gc[gc_rows * (L.off - ls[layer0].off) + (inst * rows + r) * L.d + s] = 0.f;
 }
 
 // alpha-gradient of ReLU layer L fused with the Adam step on alpha: as k_alpha_grad, the
 // block of an instance sums its rows' contributions at each slot (in the same order),
 // then steps the neuron's alpha (C-major index) with moments kept at the slot's index.
-__global__ void k_alpha_adam(int rows, long D, const LayerShape L, int layer, long n_relu,
+__global__ void k_alpha_adam(int rows, const LayerShape *ls, int layer0, long gc_rows, long n_relu,
                              const int32_t *srow, const int32_t *count, const int32_t *inv,
-                             const float *gc, float *alpha, float *m, float *v, long ld, long aoff,
+                             const float *gc, float *alpha, float *m, float *v, long ld,
                              const AdamArgs a) {
     const long inst = blockIdx.x;
     const long r = srow[inst];
+    const int layer = layer0 + (int)blockIdx.y;
+    const LayerShape L = ls[layer];
+    const long D = L.d, aoff = L.off;
+    gc += gc_rows * (L.off - ls[layer0].off);
     const int cnt = count[r * MAX_RELU_LAYERS + layer];
     const int32_t *iv = inv + r * n_relu + L.off;
     const float *g = gc + inst * rows * D;
@@ -1193,39 +1202,43 @@ hipError_t launch_fill(float *p, long n, float v, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_prep_tables(const NetShapes &ns, int used, int n_inst, long n_relu,
+hipError_t launch_prep_tables(const NetShapes &ns, int first, int used, int n_inst, long n_relu,
                               const float *lo, const float *hi, const int32_t *bound_of,
                               const float *alpha, Relax *tab, int32_t *infeas, int n_bounds,
                               int32_t *slot, int32_t *slot_inv, int32_t *slot_count,
-                              int32_t *srow, int max_rows, hipStream_t st) {
-    const long T = used > 0 ? ns.l[used - 1].off + ns.l[used - 1].d : 0;
-    if (T == 0) return launch_fill((float *)infeas, n_inst, 0.f, st);  // 0.0f is all-zero bits
+                              int32_t *srow, int max_rows, bool save, const BoxParams &box, hipStream_t st) {
     // slots per bound row when the rows fit the slot table, else per instance
     const bool per_inst = bound_of == nullptr || n_bounds > max_rows;
     const int rows = per_inst ? n_inst : n_bounds;
-    hipLaunchKernelGGL(k_prep_slots, dim3((unsigned)rows, (unsigned)used), dim3(256), 0, st, ns.dev,
-                       n_relu, lo, hi, bound_of, n_bounds, per_inst ? 1 : 0, slot, slot_inv,
-                       slot_count);
-    long tiles = 0;
-    for (int m = 0; m < used; ++m) tiles += prep_tiles(ns.l[m]);
-    if (tiles * n_inst > 0x7fffffffL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_prep_tables, dim3((unsigned)(tiles * n_inst)), dim3(256), 0, st, ns.dev,
-                       ns.tile0, used, n_relu, lo, hi, bound_of, alpha, tab, infeas, n_bounds, slot,
-                       per_inst ? 1 : 0, srow, (int)tiles);
+    long dmax = 0;
+    for (int m = first; m < used; ++m) dmax = ns.l[m].d > dmax ? ns.l[m].d : dmax;
+    if (save)
+        hipLaunchKernelGGL(k_prep_slots, dim3((unsigned)rows, (unsigned)(used - first)),
+                           dim3(dmax > 4096 ? SLOT_TPB : 256), 0, st,
+                           ns.dev, n_relu, lo, hi, bound_of, n_bounds, per_inst ? 1 : 0, first, slot, slot_inv,
+                           slot_count);
+    long tiles = 0, tile_first = 0;
+    for (int m = 0; m < used; ++m) (m < first ? tile_first : tiles) += prep_tiles(ns.l[m]);
+    const long n_tab = tiles * n_inst, n_box = (box.total + TPB - 1) / TPB;
+    if (n_tab + n_box > 0x7fffffffL) return hipErrorInvalidValue;
+    const auto f = save ? k_prep_tables<true> : k_prep_tables<false>;
+    hipLaunchKernelGGL(f, dim3((unsigned)(n_tab + n_box)), dim3(256), 0, st, ns.dev, ns.tile0, used, n_relu, lo, hi,
+                       bound_of, alpha, tab, infeas, n_bounds, slot, per_inst ? 1 : 0, srow, (int)tiles,
+                       (int)tile_first, n_tab, box);
     return hipGetLastError();
 }
 
-hipError_t launch_alpha_grad(int n_inst, int rows, long D, const LayerShape &L, int layer,
+hipError_t launch_alpha_grad(int n_inst, int rows, const NetShapes &ns, int layer0, int layers, long gc_rows,
                              long n_relu, const int32_t *srow, const int32_t *slot_count,
-                             const int32_t *slot_inv, const float *gc, float *galpha, long ga_ld,
-                             long ga_off, int nnz, const int32_t *sp_inst, const int32_t *sp_layer,
-                             const int32_t *sp_j, hipStream_t st) {
-    if (n_inst <= 0 || D <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_alpha_grad, dim3((unsigned)n_inst), dim3(TPB), 0, st, rows, D, L, layer,
-                       n_relu, srow, slot_count, slot_inv, gc, galpha, ga_ld, ga_off);
+                             const int32_t *slot_inv, const float *gc, float *galpha, long ga_ld, int nnz,
+                             const int32_t *sp_inst, const int32_t *sp_layer, const int32_t *sp_j,
+                             hipStream_t st) {
+    if (n_inst <= 0 || layers <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_alpha_grad, dim3((unsigned)n_inst, (unsigned)layers), dim3(TPB), 0, st, rows, ns.dev,
+                       layer0, gc_rows, n_relu, srow, slot_count, slot_inv, gc, galpha, ga_ld);
     if (nnz > 0)
-        hipLaunchKernelGGL(k_alpha_split_zero, dim3(blocks_for(nnz)), dim3(TPB), 0, st, nnz, layer, L,
-                           sp_inst, sp_layer, sp_j, galpha, ga_ld, ga_off);
+        hipLaunchKernelGGL(k_alpha_split_zero, dim3(blocks_for(nnz)), dim3(TPB), 0, st, nnz, layer0, layers,
+                           ns.dev, sp_inst, sp_layer, sp_j, galpha, ga_ld);
     return hipGetLastError();
 }
 
@@ -1236,31 +1249,27 @@ hipError_t launch_prep_splits(const NetShapes &ns, int used, int n_inst, long n_
                               int32_t *sp_j, int32_t *sp_dup, int n_bounds, int stop_m,
                               int stop_relu, float *stop_cen, float *stop_rad, hipStream_t st) {
     const long T = used > 0 ? ns.l[used - 1].off + ns.l[used - 1].d : 0;
-    hipLaunchKernelGGL(k_prep_splits, dim3(blocks_for(n_inst, 64)), dim3(64), 0, st, ns.dev, used, T,
+    hipLaunchKernelGGL(k_prep_splits, dim3(blocks_for(n_inst, 4)), dim3(TPB), 0, st, ns.dev, used, T,
                        n_inst, n_relu, lo, hi, bound_of, off, idx, sign, tab, infeas, sp_inst,
                        sp_layer, sp_j, sp_dup, n_bounds, stop_m, stop_relu, stop_cen, stop_rad);
     return hipGetLastError();
 }
 
-hipError_t launch_prep_box(int n_inst, int C0, int HW0, const float *x_lo, const float *x_hi,
-                           float *cen, float *rad, hipStream_t st) {
-    const long d0 = (long)C0 * HW0, total = d0 * n_inst;
-    if (total < 0x7fffffffL)
-        hipLaunchKernelGGL(k_prep_box<unsigned>, dim3(blocks_for(total)), dim3(TPB), 0, st, total,
-                           d0, C0, HW0, x_lo, x_hi, cen, rad);
-    else
-        hipLaunchKernelGGL(k_prep_box<long>, dim3(blocks_for(total)), dim3(TPB), 0, st, total, d0,
-                           C0, HW0, x_lo, x_hi, cen, rad);
+hipError_t launch_prep_box(const BoxParams &box, hipStream_t st) {
+    const long n = box.total > box.n_inst ? box.total : box.n_inst;
+    hipLaunchKernelGGL(k_prep_box, dim3(blocks_for(n)), dim3(TPB), 0, st, box);
     return hipGetLastError();
 }
 
 hipError_t launch_init_spec(long img0, long n_img, int rows, int rpi, const float *spec, long dk,
                             int Ck, int HWk, const float *bias_k, float *lam, float *s,
                             float *mag, float *low, hipStream_t st) {
-    hipLaunchKernelGGL(k_init_spec, dim3(blocks_for(n_img * dk)), dim3(TPB), 0, st, img0, n_img,
-                       rows, rpi, spec, dk, Ck, HWk, lam);
-    hipLaunchKernelGGL(k_init_spec_acc, dim3((unsigned)n_img), dim3(TPB), 0, st, img0, n_img, rows,
-                       rpi, spec, dk, HWk, bias_k, s, mag, low);
+    if (dk > 256)
+        hipLaunchKernelGGL(k_init_spec<256>, dim3((unsigned)n_img), dim3(TPB), 0, st, img0, n_img, rows, rpi,
+                           spec, dk, Ck, HWk, bias_k, lam, s, mag, low);
+    else
+        hipLaunchKernelGGL(k_init_spec<64>, dim3(blocks_for(n_img, 4)), dim3(TPB), 0, st, img0, n_img, rows, rpi,
+                           spec, dk, Ck, HWk, bias_k, lam, s, mag, low);
     return hipGetLastError();
 }
 
@@ -1337,14 +1346,13 @@ hipError_t launch_adj_init(long n_img, int rows, long d0, const float *gl, const
     return hipGetLastError();
 }
 
-hipError_t launch_beta_grad(int nnz, int rows, int layer, const BetaGradLayer &L,
-                            const int32_t *sp_inst, const int32_t *sp_layer, const int32_t *sp_j,
-                            const int32_t *sp_dup, const int8_t *sign, const float *gbar_m,
-                            const float *sbar, const int32_t *, float *gbeta, hipStream_t st) {
-    const long waves = nnz;
-    if (waves == 0 || rows == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_beta_grad, dim3(blocks_for(waves * 64)), dim3(TPB), 0, st, nnz, rows,
-                       layer, L, sp_inst, sp_layer, sp_j, sp_dup, sign, gbar_m, sbar, gbeta);
+hipError_t launch_beta_repeat(int nnz, int rows, const int32_t *sp_inst, const int32_t *sp_layer,
+                              const int32_t *sp_j, const int32_t *sp_dup, const int8_t *sign, float *gbeta,
+                              hipStream_t st) {
+    const long total = (long)nnz * rows;
+    if (total == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_beta_repeat, dim3(blocks_for(total)), dim3(TPB), 0, st, nnz, rows, sp_inst, sp_layer,
+                       sp_j, sp_dup, sign, gbeta);
     return hipGetLastError();
 }
 
@@ -1426,20 +1434,19 @@ hipError_t launch_adam(long n, float *p, const float *g, float *m, float *v, int
     return hipGetLastError();
 }
 
-hipError_t launch_alpha_adam(int n_inst, int rows, long D, const LayerShape &L, int layer,
+hipError_t launch_alpha_adam(int n_inst, int rows, const NetShapes &ns, int layer0, int layers, long gc_rows,
                              long n_relu, const int32_t *srow, const int32_t *slot_count,
                              const int32_t *slot_inv, const int32_t *slot, float *gc, float *alpha,
-                             float *m, float *v, long ld, long aoff, int nnz,
-                             const int32_t *sp_inst, const int32_t *sp_layer, const int32_t *sp_j,
-                             const AdamArgs &a, hipStream_t st) {
-    if (n_inst <= 0 || D <= 0) return hipSuccess;
+                             float *m, float *v, long ld, int nnz, const int32_t *sp_inst,
+                             const int32_t *sp_layer, const int32_t *sp_j, const AdamArgs &a, hipStream_t st) {
+    if (n_inst <= 0 || layers <= 0) return hipSuccess;
     if (nnz > 0) {
         const long nt = (long)nnz * rows;
-        hipLaunchKernelGGL(k_split_gc_zero, dim3(blocks_for(nt)), dim3(TPB), 0, st, nnz, rows, layer,
-                           D, n_relu, (long)L.off, sp_inst, sp_layer, sp_j, srow, slot, gc);
+        hipLaunchKernelGGL(k_split_gc_zero, dim3(blocks_for(nt)), dim3(TPB), 0, st, nnz, rows, layer0, layers,
+                           ns.dev, gc_rows, n_relu, sp_inst, sp_layer, sp_j, srow, slot, gc);
     }
-    hipLaunchKernelGGL(k_alpha_adam, dim3((unsigned)n_inst), dim3(TPB), 0, st, rows, D, L, layer,
-                       n_relu, srow, slot_count, slot_inv, gc, alpha, m, v, ld, aoff, a);
+    hipLaunchKernelGGL(k_alpha_adam, dim3((unsigned)n_inst, (unsigned)layers), dim3(TPB), 0, st, rows, ns.dev,
+                       layer0, gc_rows, n_relu, srow, slot_count, slot_inv, gc, alpha, m, v, ld, a);
     return hipGetLastError();
 }
 

@@ -240,18 +240,31 @@ hipError_t launch_det_reduce(long n_img, long nslot, const float *part, float *s
                              hipStream_t st);
 // cnt[0] += NaN count, cnt[1] += Inf count of p[0 .. n) (debug checks)
 hipError_t launch_count_nonfinite(const float *p, long n, int32_t *cnt, hipStream_t st);
-hipError_t launch_prep_tables(const NetShapes &ns, int n_layers_used, int n_inst,
+// input boxes -> centre / radius in internal order (x_lo null: zeros); infeas (nullable):
+// cleared for n_inst instances
+struct BoxParams {
+    long total, d0;          // n_inst * d0 elements
+    int n_inst, C0, HW0;
+    const float *x_lo, *x_hi;
+    float *cen, *rad;
+    int32_t *infeas;
+};
+// relaxation tables of ReLU layers [first, used), their slots when the pass saves, and the box
+hipError_t launch_prep_tables(const NetShapes &ns, int first, int used, int n_inst,
                               long n_relu, const float *lo, const float *hi,
                               const int32_t *bound_of, const float *alpha, Relax *tab,
                               int32_t *infeas, int n_bounds, int32_t *slot, int32_t *slot_inv,
-                              int32_t *slot_count, int32_t *srow, int max_rows, hipStream_t st);
-// alpha-gradient of one layer from the compact per-row contributions gc (sum over an
-// instance's rows per slot, written C-major), then 0 at the layer's split neurons
-hipError_t launch_alpha_grad(int n_inst, int rows, long D, const LayerShape &L, int layer,
+                              int32_t *slot_count, int32_t *srow, int max_rows, bool save,
+                              const BoxParams &box, hipStream_t st);
+hipError_t launch_prep_box(const BoxParams &box, hipStream_t st);
+// alpha-gradient of the ReLU layers [layer0, layer0 + layers) from the compact per-row
+// contributions gc (sum over an instance's rows per slot, written C-major), then 0 at the
+// layers' split neurons; layer l's rows start at gc + gc_rows * (off_l - off_layer0)
+hipError_t launch_alpha_grad(int n_inst, int rows, const NetShapes &ns, int layer0, int layers, long gc_rows,
                              long n_relu, const int32_t *srow, const int32_t *slot_count,
-                             const int32_t *slot_inv, const float *gc, float *galpha, long ga_ld,
-                             long ga_off, int nnz, const int32_t *sp_inst, const int32_t *sp_layer,
-                             const int32_t *sp_j, hipStream_t st);
+                             const int32_t *slot_inv, const float *gc, float *galpha, long ga_ld, int nnz,
+                             const int32_t *sp_inst, const int32_t *sp_layer, const int32_t *sp_j,
+                             hipStream_t st);
 hipError_t launch_prep_splits(const NetShapes &ns, int n_layers_used, int n_inst, long n_relu,
                               const float *lo, const float *hi, const int32_t *bound_of,
                               const int32_t *off, const int32_t *idx, const int8_t *sign,
@@ -272,8 +285,6 @@ hipError_t launch_beta_grad_stop(int nnz, int rows, int layer, long D, const int
                                  const int32_t *sp_layer, const int32_t *sp_j, const int8_t *sign,
                                  const float *lam, const float *cen, const float *rad,
                                  const float *sbar, float *gbeta, hipStream_t st);
-hipError_t launch_prep_box(int n_inst, int C0, int HW0, const float *x_lo, const float *x_hi,
-                           float *cen, float *rad, hipStream_t st);
 hipError_t launch_init_spec(long img0, long n_img, int rows, int rpi, const float *spec,
                             long dk, int Ck, int HWk, const float *bias_k, float *lam,
                             float *s, float *mag, float *low, hipStream_t st);
@@ -329,18 +340,10 @@ hipError_t launch_adj_init(long n_img, int rows, long d0, const float *gl, const
                            const float *cen, const float *rad, const int32_t *infeas,
                            float *gbar, float *sbar, hipStream_t st);
 
-struct BetaGradLayer {         // layer m, for the split-multiplier gradient
-    int kind;
-    const float *W;            // user weight (C-major)
-    const float *bias;
-    int ci, hi_, wi, co, ho, wo, kh, kw, stride, pad;
-    long din, dout;
-};
-hipError_t launch_beta_grad(int nnz, int rows, int layer, const BetaGradLayer &L,
-                            const int32_t *sp_inst, const int32_t *sp_layer,
-                            const int32_t *sp_j, const int32_t *sp_dup, const int8_t *sign,
-                            const float *gbar_m, const float *gl, const int32_t *infeas,
-                            float *gbeta, hipStream_t st);
+// beta-gradient of repeated split entries from their neurons' first entries
+hipError_t launch_beta_repeat(int nnz, int rows, const int32_t *sp_inst, const int32_t *sp_layer,
+                              const int32_t *sp_j, const int32_t *sp_dup, const int8_t *sign, float *gbeta,
+                              hipStream_t st);
 hipError_t launch_to_internal(long n_img, int C, int HW, const float *x, float *y, hipStream_t st);
 hipError_t launch_sample_minmax(long n_sub, int per_sub, long D, int C, int HW, float *z,
                                 float *lo, float *hi, long ld, bool relu, float *out, bool merge,
@@ -353,14 +356,13 @@ struct AdamArgs {
     float b1, b2, bc1, bc2s, lr, eps, gs, lo, hi;
 };
 AdamArgs adam_args(int step, float lr, float b1, float b2, float eps, float gs, float lo, float hi);
-// alpha-gradient of one ReLU layer fused with the Adam step on alpha (moments in slot
-// order); clears split neurons' slots of gc first
-hipError_t launch_alpha_adam(int n_inst, int rows, long D, const LayerShape &L, int layer,
+// alpha-gradient of ReLU layers (as launch_alpha_grad) fused with the Adam step on alpha
+// (moments in slot order); clears split neurons' slots of gc first
+hipError_t launch_alpha_adam(int n_inst, int rows, const NetShapes &ns, int layer0, int layers, long gc_rows,
                              long n_relu, const int32_t *srow, const int32_t *slot_count,
                              const int32_t *slot_inv, const int32_t *slot, float *gc, float *alpha,
-                             float *m, float *v, long ld, long aoff, int nnz,
-                             const int32_t *sp_inst, const int32_t *sp_layer, const int32_t *sp_j,
-                             const AdamArgs &a, hipStream_t st);
+                             float *m, float *v, long ld, int nnz, const int32_t *sp_inst,
+                             const int32_t *sp_layer, const int32_t *sp_j, const AdamArgs &a, hipStream_t st);
 hipError_t launch_concretize(int n_inst, int rows, long d0, const float *coeff,
                              const float *offset, const float *offset_mag, const float *x_lo,
                              const float *x_hi, bool slack, float *lower, hipStream_t st);
