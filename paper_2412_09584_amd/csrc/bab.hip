@@ -416,6 +416,293 @@ __global__ __launch_bounds__(TPB) void k_prune_scatter(int n, const float *f_lo,
     }
 }
 
+// ---- pick-out and pruning of up to ONE_MAX subdomains by one block.  Wave w holds the
+// subdomains from w * 64 * rounds on, round it's lane l the one at 64 it + l; flags of them
+// are bits of a word per lane, and their keys stay in registers over the whole selection: a
+// device-wide sort of 60000 pairs takes a dozen dependent launches for the same picks.  What
+// bounds it is the one unit's instruction rate, and its LDS in the histograms, where every
+// lane has 16-bit counters of its own: the leading byte of FP32 keys takes few values, and a
+// shared bin would serialise the wave.  Pick-out of 1024 from 60000, split, best and pruner:
+// 223 -> 148 us (keys in memory and one histogram: 200 us).  Larger sets and picks keep the
+// device-wide sort.
+constexpr int ONE_T = 1024, ONE_PER = 64, ONE_MAX = ONE_T * ONE_PER, ONE_SORT = 4096;
+
+// order-preserving bits of a comparison key
+__device__ inline unsigned order_bits(float x) {
+    const unsigned u = __float_as_uint(canon(x));
+    return u ^ ((u >> 31) ? 0xffffffffu : 0x80000000u);
+}
+
+struct OneShared {
+    union {
+        unsigned hist[128 * 64];                // [bin / 2][lane], two 16-bit counters (<= 1024)
+        unsigned long long sort[ONE_SORT];
+    };
+    int wave[ONE_T / 64];
+    float fmin[ONE_T / 64], fmax[ONE_T / 64];
+    int bin, less, n;
+};
+
+// Exclusive scan over the block of one value per thread.
+__device__ inline int block_scan(OneShared &sh, int v, int &total) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    int incl = v;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int o = __shfl_up(incl, d, 64);
+        if (lane >= d) incl += o;
+    }
+    if (lane == 63) sh.wave[wv] = incl;
+    __syncthreads();
+    int before = 0;
+    total = 0;
+    for (int w = 0; w < ONE_T / 64; ++w) {
+        if (w < wv) before += sh.wave[w];
+        total += sh.wave[w];
+    }
+    __syncthreads();
+    return before + incl - v;
+}
+
+// A wave's first subdomain, of n in rounds of 64 a wave.
+__device__ inline int one_first(int rounds) { return (int)(threadIdx.x >> 6) * 64 * rounds + (threadIdx.x & 63); }
+
+// Positions, in index order, of the flagged subdomains (bit `it` of flags): calls
+// put(it, position) for each; returns how many there are.
+template <class Put> __device__ inline int ordered(OneShared &sh, unsigned long long flags, Put put) {
+    const int lane = threadIdx.x & 63;
+    int total, pos = block_scan(sh, __popcll(flags), total);
+    pos = __builtin_amdgcn_readfirstlane(pos);                  // the wave's first position
+    unsigned lo = (unsigned)flags, hi = (unsigned)(flags >> 32);
+    for (int m = 1; m < 64; m <<= 1) {
+        lo |= __shfl_xor(lo, m, 64);
+        hi |= __shfl_xor(hi, m, 64);
+    }
+    const unsigned long long below = lane ? (~0ull >> (64 - lane)) : 0ull;
+    // the rounds in which any lane has a flag
+    unsigned long long any = ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane(hi) << 32) |
+                             (unsigned)__builtin_amdgcn_readfirstlane(lo);
+    for (; any; any &= any - 1) {
+        const int it = __builtin_ctzll(any);
+        const bool f = (flags >> it) & 1;
+        const unsigned long long m = __ballot(f);
+        if (f) put(it, pos + __popcll(m & below));
+        pos += __popcll(m);
+    }
+    return total;
+}
+
+// The want (<= ONE_SORT) smallest (key, index) pairs, ascending, to out; taken gets their
+// bits.  At least want keys are below ONE_NONE, which stands for no subdomain (comparison
+// keys end at +inf).  Radix selection of the want-th key, a byte a pass, then a bitonic sort
+// of the selected.
+constexpr unsigned ONE_NONE = 0xffffffffu;
+template <int PER>
+__device__ void one_select(OneShared &sh, const unsigned (&key)[PER], int rounds, int want, int32_t *out,
+                           unsigned long long &taken) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    unsigned prefix = 0, mask = 0;
+    int need = want;
+    for (int shift = 24; shift >= 0; shift -= 8) {
+        for (int q = tid; q < 128 * 64; q += ONE_T) sh.hist[q] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < PER; ++it)
+            if ((key[it] & mask) == prefix) {
+                const unsigned bin = (key[it] >> shift) & 255;
+                atomicAdd(&sh.hist[(bin >> 1) * 64 + lane], bin & 1 ? 1u << 16 : 1u);
+            }
+        __syncthreads();
+        // eight threads a pair of bins; the rotation spreads a wave's eight pairs over the banks
+        const int pair = tid >> 3;
+        int h0 = 0, h1 = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const unsigned c = sh.hist[pair * 64 + (tid & 7) * 8 + ((i + pair) & 7)];
+            h0 += c & 0xffff;
+            h1 += c >> 16;
+        }
+#pragma unroll
+        for (int m = 1; m < 8; m <<= 1) {
+            h0 += __shfl_xor(h0, m, 64);
+            h1 += __shfl_xor(h1, m, 64);
+        }
+        int total;
+        const int before = block_scan(sh, tid & 7 ? 0 : h0 + h1, total);
+        if ((tid & 7) == 0 && before < need && need <= before + h0 + h1) {
+            const bool second = need > before + h0;
+            sh.bin = 2 * pair + (second ? 1 : 0);
+            sh.less = before + (second ? h0 : 0);
+        }
+        __syncthreads();
+        prefix |= (unsigned)sh.bin << shift;
+        mask |= 255u << shift;
+        need -= sh.less;
+    }
+    // keys below the want-th, and the first `need` in index order of those equal to it
+    unsigned long long sel = 0, eq = 0;
+#pragma unroll
+    for (int it = 0; it < PER; ++it) {
+        sel |= key[it] < prefix ? 1ull << it : 0;
+        eq |= key[it] == prefix ? 1ull << it : 0;
+    }
+    ordered(sh, eq, [&](int it, int pos) {
+        if (pos < need) sel |= 1ull << it;
+    });
+    int P2 = 1;
+    while (P2 < want) P2 <<= 1;
+    for (int q = want + tid; q < P2; q += ONE_T) sh.sort[q] = ~0ull;
+    if (tid == 0) sh.n = 0;
+    __syncthreads();
+    // one atomic a thread reserves its places; the sort puts them in order
+    int at = sel ? atomicAdd(&sh.n, __popcll(sel)) : 0;
+#pragma unroll
+    for (int it = 0; it < PER; ++it)
+        if ((sel >> it) & 1) sh.sort[at++] = ((unsigned long long)key[it] << 32) | (unsigned)(one_first(rounds) + it * 64);
+    __syncthreads();
+    if (P2 <= ONE_T) {
+        // an element a thread: strides inside a wave are register exchanges
+        unsigned long long x = tid < P2 ? sh.sort[tid] : ~0ull;
+        for (int size = 2; size <= P2; size <<= 1)
+            for (int stride = size >> 1; stride > 0; stride >>= 1) {
+                unsigned long long y;
+                if (stride >= 64) {
+                    if (tid < P2) sh.sort[tid] = x;
+                    __syncthreads();
+                    y = tid < P2 ? sh.sort[tid ^ stride] : x;
+                    __syncthreads();
+                } else {
+                    y = __shfl_xor(x, stride, 64);
+                }
+                const bool up = (tid & size) == 0, lower = (tid & stride) == 0;
+                if ((x > y) == (up == lower)) x = y;
+            }
+        if (tid < want) out[tid] = (int32_t)(unsigned)x;
+    } else {
+        for (int size = 2; size <= P2; size <<= 1)
+            for (int stride = size >> 1; stride > 0; stride >>= 1) {
+                for (int q = tid; q < P2 / 2; q += ONE_T) {
+                    const int a = 2 * q - (q & (stride - 1)), c = a + stride;
+                    const unsigned long long x = sh.sort[a], y = sh.sort[c];
+                    if ((x > y) == ((a & size) == 0)) {
+                        sh.sort[a] = y;
+                        sh.sort[c] = x;
+                    }
+                }
+                __syncthreads();
+            }
+        for (int q = tid; q < want; q += ONE_T) out[q] = (int32_t)(unsigned)sh.sort[q];
+    }
+    __syncthreads();
+    taken |= sel;
+}
+
+template <int PER>
+__global__ __launch_bounds__(ONE_T) void k_pick_one(int n_dom, int n1, int n, const float *f_lo,
+                                                    const float *f_hi, const float *gum, float inv_t,
+                                                    int32_t *picked, int32_t *rest) {
+#pragma clang fp contract(off)   // s * inv_t and the subtraction rounded separately
+    __shared__ OneShared sh;
+    const int tid = threadIdx.x, rounds = (n_dom + ONE_T - 1) / ONE_T;   // <= PER
+    unsigned long long all = 0, taken = 0;
+    const int i0 = one_first(rounds);
+    for (int it = 0; it < rounds; ++it)
+        if (i0 + it * 64 < n_dom) all |= 1ull << it;
+    // clamped loads in batches, so that no branch and no wait stands between those of a batch
+    auto at = [&](int it, int i) { return (unsigned)(i + it * 64 < n_dom ? i + it * 64 : n_dom - 1); };
+    // a value anew for each batch: indices and masks kept from one use to the next would push
+    // the keys out of the registers
+    auto fresh = [](auto v) {
+        asm volatile("" : "+v"(v));
+        return v;
+    };
+    constexpr int NB = PER < 16 ? PER : 16;
+    unsigned key[PER];
+    if (n1 > 0) {
+#pragma unroll
+        for (int r0 = 0; r0 < PER; r0 += NB) {
+            const int i = fresh(i0);
+            const unsigned long long avail = fresh(all);
+            float v[NB];
+#pragma unroll
+            for (int q = 0; q < NB; ++q) v[q] = f_hi[at(r0 + q, i)];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < NB; ++q) key[r0 + q] = (avail >> (r0 + q)) & 1 ? order_bits(v[q]) : ONE_NONE;
+        }
+        one_select(sh, key, rounds, n1, picked, taken);
+    }
+    if (n > n1) {
+        float lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+        for (int r0 = 0; r0 < PER; r0 += NB) {
+            const int i = fresh(i0);
+            const unsigned long long avail = fresh(all & ~taken);
+#pragma unroll
+            for (int q = 0; q < NB; ++q) key[r0 + q] = __float_as_uint(f_lo[at(r0 + q, i)]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+                const float v = __uint_as_float(key[r0 + q]);
+                if (isfinite(v) && ((avail >> (r0 + q)) & 1)) {
+                    lo = fminf(lo, v);
+                    hi = fmaxf(hi, v);
+                }
+            }
+        }
+        for (int m = 1; m < 64; m <<= 1) {
+            lo = fminf(lo, __shfl_xor(lo, m, 64));
+            hi = fmaxf(hi, __shfl_xor(hi, m, 64));
+        }
+        if ((tid & 63) == 0) {
+            sh.fmin[tid >> 6] = lo;
+            sh.fmax[tid >> 6] = hi;
+        }
+        __syncthreads();
+        for (int w = 0; w < ONE_T / 64; ++w) {
+            lo = fminf(lo, sh.fmin[w]);
+            hi = fmaxf(hi, sh.fmax[w]);
+        }
+#pragma unroll
+        for (int r0 = 0; r0 < PER; r0 += NB) {
+            const int i = fresh(i0);
+            const unsigned long long avail = fresh(all & ~taken);
+            float gv[NB];
+#pragma unroll
+            for (int q = 0; q < NB; ++q) gv[q] = gum[at(r0 + q, i)];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+                const float v = __uint_as_float(key[r0 + q]);
+                float k = FLT_MAX;                       // non-finite f_lo comes last
+                if (isfinite(v)) {
+                    const float s = hi > lo ? (v - lo) / (hi - lo) : 0.f;
+                    k = canon(s * inv_t - gv[q]);
+                }
+                key[r0 + q] = (avail >> (r0 + q)) & 1 ? order_bits(k) : ONE_NONE;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        one_select(sh, key, rounds, n - n1, picked + n1, taken);
+    }
+    if (n_dom > n) ordered(sh, all & ~taken, [&](int it, int pos) { rest[pos] = i0 + it * 64; });
+}
+
+__global__ __launch_bounds__(ONE_T) void k_prune_one(int n, const float *f_lo, const float *best, int32_t *keep,
+                                                     int32_t *n_keep) {
+    __shared__ OneShared sh;
+    const int tid = threadIdx.x, rounds = (n + ONE_T - 1) / ONE_T, i0 = one_first(rounds);
+    const float b = canon(*best);
+    unsigned long long f = 0;
+#pragma unroll 8
+    for (int it = 0; it < rounds; ++it) {
+        const int i = i0 + it * 64;
+        if (i < n && kept(f_lo, i, b)) f |= 1ull << it;
+    }
+    const int total = ordered(sh, f, [&](int it, int pos) { keep[pos] = i0 + it * 64; });
+    if (tid == 0) *n_keep = total;
+}
+
 std::mutex g_scratch_mu;
 int32_t *g_scratch_ptr[64] = {};   // per device: the address of `scratch` on that GPU
 
@@ -488,6 +775,15 @@ bound_status bound_bab_pick_out(bound_bab *b, int32_t n_dom, const float *f_lo, 
     hipStream_t st = (hipStream_t)stream;
     const int n = n_pick < n_dom ? n_pick : n_dom;
     const int n1 = (int)std::floor((double)eta * (double)n);
+    if (n_dom <= bp::ONE_MAX && n1 <= bp::ONE_SORT && n - n1 <= bp::ONE_SORT) {
+        const auto f = n_dom <= 8 * bp::ONE_T    ? bp::k_pick_one<8>
+                       : n_dom <= 32 * bp::ONE_T ? bp::k_pick_one<32>
+                                                 : bp::k_pick_one<bp::ONE_PER>;
+        hipLaunchKernelGGL(f, dim3(1), dim3(bp::ONE_T), 0, st, n_dom, n1, n, f_lo, f_hi, g, 1.0f / temperature,
+                           picked, rest);
+        BCHK(hipGetLastError());
+        return BOUND_OK;
+    }
     hipLaunchKernelGGL(bp::k_fill_u8, dim3(bp::blocks(n_dom)), dim3(bp::TPB), 0, st, n_dom, b->flag,
                        (uint8_t)1);
     if (n1 > 0) {
@@ -641,6 +937,11 @@ bound_status bound_bab_prune(bound_bab *b, int32_t n, const float *f_lo, const f
     hipStream_t st = (hipStream_t)stream;
     if (n == 0) {
         hipLaunchKernelGGL(bp::k_zero_i32, dim3(1), dim3(1), 0, st, n_keep);
+        BCHK(hipGetLastError());
+        return BOUND_OK;
+    }
+    if (n <= bp::ONE_MAX) {
+        hipLaunchKernelGGL(bp::k_prune_one, dim3(1), dim3(bp::ONE_T), 0, st, n, f_lo, best, keep, n_keep);
         BCHK(hipGetLastError());
         return BOUND_OK;
     }
