@@ -41,6 +41,7 @@ struct ConvTile {
     // and of the weight tile (k quad, output row), each below its radix but the last
     int dC4, dIX, dIY, dGI, dK4, dN;
     int rowdma;    // DMA staging of the input tile by rows (else by 256-slot steps)
+    int loop;      // DMA staging, tiles of whole images: image groups a block takes in turn
     int pxp;       // narrow-output kernel: threads per image (TR * OW, rounded up to whole
                    // waves in window passes)
 };
@@ -187,10 +188,13 @@ __global__ __launch_bounds__(256) void k_conv(const GeomSet gs, const ConvTile c
 
     const TileIdx ti = xcd_tile((gs.g[0].N + BN - 1) / BN, gs.n);
     const Geom &g = gs.g[ti.z];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane0 = tid & 63, wave = tid >> 6;
+    // a block of whole images takes `loop` groups in turn: the set-up below is the same for
+    // all of them (for 64-pixel windows it costs as much as the products of one group)
+    const int loop = DMA ? ct.loop : 1;
     const long grp = ldiv_by(ti.x, ct.tiles_y, ct.rTY);
     const int band = (int)(ti.x - grp * ct.tiles_y);
-    const long img0 = grp * ct.G;
+    long img0 = grp * loop * ct.G;
     if (img0 >= n_img) return;
     const int oyb = band * ct.TR;
     const int n0 = ti.y * BN;
@@ -214,18 +218,11 @@ __global__ __launch_bounds__(256) void k_conv(const GeomSet gs, const ConvTile c
     int abase[FM];
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
-        const int lr = wave * 64 + i * MF + MM::idx(lane);
+        const int lr = wave * 64 + i * MF + MM::idx(lane0);
         const int gi = qdiv(lr, ct.rTP), q = lr - gi * tile_px;
         const int py = qdiv(q, g.rOW), px = q - py * g.OW;
         abase[i] = ((gi * ct.IH + py * g.stride) * ct.IW + px * g.stride) * ct.CS;
     }
-    acc_t acc[FM][FN];
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int v = 0; v < MM::NACC; ++v) acc[i][j][v] = 0.f;
 
     // Staging of one channel chunk through registers (VEC: CC is a power of two >= 4).
     // The tile position of each staged float4 is the same for every chunk; only the
@@ -252,7 +249,7 @@ __global__ __launch_bounds__(256) void k_conv(const GeomSet gs, const ConvTile c
     const int c4s = VEC ? ct.lcc - 2 : 0;             // log2(CC / 4)
     const int Pin = ct.IW << c4s, Rin = ct.G * ct.IH;  // input grid [G*IH][IW*CC/4]
     const int Pw = ct.KB >> 2;                         // weight grid [BN][KB/4]
-    const float *Xb = X + img0 * (long)g.H * g.W * g.C;
+    const float *Xb = X + img0 * (long)g.H * g.W * g.C;     // of the group being staged
     const float *Bb = g.Bt + (long)n0 * g.Kp;
     int gin[NIN], lin[NIN], gw[NW], lw[NW];
     if (VEC && DMA && ct.rowdma) {
@@ -261,7 +258,7 @@ __global__ __launch_bounds__(256) void k_conv(const GeomSet gs, const ConvTile c
         const int lsp = ct.lcc - 2, rs = ct.IW << lsp;
 #pragma unroll
         for (int q = 0; q < NIN / 4; ++q) {
-            const int sl = q * 64 + lane;
+            const int sl = q * 64 + lane0;
             const int x = ix0 + (sl >> lsp), c4 = sl & ((1 << lsp) - 1);
             gin[q] = sl < rs && (unsigned)x < (unsigned)g.W ? (x * g.C + 4 * c4) * 4 : -1;
         }
@@ -382,10 +379,17 @@ __global__ __launch_bounds__(256) void k_conv(const GeomSet gs, const ConvTile c
     };
     // buffer extents: the block's image group (clipped to the images that exist) and
     // its weight rows
-    const long nvg = n_img - img0 < ct.G ? n_img - img0 : ct.G;
-    const int xbytes = (int)(nvg * g.H * g.W * g.C * 4), wbytes = BN * g.Kp * 4;
+    int xbytes = 0, wbytes = BN * g.Kp * 4;
+    long simg0 = img0;                                      // first image of that group
+    auto group_at = [&](long i0) {
+        simg0 = i0;
+        Xb = X + i0 * (long)g.H * g.W * g.C;
+        xbytes = (int)((n_img - i0 < ct.G ? n_img - i0 : ct.G) * g.H * g.W * g.C * 4);
+    };
+    group_at(img0);
     const int wv = __builtin_amdgcn_readfirstlane(wave);
-    auto dma_chunk = [&](int c0) {
+    // issues the chunk's loads (weights unless they are there already); the caller waits
+    auto dma_chunk = [&](int c0, bool weights) {
         if (ct.rowdma) {
             // rows wv, wv + 4, ... of the tile, (gi, iy) stepped by 4 rows (wave-uniform)
             const int rs = ct.IW << (ct.lcc - 2), nrow = ct.G * ct.IH;
@@ -393,7 +397,7 @@ __global__ __launch_bounds__(256) void k_conv(const GeomSet gs, const ConvTile c
             while (iy >= ct.IH) { iy -= ct.IH; ++gi; }
             for (int r = wv; r < nrow; r += 4) {
                 const int y = iy0 + iy;
-                if ((unsigned)y < (unsigned)g.H && img0 + gi < n_img) {
+                if ((unsigned)y < (unsigned)g.H && simg0 + gi < n_img) {
                     const int ro = (((gi * g.H + y) * g.W) * g.C + c0) * 4;
                     float *dst = In + r * rs * 4;
 #pragma unroll
@@ -408,15 +412,15 @@ __global__ __launch_bounds__(256) void k_conv(const GeomSet gs, const ConvTile c
             for (int i = 0; i < NIN; ++i)
                 if (gin[i] >= 0) lds_dma16(Xb, xbytes, In + (i * 256 + wv * 64) * 4, gin[i] + 4 * c0);
         }
+        if (!weights) return;
 #pragma unroll
         for (int i = 0; i < NW; ++i)
             if (gw[i] >= 0) lds_dma16(Bb, wbytes, Wl + (i * 256 + wv * 64) * 4, gw[i] + 4 * c0);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     };
 
-    const int kgrp = MM::grp(lane) * KPL;   // this lane's first k inside a 16-wide k block
+    const int kgrp = MM::grp(lane0) * KPL;   // this lane's first k inside a 16-wide k block
     if (VEC && DMA) {
-        dma_chunk(0);
+        dma_chunk(0, true);
     } else if (VEC) {
         load_chunk(0);
         store_chunk();
@@ -424,6 +428,15 @@ __global__ __launch_bounds__(256) void k_conv(const GeomSet gs, const ConvTile c
         stage_input<false>(In, ct, g, X, img0, n_img, iy0, ix0, 0);
         stage_weights(Wl, ct, g, BN, n0, 0);
     }
+    for (int it = 0;; ++it) {
+    acc_t acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int v = 0; v < MM::NACC; ++v) acc[i][j][v] = 0.f;
+    if (DMA) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     for (int ch = 0; ch < ct.nchunk; ++ch) {
         const bool more = VEC && ch + 1 < ct.nchunk;
@@ -452,7 +465,7 @@ __global__ __launch_bounds__(256) void k_conv(const GeomSet gs, const ConvTile c
             for (int j = 0; j < FN; ++j)
 #pragma unroll
                 for (int q = 0; q < KPL; q += 4) {
-                    const f32x4v b = *(const f32x4v *)(Wl + (j * MF + MM::idx(lane)) * ct.WS + k + q);
+                    const f32x4v b = *(const f32x4v *)(Wl + (j * MF + MM::idx(lane0)) * ct.WS + k + q);
                     bf[j][q] = b[0]; bf[j][q + 1] = b[1]; bf[j][q + 2] = b[2]; bf[j][q + 3] = b[3];
                 }
 #pragma unroll
@@ -464,15 +477,29 @@ __global__ __launch_bounds__(256) void k_conv(const GeomSet gs, const ConvTile c
         }
         if (more) {
             __syncthreads();
-            if (DMA)
-                dma_chunk((ch + 1) * ct.CC);
-            else
+            if (DMA) {
+                dma_chunk((ch + 1) * ct.CC, true);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            } else {
                 store_chunk();
+            }
             __syncthreads();
         }
     }
 
+    // the next group's first chunk is under way during this group's epilogue
+    const bool next = DMA && it + 1 < loop && img0 + ct.G < n_img;
+    if (next) {
+        __syncthreads();          // every wave is done with the tile
+        group_at(img0 + ct.G);
+        dma_chunk(0, ct.nchunk > 1);
+    }
+
     // ---------------------------------------------------------------- epilogue
+    // its row indices are formed anew for each group: kept over the products they would cost
+    // a block per CU
+    int lane = lane0;
+    if (DMA) asm volatile("" : "+v"(lane));
     int ncol[FN];
     float bcol[FN];
 #pragma unroll
@@ -480,46 +507,41 @@ __global__ __launch_bounds__(256) void k_conv(const GeomSet gs, const ConvTile c
         ncol[j] = n0 + j * MF + MM::col(lane);
         bcol[j] = ncol[j] < g.N ? epi.colv(ncol[j]) : 0.f;
     }
-    const float rTP = ct.rTP;
-    const int gfirst = qdiv(wave * 64, rTP), glast = qdiv(wave * 64 + 63, rTP);
-    const bool uniform = gfirst == glast && img0 + gfirst < n_img;
-    // Local row lr < 256 -> (image of the block, pixel); with OW a multiple of 4 a group
-    // of four consecutive rows is four neighbouring pixels of one output row.
-    const float rOW = g.rOW;
-    const bool quad = g.OW % 4 == 0;
-    auto rowfn4 = [&](int i, int vg, int (&img)[4], int (&dp)[4]) -> bool {
-        const int lr0 = wave * 64 + i * MF + MM::row(4 * vg, lane);
-#pragma unroll
-        for (int q = 0; q < (quad ? 1 : 4); ++q) {
-            const int lr = lr0 + q;
-            const int gi = qdiv(lr, rTP), r = lr - gi * tile_px;
-            const int py = qdiv(r, rOW), px = r - py * g.OW;
-            img[q] = img0 + gi < n_img ? (int)(img0 + gi) : -1;
-            dp[q] = ((oyb + py) * g.ostr + g.oy0) * g.DW + (px * g.ostr + g.ox0);
-        }
-        if (quad) {
-#pragma unroll
-            for (int q = 1; q < 4; ++q) {
-                img[q] = img[0];
-                dp[q] = dp[0] + q * g.ostr;
-            }
-        }
-        return quad;
-    };
     if constexpr (Epi::WIN) {
-        if (tile_px % 64 != 0 && tile_px % MF == 0 && quad) {
-            int fimg[FM];
-#pragma unroll
-            for (int i = 0; i < FM; ++i) {
-                const long im = img0 + qdiv(wv * 64 + i * MF, rTP);
-                fimg[i] = __builtin_amdgcn_readfirstlane(im < n_img ? (int)im : -1);
+        tile_epilogue_win<Epi, MF, FM, FN>(epi, acc, ncol, bcol, g, tile_px, lane, wv * 64, img0, n_img);
+    } else {
+        const float rTP = ct.rTP;
+        const int gfirst = qdiv(wave * 64, rTP), glast = qdiv(wave * 64 + 63, rTP);
+        const bool uniform = gfirst == glast && img0 + gfirst < n_img;
+        // Local row lr < 256 -> (image of the block, pixel); with OW a multiple of 4 a group
+        // of four consecutive rows is four neighbouring pixels of one output row.
+        const float rOW = g.rOW;
+        const bool quad = g.OW % 4 == 0;
+        auto rowfn4 = [&](int i, int vg, int (&img)[4], int (&dp)[4]) -> bool {
+            const int lr0 = wave * 64 + i * MF + MM::row(4 * vg, lane);
+    #pragma unroll
+            for (int q = 0; q < (quad ? 1 : 4); ++q) {
+                const int lr = lr0 + q;
+                const int gi = qdiv(lr, rTP), r = lr - gi * tile_px;
+                const int py = qdiv(r, rOW), px = r - py * g.OW;
+                img[q] = img0 + gi < n_img ? (int)(img0 + gi) : -1;
+                dp[q] = ((oyb + py) * g.ostr + g.oy0) * g.DW + (px * g.ostr + g.ox0);
             }
-            tile_epilogue_frag<Epi, MF, FM, FN>(epi, acc, ncol, bcol, g.N, rowfn4, lane, fimg);
-            return;
-        }
+            if (quad) {
+    #pragma unroll
+                for (int q = 1; q < 4; ++q) {
+                    img[q] = img[0];
+                    dp[q] = dp[0] + q * g.ostr;
+                }
+            }
+            return quad;
+        };
+        tile_epilogue<Epi, MF, FM, FN, true>(epi, acc, ncol, bcol, g.N, rowfn4, lane, uniform && quad,
+                                             (int)(img0 + gfirst));
     }
-    tile_epilogue<Epi, MF, FM, FN, true>(epi, acc, ncol, bcol, g.N, rowfn4, lane, uniform && quad,
-                                         (int)(img0 + gfirst));
+    if (!next) return;
+    img0 += ct.G;
+    }
 }
 
 // One thread per output pixel, up to NMAX output channels, VALU FMAs from LDS.
@@ -683,8 +705,11 @@ __global__ __launch_bounds__(256) void k_conv_valu(const GeomSet gs, const ConvT
     const long img = img0 + gi;
     float r0 = 0.f, r1 = 0.f;
     const int dpix = ((oyb + py) * g.ostr + g.oy0) * g.DW + (px * g.ostr + g.ox0);
+    // the pixels of a wave mostly lie in one image: its row then comes from scalar arithmetic
+    const int gf = qdiv(tid & ~63, ct.rPxp), gl = qdiv(tid | 63, ct.rPxp);
+    const int ur = __builtin_amdgcn_readfirstlane((int)(img0 + gf));
     if (in && img < n_img) {
-        const auto rc = epi.row((int)img);
+        const auto rc = gf == gl ? epi.row(ur) : epi.row((int)img);
         typename Epi::Pre pre[NMAX];
 #pragma unroll
         for (int n = 0; n < NMAX; ++n)
@@ -699,8 +724,6 @@ __global__ __launch_bounds__(256) void k_conv_valu(const GeomSet gs, const ConvT
     if (Epi::NRED > 0) {
         // a wave's 64 pixels lie in one image whenever an image has >= 64 pixels
         const int lane = tid & 63;
-        const int wave = tid >> 6;
-        const int gf = qdiv(wave * 64, ct.rPxp), gl = qdiv(wave * 64 + 63, ct.rPxp);
         if (gf == gl) {
             if (gf < ct.G && img0 + gf < n_img) reduce_wave(epi, r0, r1, img0 + gf, dpix, 0, lane);
         } else {
@@ -834,17 +857,27 @@ hipError_t launch_slots(const GeomSet &gs, const ConvTile &ct, size_t lds, const
     return hipGetLastError();
 }
 
+// Image groups a block of a DMA-staged product takes in turn: up to eight, as long as 16
+// blocks a CU remain, so that the last round of blocks stays a small part.
+int group_loop(const ConvTile &ct, long tiles) {
+    if (ct.tiles_y != 1) return 1;
+    const long n = tiles / (256 * 16);
+    return n < 1 ? 1 : (n > 8 ? 8 : (int)n);
+}
+
 template <class Epi, int MF, int BN>
 hipError_t launch_mfma_dma(const GeomSet &gs, const ConvTile &ct, size_t lds, const float *X, long n_img,
                            const Epi &epi, hipStream_t st) {   // planned only with C % 4 == 0
     const long groups = (n_img + ct.G - 1) / ct.G;
-    const dim3 grid((unsigned)(groups * ct.tiles_y * ((gs.g[0].N + BN - 1) / BN) * gs.n));   // xcd_tile order
+    ConvTile c2 = ct;
+    const long per = ct.tiles_y * ((gs.g[0].N + BN - 1) / BN) * gs.n;
+    c2.loop = group_loop(ct, groups * per);
+    const dim3 grid((unsigned)((groups + c2.loop - 1) / c2.loop * per));   // xcd_tile order
     const bool dsmall = ct.in_floats / 4 <= 256 * DMA_SMALL_IN4 &&
                         BN * ct.WS / 4 <= 256 * DMA_SMALL_W4;
     // staging by rows where a row fills at least one 64-slot segment (narrower rows
     // would leave most lanes of each DMA instruction idle) and fits the offset
     // registers (NIN / 4 segments)
-    ConvTile c2 = ct;
     const int rs = ct.IW * (ct.CS / 4);
     c2.rowdma = rs >= 64 && rs <= 64 * ((dsmall ? DMA_SMALL_IN4 : DMA_IN4) / 4);
     if (dsmall) {

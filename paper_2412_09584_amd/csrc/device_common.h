@@ -308,7 +308,7 @@ struct EpiRelaxWin {
         return px >= 0 && n < N ? ld(rc.tb, px * N + n) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
     __device__ void pre2(const Row &, Pre &) const {}
-    __device__ void post(const Pre &t, const Row &rc, int, int n, int j, float bcol, float g,
+    __device__ void post(const Pre &t, const Row &rc, int, int, int j, float bcol, float g,
                          float &r0, float &r1) const {
         const float lam = g >= 0.f ? g * t.x : g * t.y;
         const float off = g < 0.f ? g * t.z : 0.f;
@@ -316,7 +316,12 @@ struct EpiRelaxWin {
         r0 += bt + off;
         r1 += fabsf(bt) + fabsf(off);
         asm volatile("" : "+v"(r0), "+v"(r1));   // in order, as in EpiRelax
-        if (n < w.N) st(rc.out, j, lam);
+        st(rc.out, j, lam);
+    }
+    // record i of row rc, zero where !ok
+    __device__ Pre at(const Row &rc, int i, bool ok) const {
+        const Relax t = ld(rc.tb, ok ? i : 0);
+        return make_float4(ok ? t.x : 0.f, ok ? t.y : 0.f, ok ? t.z : 0.f, 0.f);
     }
 };
 
@@ -347,6 +352,10 @@ struct EpiConcWin {
         r0 += g * cr.x - fabsf(g) * cr.y;
         r1 += fabsf(g) * (fabsf(cr.x) + cr.y);
         asm volatile("" : "+v"(r0), "+v"(r1));
+    }
+    __device__ Pre at(const Row &rc, int i, bool ok) const {
+        const float c = ld(rc.cen, ok ? i : 0), r = ld(rc.rad, ok ? i : 0);
+        return make_float2(ok ? c : 0.f, ok ? r : 0.f);
     }
 };
 
@@ -551,59 +560,6 @@ __device__ inline void tile_epilogue_impl(const Epi &epi, Acc (&acc)[FM][FN], co
     }
 }
 
-// Window tiles whose images are smaller than a wave's 64 rows, but hold whole MF-row
-// fragments: fragment i lies in img fimg[i] (wave-uniform; -1 past the batch, where no
-// later fragment exists either).  Rows are resolved and summed per fragment; the next
-// group's records are in flight while a group is finished, as in the FAST path.
-template <class Epi, int MF, int FM, int FN, class Acc, class RowFn>
-__device__ inline void tile_epilogue_frag(const Epi &epi, Acc (&acc)[FM][FN], const int (&ncol)[FN],
-                                          const float (&bcol)[FN], int N, const RowFn &rowfn4,
-                                          int lane, const int (&fimg)[FM]) {
-    constexpr int NGF = Mma<MF>::NACC / 4, NG = FM * NGF;
-    typename Epi::Row rwA, rwB;
-    typename Epi::Pre preA[FN][4], preB[FN][4];
-    int dpA[4], dpB[4];
-    auto load = [&](int g, typename Epi::Row &rw, int (&dp)[4], typename Epi::Pre (&pre)[FN][4]) {
-        int img[4];
-        if (g % NGF == 0) rw = epi.row(fimg[g / NGF]);
-        rowfn4(g / NGF, g % NGF, img, dp);
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) pre[j][q] = epi.pre(rw, dp[q], ncol[j], N);
-    };
-    if (fimg[0] < 0) return;
-    load(0, rwA, dpA, preA);
-    float u0 = 0.f, u1 = 0.f;
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-        const int i = g / NGF, vg = g % NGF;
-        const bool more = g + 1 < NG && fimg[(g + 1) / NGF < FM ? (g + 1) / NGF : FM - 1] >= 0;
-        if (more) {
-            rwB = rwA;
-            load(g + 1, rwB, dpB, preB);
-        }
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                epi.post(preA[j][q], rwA, dpA[q], ncol[j], dpA[q] * N + ncol[j], bcol[j],
-                         acc[i][j][vg * 4 + q], u0, u1);
-        if (vg == NGF - 1) {
-            reduce_wave(epi, u0, u1, fimg[i], dpA[0], ncol[0], lane);
-            u0 = u1 = 0.f;
-        }
-        if (!more) return;
-        rwA = rwB;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            dpA[q] = dpB[q];
-#pragma unroll
-            for (int j = 0; j < FN; ++j) preA[j][q] = preB[j][q];
-        }
-    }
-}
-
 // Sums over the MF lanes that share output rows, for the NV = 4 or 16 rows v of a lane at
 // once: each step halves the rows a lane carries by exchanging the other half with its
 // partner, so 16 rows over 32 lanes take 16 shuffles instead of 80.  Returns the sum of the
@@ -628,6 +584,83 @@ template <int MF, int NV> __device__ inline float sum_rows(float (&v)[NV], int l
         }
     }
     return v[0];
+}
+
+// Epilogue of a wave's fragments in a window pass: whole images of tile_px (a power of two,
+// >= MF) pixels, rows of ow = 2^low pixels, low >= 2.  A lane's four consecutive rows are
+// neighbouring pixels of one row; their window coordinates depend on the lane alone, so a
+// record's index and its validity take an add and a compare per pixel instead of the
+// divisions and 32-bit multiplications of win_pixel.  Fragment i's image is img0 + its
+// number in the block; fragments past the batch load the last image's records and write
+// nothing.
+template <class Epi, int MF, int FM, int FN, class Acc>
+__device__ inline void tile_epilogue_win(const Epi &epi, Acc (&acc)[FM][FN], const int (&ncol)[FN],
+                                         const float (&bcol)[FN], const Geom &g, int tile_px, int lane,
+                                         int row0, long img0, long n_img) {
+    constexpr int NGF = Mma<MF>::NACC / 4, NG = FM * NGF, DEPTH = NG < 3 ? NG : 3;
+    const int lpx = __builtin_ctz(tile_px), low = __builtin_ctz(g.OW), N = g.N, step = g.ostr * N;
+    const WinMap &w = epi.w;
+    const bool one = tile_px >= 64;          // the wave's fragments lie in one image
+    long img[FM];
+    typename Epi::Row rw[FM];
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+        if (i > 0 && one) {
+            img[i] = img[0];
+            rw[i] = rw[0];
+            continue;
+        }
+        img[i] = img0 + ((row0 + i * MF) >> lpx);
+        rw[i] = epi.row((int)(img[i] < n_img ? img[i] : n_img - 1));
+    }
+    float sums[2 * FM];
+#pragma unroll
+    for (int i = 0; i < 2 * FM; ++i) sums[i] = 0.f;
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+        if (ncol[j] < N) {
+            typename Epi::Pre t[NG][4];
+            int oi[NG];
+            auto load = [&](int gi) {
+                const int i = gi / NGF, q = (row0 + i * MF + Mma<MF>::row(4 * (gi % NGF), lane)) & (tile_px - 1);
+                const int py = q >> low, px = q & (g.OW - 1);
+                const int wy = __mul24(py, g.ostr) + g.oy0, wx = __mul24(px, g.ostr) + g.ox0;
+                const int y = rw[i].y0 + wy, x = rw[i].x0 + wx;
+                const int ri = __mul24(__mul24(y, w.W) + x, N) + ncol[j];
+                oi[gi] = __mul24(__mul24(wy, w.DW) + wx, N) + ncol[j];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    t[gi][e] = epi.at(rw[i], ri + e * step, (unsigned)y < (unsigned)w.H &&
+                                                                (unsigned)(x + e * g.ostr) < (unsigned)w.W);
+            };
+#pragma unroll
+            for (int gi = 0; gi < DEPTH - 1; ++gi) load(gi);
+#pragma unroll
+            for (int gi = 0; gi < NG; ++gi) {
+                if (gi + DEPTH - 1 < NG) load(gi + DEPTH - 1);
+                __builtin_amdgcn_sched_barrier(0);
+                const int i = gi / NGF;
+                if (img[i] < n_img)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        epi.post(t[gi][e], rw[i], 0, ncol[j], oi[gi] + e * step, bcol[j],
+                                 acc[i][j][(gi % NGF) * 4 + e], sums[2 * i], sums[2 * i + 1]);
+            }
+        }
+    if (one) {
+        float u0 = sums[0], u1 = sums[1];
+#pragma unroll
+        for (int i = 1; i < FM; ++i) {
+            u0 += sums[2 * i];
+            u1 += sums[2 * i + 1];
+        }
+        if (img[0] < n_img) reduce_wave(epi, u0, u1, img[0], 0, 0, lane);
+        return;
+    }
+    int v;
+    const float x = sum_rows<64, 2 * FM>(sums, lane, v);
+    const long im = img0 + ((row0 + (v >> 1) * MF) >> lpx);
+    if ((lane & (64 / (2 * FM) - 1)) == 0 && im < n_img) atomicAdd((v & 1 ? epi.red1() : epi.red0()) + im, x);
 }
 
 // Epilogue of a wave that holds one MF x MF tile of a dense product (rows m0 .., M rows in
