@@ -198,6 +198,7 @@ hipError_t direct_adj(const GeomSet &gs, const float *A, long n_img, const AdjPa
                       hipStream_t st, int cc, int mode, bool *used);
 hipError_t direct_fwd(const GeomSet &gs, const float *A, long n_img, const FwdParams &p,
                       hipStream_t st, int cc, int mode, bool *used);
+constexpr int DIRECT_AUTO = 4;      // the direct kernels' own choice of staging
 int direct_candidates(const GeomSet &gs, int *cc, int *mode, int cap);
 // window.hip: the products of a window pass (direct convolution, DMA-staged); window_fits
 // tells whether the kernels cover a geometry (conc: the concretising step)

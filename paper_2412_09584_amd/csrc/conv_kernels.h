@@ -41,7 +41,7 @@ struct ConvTile {
     // and of the weight tile (k quad, output row), each below its radix but the last
     int dC4, dIX, dIY, dGI, dK4, dN;
     int rowdma;    // DMA staging of the input tile by rows (else by 256-slot steps)
-    int loop;      // DMA staging, tiles of whole images: image groups a block takes in turn
+    int loop;      // window passes: image groups a block takes in turn
     int pxp;       // narrow-output kernel: threads per image (TR * OW, rounded up to whole
                    // waves in window passes)
 };
@@ -189,9 +189,12 @@ __global__ __launch_bounds__(256) void k_conv(const GeomSet gs, const ConvTile c
     const TileIdx ti = xcd_tile((gs.g[0].N + BN - 1) / BN, gs.n);
     const Geom &g = gs.g[ti.z];
     const int tid = threadIdx.x, lane0 = tid & 63, wave = tid >> 6;
-    // a block of whole images takes `loop` groups in turn: the set-up below is the same for
-    // all of them (for 64-pixel windows it costs as much as the products of one group)
-    const int loop = DMA ? ct.loop : 1;
+    // in a window pass a block takes `loop` groups in turn: the set-up below is the same for
+    // all of them and costs as much as the products of one group; on whole layers the longer
+    // products hide it, and the registers of a loop cost more (3x3 layer of the 3x32x32 CNN,
+    // 4096 subdomains: 1.70 -> 1.93 ms with the loop)
+    constexpr bool LOOP = Epi::WIN && DMA;
+    const int loop = LOOP ? ct.loop : 1;
     const long grp = ldiv_by(ti.x, ct.tiles_y, ct.rTY);
     const int band = (int)(ti.x - grp * ct.tiles_y);
     long img0 = grp * loop * ct.G;
@@ -488,7 +491,7 @@ __global__ __launch_bounds__(256) void k_conv(const GeomSet gs, const ConvTile c
     }
 
     // the next group's first chunk is under way during this group's epilogue
-    const bool next = DMA && it + 1 < loop && img0 + ct.G < n_img;
+    const bool next = LOOP && it + 1 < loop && img0 + ct.G < n_img;
     if (next) {
         __syncthreads();          // every wave is done with the tile
         group_at(img0 + ct.G);
@@ -499,7 +502,7 @@ __global__ __launch_bounds__(256) void k_conv(const GeomSet gs, const ConvTile c
     // its row indices are formed anew for each group: kept over the products they would cost
     // a block per CU
     int lane = lane0;
-    if (DMA) asm volatile("" : "+v"(lane));
+    if (LOOP) asm volatile("" : "+v"(lane));
     int ncol[FN];
     float bcol[FN];
 #pragma unroll
@@ -857,7 +860,7 @@ hipError_t launch_slots(const GeomSet &gs, const ConvTile &ct, size_t lds, const
     return hipGetLastError();
 }
 
-// Image groups a block of a DMA-staged product takes in turn: up to eight, as long as 16
+// Image groups a block of a window product takes in turn: up to eight, as long as 16
 // blocks a CU remain, so that the last round of blocks stays a small part.
 int group_loop(const ConvTile &ct, long tiles) {
     if (ct.tiles_y != 1) return 1;
@@ -871,7 +874,7 @@ hipError_t launch_mfma_dma(const GeomSet &gs, const ConvTile &ct, size_t lds, co
     const long groups = (n_img + ct.G - 1) / ct.G;
     ConvTile c2 = ct;
     const long per = ct.tiles_y * ((gs.g[0].N + BN - 1) / BN) * gs.n;
-    c2.loop = group_loop(ct, groups * per);
+    c2.loop = Epi::WIN ? group_loop(ct, groups * per) : 1;
     const dim3 grid((unsigned)((groups + c2.loop - 1) / c2.loop * per));   // xcd_tile order
     const bool dsmall = ct.in_floats / 4 <= 256 * DMA_SMALL_IN4 &&
                         BN * ct.WS / 4 <= 256 * DMA_SMALL_W4;
@@ -928,8 +931,14 @@ hipError_t try_direct(const GeomSet &gs, const float *X, long n_img, const Epi &
     if (groups * ct.tiles_y * (g.N / 4 + 1) * gs.n > 0x7fffffffL) return hipSuccess;
     if (g.N <= 4 && g.C % 4 == 0) {      // narrow output: VALU kernel
         ct.CC = g.C;
-        ct.CS = mode == 3 ? g.C : g.C + 4;   // mode 3: DMA into unpadded rows
+        ct.CS = g.C + 4;
         ct.in_floats = ct.G * ct.IH * ct.IW * ct.CS;
+        if (mode == DIRECT_AUTO)
+            mode = ct.in_floats * 4 <= LDS_BUDGET && ct.G * ct.IH * ct.IW * (g.C / 4) <= 256 * VALU_DMA_IN4 ? 3 : -1;
+        if (mode == 3) {                     // DMA into unpadded rows
+            ct.CS = g.C;
+            ct.in_floats = ct.G * ct.IH * ct.IW * ct.CS;
+        }
         const size_t lds = (size_t)ct.in_floats * 4;
         if (lds > LDS_BUDGET) return hipSuccess;
         set_tile_recips(g, ct);
@@ -966,6 +975,23 @@ hipError_t try_direct(const GeomSet &gs, const float *X, long n_img, const Epi &
     // mode: bit 0 (1, 3) LDS DMA staging, bit 1 (2, 3) 16x16 MFMA tiles for 32 outputs
     const bool mf16 = BN == 32 && (mode == 2 || mode == 3);
     const int KPL = BN == 16 || mf16 ? Mma<16>::KPL : Mma<32>::KPL;
+    if (mode == DIRECT_AUTO) {
+        // DMA staging of the chunk that register staging would take, where it fits: the same
+        // sums (they are formed chunk by chunk) and the same products accepted.  4096
+        // subdomains of the 3x32x32 CNN, registers -> DMA: relaxing products of its layers 2
+        // .. 4 2.24, 2.04, 1.91 -> 2.20, 1.77, 1.65, the 3x3 layer's adjoint 2.66 -> 2.02, the
+        // concretising product 1.17 -> 0.94 ms.  Fewer blocks than CUs keep the registers,
+        // which fetch the next chunk during this one's products: a block alone on its CU has
+        // no other to hide DMA's wait (gradient of one subdomain: 306 and 314 us).
+        ConvTile t = ct;
+        mode = -1;
+        if (!plan_chunk(g, BN, KPL, t)) return hipSuccess;
+        want_cc = t.CC;
+        t = ct;
+        if (groups * ct.tiles_y * ((g.N + BN - 1) / BN) * gs.n >= 256 && g.C % 4 == 0 &&
+            plan_chunk(g, BN, KPL, t, want_cc, true))
+            mode = 1;
+    }
     const bool dma = (mode == 1 || mode == 3) && g.C % 4 == 0;
     const size_t lds = plan_chunk(g, BN, KPL, ct, want_cc, dma);
     if (!lds) return hipSuccess;

@@ -56,8 +56,8 @@ int plan_candidates(const GeomSet &gs, Plan *out, int cap) {
                     hipStream_t st, const Plan &plan) {                                      \
         if (plan.path != 2) {                                                                \
             bool used = false;                                                               \
-            const hipError_t e = DIRECT(gs, A, n_img, p, st, plan.path == 1 ? plan.cc : 0,      \
-                                        plan.cfg, &used);                                     \
+            const hipError_t e = DIRECT(gs, A, n_img, p, st, plan.path == 1 ? plan.cc : 0,   \
+                                        plan.path == 1 ? plan.cfg : DIRECT_AUTO, &used);      \
             if (used || e != hipSuccess) return e;                                           \
             const int d = plan.path == 0 ? dense_auto(gs, n_img, plan.keep) : -1;            \
             if (d >= 0) return DENSE(gs, A, n_img, p, st, d);                                \
