@@ -38,6 +38,7 @@ struct LayerInfo {
     long din, dout;
     GeomSet gT;  // backward product Lambda W (transposed convolution for Conv2d)
     GeomSet gF;  // forward product (adjoint pass)
+    GeomSet gW;  // pairs of gT's phases as a window's phases (conv_split.hip), n = 0: none
 };
 
 }  // namespace
@@ -260,6 +261,34 @@ bool split_weights(bound_net *net, Geom &g, int Np, hipStream_t st) {
     return launch_pack_split(g.Bt, Np, g.Kp, g.Kc, bs, st) == hipSuccess;
 }
 
+// The layer's pairs of phases in windows (none unless it has four phases of one shape and 5 ..
+// 16 columns): phase (wy, 0) and (wy, 1) of a window take the weights packed for the layer's
+// phases with the same first taps, (p + pad) % 2.
+bool build_pairs(bound_net *net, LayerInfo &li, hipStream_t st) {
+    const bound_layer &L = li.L;
+    if (L.stride != 2 || li.gT.n != 4 || L.in_c > 16 || L.in_c <= 4) return true;
+    for (int i = 1; i < 4; ++i)
+        if (li.gT.g[0].kh != li.gT.g[i].kh || li.gT.g[0].kw != li.gT.g[i].kw) return true;
+    auto phase = [&](int y, int x) {
+        int i = 0;
+        while (i < 3 && ((li.gT.g[i].oy0 + L.pad) % 2 != y || (li.gT.g[i].ox0 + L.pad) % 2 != x)) ++i;
+        return li.gT.g[i];
+    };
+    for (int y = 0; y < 2; ++y) {
+        Geom t = phase(y, 0);
+        const Geom second = phase(y, 1);
+        t.N = 2 * L.in_c;
+        const long n = conv_split_size(t);
+        unsigned short *bs;
+        if (n == 0) return true;
+        if (!net->alloc(&bs, n) || launch_pack_conv(t, &second, bs, st) != hipSuccess) return false;
+        t.Bs = bs;
+        li.gW.g[y] = t;
+    }
+    li.gW.n = 2;
+    return true;
+}
+
 bound_status build_geoms(bound_net *net, hipStream_t st) {
     for (int i = 0; i < net->n_layers; ++i) {
         LayerInfo &li = net->layers[i];
@@ -333,10 +362,17 @@ bound_status build_geoms(bound_net *net, hipStream_t st) {
                                          t.N, t.K, t.Kp, (int)NpT, bt, st));
                     t.Bt = bt;
                     set_recips(t);
+                    if (const long n = conv_split_size(t)) {
+                        unsigned short *bs;
+                        if (!net->alloc(&bs, n)) return fail(BOUND_E_NOMEM, "weight packing");
+                        HIPCHK(launch_pack_conv(t, nullptr, bs, st));
+                        t.Bs = bs;
+                    }
                     li.gT.g[np++] = t;
                 }
             }
             li.gT.n = np;
+            if (!build_pairs(net, li, st)) return fail(BOUND_E_NOMEM, "weight packing");
         }
     }
     return BOUND_OK;
@@ -347,6 +383,7 @@ bound_status build_geoms(bound_net *net, hipStream_t st) {
 // maps of the windows' positions (map[m]: window on z_m's neurons, map[0]: on the input).
 struct WinPlan {
     std::vector<GeomSet> gs;     // index m
+    std::vector<GeomSet> gp;     // index m: pairs of its phases (n = 0: none)
     std::vector<WinMap> map;     // index m
     std::vector<long> elems;     // index m: floats per img of the window of z_m (0: the input)
 };
@@ -360,6 +397,7 @@ bool window_plan(const bound_net *net, int k, int rpi, WinPlan &wp) {
     const long lim = 1L << 20;                 // FP32-reciprocal quotients
     if (T.kind != BOUND_CONV2D || k < 2 || rpi > lim || net->d[k] > lim) return false;
     wp.gs.assign(k, GeomSet{});
+    wp.gp.assign(k, GeomSet{});
     wp.map.assign(k, WinMap{});
     wp.elems.assign(k, 0);
     int need = T.kh, store = T.kh, S = T.stride, P = T.pad;   // window of z_{k-1}
@@ -396,6 +434,19 @@ bool window_plan(const bound_net *net, int k, int rpi, WinPlan &wp) {
         // with the same first tap, (p + pad) % s == ph
         GeomSet &gs = wp.gs[m];
         gs.n = 0;
+        auto place = [&](Geom g, int py, int px) {
+            g.H = g.W = in;
+            g.OH = g.OW = A;
+            g.pad_y = g.kh - 1;
+            g.pad_x = g.kw - 1;
+            g.DH = g.DW = store;
+            g.oy0 = py;
+            g.ox0 = px;
+            set_recips(g);
+            return g;
+        };
+        for (int py = 0; py < li.gW.n; ++py) wp.gp[m].g[py] = place(li.gW.g[py], py, 0);
+        wp.gp[m].n = li.gW.n;
         for (int py = 0; py < s; ++py)
             for (int px = 0; px < s; ++px) {
                 const Geom *src = nullptr;
@@ -403,17 +454,8 @@ bool window_plan(const bound_net *net, int k, int rpi, WinPlan &wp) {
                     if ((li.gT.g[i].oy0 + L.pad) % s == py && (li.gT.g[i].ox0 + L.pad) % s == px)
                         src = &li.gT.g[i];
                 if (!src) return false;
-                Geom g = *src;
-                g.H = g.W = in;
-                g.OH = g.OW = A;
-                g.pad_y = g.kh - 1;
-                g.pad_x = g.kw - 1;
-                g.DH = g.DW = store;
-                g.oy0 = py;
-                g.ox0 = px;
-                set_recips(g);
-                win += (double)A * A * g.K * g.N;
-                gs.g[gs.n++] = g;
+                win += (double)A * A * src->K * src->N;
+                gs.g[gs.n++] = place(*src, py, px);
             }
         dense += (double)L.out_h * L.out_w * L.out_c * L.kh * L.kw * L.in_c;
         if (wp.elems[m - 1] > net->max_d || !window_fits(gs, m == 1)) return false;
@@ -495,7 +537,7 @@ bound_status window_pass(bound_net *net, const bound_pass *P, const bound_out *o
             rp.s = net->acc_s;
             rp.mag = net->acc_mag;
             ProfScope ps(net, st, lbl("win_relax_L%d", m));
-            HIPCHK(window_relax(wp.gs[m], cur, n_img, rp, wp.map[m - 1], st));
+            HIPCHK(window_relax(wp.gs[m], wp.gp[m], cur, n_img, rp, wp.map[m - 1], st));
             std::swap(cur, nxt);
         }
         ConcParams cp{};

@@ -25,7 +25,9 @@ struct Geom {
     float rC, rKW;             // fl(1 / C), fl(1 / kw)
     double rMd;                // 1 / (OH * OW) in FP64 for row indices beyond 2^21
     const float *Bt;
-    const unsigned short *Bs;  // dense layers: Bt in three bf16 parts, [n][Kc][3][32] (split.hip)
+    // Bt in three bf16 parts: dense layers [n][Kc][3][32] (split.hip), transposed
+    // convolutions as conv_split.hip packs them (null where it does not take them)
+    const unsigned short *Bs;
     int Kc;                    // its 32-wide k chunks
 };
 
@@ -200,10 +202,21 @@ hipError_t direct_fwd(const GeomSet &gs, const float *A, long n_img, const FwdPa
                       hipStream_t st, int cc, int mode, bool *used);
 constexpr int DIRECT_AUTO = 4;      // the direct kernels' own choice of staging
 int direct_candidates(const GeomSet &gs, int *cc, int *mode, int cap);
+// conv_split.hip: relaxing direct convolutions on the bf16 matrix cores at FP32 precision, for
+// passes that save nothing; the launchers take what conv_split_fits accepts.  conv_split_size:
+// elements of a geometry's packed weights (0: not taken); launch_pack_conv packs them, a
+// pair's with the second phase's geometry
+bool conv_split_fits(const GeomSet &gs, long n_img, bool window);
+bool conv_split_pair_fits(const GeomSet &pair, long n_img);
+hipError_t conv_split_relax(const GeomSet &gs, const float *A, long n_img, const RelaxParams &p, hipStream_t st);
+hipError_t conv_split_relax_win(const GeomSet &gs, bool pair, const float *A, long n_img, const RelaxParams &p,
+                                const WinMap &w, hipStream_t st);
+long conv_split_size(const Geom &g);
+hipError_t launch_pack_conv(const Geom &g, const Geom *pair, unsigned short *out, hipStream_t st);
 // window.hip: the products of a window pass (direct convolution, DMA-staged); window_fits
 // tells whether the kernels cover a geometry (conc: the concretising step)
 bool window_fits(const GeomSet &gs, bool conc);
-hipError_t window_relax(const GeomSet &gs, const float *A, long n_img, const RelaxParams &p,
+hipError_t window_relax(const GeomSet &gs, const GeomSet &pair, const float *A, long n_img, const RelaxParams &p,
                         const WinMap &w, hipStream_t st);
 hipError_t window_conc(const GeomSet &gs, const float *A, long n_img, const ConcParams &p,
                        const WinMap &w, hipStream_t st);

@@ -586,48 +586,52 @@ template <int MF, int NV> __device__ inline float sum_rows(float (&v)[NV], int l
     return v[0];
 }
 
-// Epilogue of a wave's fragments in a window pass: whole images of tile_px (a power of two,
-// >= MF) pixels, rows of ow = 2^low pixels, low >= 2.  A lane's four consecutive rows are
+// Epilogue of a wave's 64 rows in a window pass: whole images of tile_px (a power of two, >=
+// 16) pixels, rows of ow = 2^low pixels, low >= 2.  A lane's four consecutive rows are
 // neighbouring pixels of one row; their window coordinates depend on the lane alone, so a
 // record's index and its validity take an add and a compare per pixel instead of the
-// divisions and 32-bit multiplications of win_pixel.  Fragment i's image is img0 + its
-// number in the block; fragments past the batch load the last image's records and write
-// nothing.
-template <class Epi, int MF, int FM, int FN, class Acc>
+// divisions and 32-bit multiplications of win_pixel.  Sixteen rows i lie in one image, img0 +
+// its number in the block; those past the batch load the last image's records and write
+// nothing.  PAIR: columns 16 h + n are channel n of the pixel h further on, g.N / 2 channels.
+template <class Epi, int MF, int FM, int FN, bool PAIR = false, class Acc>
 __device__ inline void tile_epilogue_win(const Epi &epi, Acc (&acc)[FM][FN], const int (&ncol)[FN],
                                          const float (&bcol)[FN], const Geom &g, int tile_px, int lane,
                                          int row0, long img0, long n_img) {
-    constexpr int NGF = Mma<MF>::NACC / 4, NG = FM * NGF, DEPTH = NG < 3 ? NG : 3;
-    const int lpx = __builtin_ctz(tile_px), low = __builtin_ctz(g.OW), N = g.N, step = g.ostr * N;
+    constexpr int NGF = Mma<MF>::NACC / 4, NG = FM * NGF, DEPTH = NG < 3 ? NG : 3, NI = FM * MF / 16;
+    const int lpx = __builtin_ctz(tile_px), low = __builtin_ctz(g.OW);
+    const int N = PAIR ? g.N >> 1 : g.N, step = g.ostr * N;
     const WinMap &w = epi.w;
-    const bool one = tile_px >= 64;          // the wave's fragments lie in one image
-    long img[FM];
-    typename Epi::Row rw[FM];
+    const bool one = tile_px >= 64;          // the wave's rows lie in one image
+    long img[NI];
+    typename Epi::Row rw[NI];
 #pragma unroll
-    for (int i = 0; i < FM; ++i) {
+    for (int i = 0; i < NI; ++i) {
         if (i > 0 && one) {
             img[i] = img[0];
             rw[i] = rw[0];
             continue;
         }
-        img[i] = img0 + ((row0 + i * MF) >> lpx);
+        img[i] = img0 + ((row0 + i * 16) >> lpx);
         rw[i] = epi.row((int)(img[i] < n_img ? img[i] : n_img - 1));
     }
-    float sums[2 * FM];
+    float sums[2 * NI];
 #pragma unroll
-    for (int i = 0; i < 2 * FM; ++i) sums[i] = 0.f;
+    for (int i = 0; i < 2 * NI; ++i) sums[i] = 0.f;
 #pragma unroll
     for (int j = 0; j < FN; ++j)
-        if (ncol[j] < N) {
+        if (const int n = PAIR ? ncol[j] & 15 : ncol[j], h = PAIR ? ncol[j] >> 4 : 0; n < N) {
             typename Epi::Pre t[NG][4];
             int oi[NG];
+            // rows 8 vg + .. of a 32-row fragment, 4 .. of a 16-row one
+            auto im = [](int gi) { return MF == 32 ? gi / NGF * 2 + (gi % NGF) / 2 : gi; };
             auto load = [&](int gi) {
-                const int i = gi / NGF, q = (row0 + i * MF + Mma<MF>::row(4 * (gi % NGF), lane)) & (tile_px - 1);
+                const int i = im(gi);
+                const int q = (row0 + gi / NGF * MF + Mma<MF>::row(4 * (gi % NGF), lane)) & (tile_px - 1);
                 const int py = q >> low, px = q & (g.OW - 1);
-                const int wy = __mul24(py, g.ostr) + g.oy0, wx = __mul24(px, g.ostr) + g.ox0;
+                const int wy = __mul24(py, g.ostr) + g.oy0, wx = __mul24(px, g.ostr) + g.ox0 + h;
                 const int y = rw[i].y0 + wy, x = rw[i].x0 + wx;
-                const int ri = __mul24(__mul24(y, w.W) + x, N) + ncol[j];
-                oi[gi] = __mul24(__mul24(wy, w.DW) + wx, N) + ncol[j];
+                const int ri = __mul24(__mul24(y, w.W) + x, N) + n;
+                oi[gi] = __mul24(__mul24(wy, w.DW) + wx, N) + n;
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     t[gi][e] = epi.at(rw[i], ri + e * step, (unsigned)y < (unsigned)w.H &&
@@ -639,18 +643,18 @@ __device__ inline void tile_epilogue_win(const Epi &epi, Acc (&acc)[FM][FN], con
             for (int gi = 0; gi < NG; ++gi) {
                 if (gi + DEPTH - 1 < NG) load(gi + DEPTH - 1);
                 __builtin_amdgcn_sched_barrier(0);
-                const int i = gi / NGF;
+                const int i = im(gi);
                 if (img[i] < n_img)
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        epi.post(t[gi][e], rw[i], 0, ncol[j], oi[gi] + e * step, bcol[j],
-                                 acc[i][j][(gi % NGF) * 4 + e], sums[2 * i], sums[2 * i + 1]);
+                        epi.post(t[gi][e], rw[i], 0, n, oi[gi] + e * step, bcol[j],
+                                 acc[gi / NGF][j][(gi % NGF) * 4 + e], sums[2 * i], sums[2 * i + 1]);
             }
         }
     if (one) {
         float u0 = sums[0], u1 = sums[1];
 #pragma unroll
-        for (int i = 1; i < FM; ++i) {
+        for (int i = 1; i < NI; ++i) {
             u0 += sums[2 * i];
             u1 += sums[2 * i + 1];
         }
@@ -658,9 +662,9 @@ __device__ inline void tile_epilogue_win(const Epi &epi, Acc (&acc)[FM][FN], con
         return;
     }
     int v;
-    const float x = sum_rows<64, 2 * FM>(sums, lane, v);
-    const long im = img0 + ((row0 + (v >> 1) * MF) >> lpx);
-    if ((lane & (64 / (2 * FM) - 1)) == 0 && im < n_img) atomicAdd((v & 1 ? epi.red1() : epi.red0()) + im, x);
+    const float x = sum_rows<64, 2 * NI>(sums, lane, v);
+    const long im = img0 + ((row0 + (v >> 1) * 16) >> lpx);
+    if ((lane & (64 / (2 * NI) - 1)) == 0 && im < n_img) atomicAdd((v & 1 ? epi.red1() : epi.red0()) + im, x);
 }
 
 // Epilogue of a wave that holds one MF x MF tile of a dense product (rows m0 .., M rows in

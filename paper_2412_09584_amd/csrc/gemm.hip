@@ -51,6 +51,15 @@ int plan_candidates(const GeomSet &gs, Plan *out, int cap) {
     return n;
 }
 
+static hipError_t relax_general(const GeomSet &gs, const float *A, long n_img, const RelaxParams &p,
+                                hipStream_t st, const Plan &plan);
+hipError_t gemm_relax(const GeomSet &gs, const float *A, long n_img, const RelaxParams &p,
+                      hipStream_t st, const Plan &plan) {
+    if (plan.path == 0 && !plan.keep && !p.save && conv_split_fits(gs, n_img, false))
+        return conv_split_relax(gs, A, n_img, p, st);
+    return relax_general(gs, A, n_img, p, st, plan);
+}
+
 #define BOUND_PRODUCT(NAME, PARAMS, DIRECT, CFG, DENSE)                                      \
     hipError_t NAME(const GeomSet &gs, const float *A, long n_img, const PARAMS &p,          \
                     hipStream_t st, const Plan &plan) {                                      \
@@ -66,7 +75,7 @@ int plan_candidates(const GeomSet &gs, Plan *out, int cap) {
         }                                                                                    \
         return CFG(gs, A, n_img, p, st, plan.path == 2 ? plan.cfg : -1);                     \
     }
-BOUND_PRODUCT(gemm_relax, RelaxParams, direct_relax, gemm_relax_cfg, dense_relax)
+BOUND_PRODUCT(relax_general, RelaxParams, direct_relax, gemm_relax_cfg, dense_relax)
 BOUND_PRODUCT(gemm_conc, ConcParams, direct_conc, gemm_conc_cfg, dense_conc)
 BOUND_PRODUCT(gemm_adj, AdjParams, direct_adj, gemm_adj_cfg, dense_adj)
 BOUND_PRODUCT(gemm_fwd, FwdParams, direct_fwd, gemm_fwd_cfg, dense_fwd)

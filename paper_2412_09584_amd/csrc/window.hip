@@ -77,8 +77,10 @@ static hipError_t window_launch(const GeomSet &gs, const float *A, long n_img, c
     return launch_mfma_dma<Epi, 32, 64>(gs, ct, lds, A, n_img, epi, st);
 }
 
-hipError_t window_relax(const GeomSet &gs, const float *A, long n_img, const RelaxParams &p,
+hipError_t window_relax(const GeomSet &gs, const GeomSet &pair, const float *A, long n_img, const RelaxParams &p,
                         const WinMap &w, hipStream_t st) {
+    if (conv_split_pair_fits(pair, n_img)) return conv_split_relax_win(pair, true, A, n_img, p, w, st);
+    if (conv_split_fits(gs, n_img, true)) return conv_split_relax_win(gs, false, A, n_img, p, w, st);
     ConvTile ct{};
     int mf = 0;
     size_t lds = 0;
