@@ -952,6 +952,8 @@ bound_status bound_backward(bound_net *net, const bound_pass *P, const bound_out
             rp.img0 = img0;
             rp.rpi = rpi;
             rp.rrpi = 1.0f / (float)rpi;
+            rp.rDd = 1.0 / (double)rp.D;
+            rp.rrpid = 1.0 / (double)rpi;
             rp.bsum = inject ? net->bsum : nullptr;   // split terms fused into the epilogue
             {
                 bound_status bs = det_begin(net, st, m, n_img, rp.det);
@@ -1151,6 +1153,8 @@ bound_status grad_impl(bound_net *net, int64_t pass_id, int32_t n_inst, int32_t 
                 rp.img0 = 0;
                 rp.rpi = rows;
                 rp.rrpi = 1.0f / (float)rows;
+                rp.rDd = 1.0 / (double)rp.D;
+                rp.rrpid = 1.0 / (double)rows;
                 rp.bsum = net->s_inject ? net->bsum : nullptr;
                 {
                     ProfScope ps(net, st, lbl("recompute_L%d", p));

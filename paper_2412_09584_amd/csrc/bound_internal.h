@@ -80,6 +80,7 @@ struct RelaxParams {       // G_m = Lambda_m W_m  ->  Lambda_{m-1} = relax(G_m)
     long img0;             // global img index of local img 0
     int rpi;               // imgs per instance
     float rrpi;            // fl(1 / rpi)
+    double rDd, rrpid;     // 1 / D and 1 / rpi in FP64, set with bsum
     const float *bsum;     // [nnz][rpi] split-multiplier term per first split entry and
                            // row, subtracted at the split neuron (nullable: no beta)
     DetSums det;           // deterministic row sums (det.part null: float atomics)

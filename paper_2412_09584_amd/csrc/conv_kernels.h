@@ -979,7 +979,7 @@ hipError_t try_direct(const GeomSet &gs, const float *X, long n_img, const Epi &
         // DMA staging of the chunk that register staging would take, where it fits: the same
         // sums (they are formed chunk by chunk) and the same products accepted.  4096
         // subdomains of the 3x32x32 CNN, registers -> DMA: relaxing products of its layers 2
-        // .. 4 2.24, 2.04, 1.91 -> 2.20, 1.77, 1.65, the 3x3 layer's adjoint 2.66 -> 2.02, the
+        // .. 4 2.24, 2.04, 1.91 -> 2.04, 1.77, 1.65, the 3x3 layer's adjoint 2.66 -> 2.02, the
         // concretising product 1.17 -> 0.94 ms.  Fewer blocks than CUs keep the registers,
         // which fetch the next chunk during this one's products: a block alone on its CU has
         // no other to hide DMA's wait (gradient of one subdomain: 306 and 314 us).

@@ -140,8 +140,10 @@ struct EpiRelax {
     // instance is recovered from the row's output pointer (only on this rare path, so the
     // common path keeps no extra register per row)
     __device__ float split_term(const Row &rc, int q) const {
-        const long gi = p.img0 + (long)((double)(rc.out - p.out) / (double)p.D + 0.5);   // exact multiple
-        const long r = gi - ldiv_by(gi, p.rpi, p.rrpi) * p.rpi;
+        // (host reciprocals: a division here costs 12 registers in every tile's epilogue, two
+        // waves per SIMD of the 16-channel relaxing product: 2.05 -> 2.15 ms on 4096 subdomains)
+        const long gi = p.img0 + ldiv64(rc.out - p.out, p.rDd);   // exact multiple of D
+        const long r = gi - ldiv64(gi, p.rrpid) * p.rpi;
         return p.bsum[(long)q * p.rpi + r];
     }
     __device__ float colv(int n) const { return p.bias[n % p.chan]; }

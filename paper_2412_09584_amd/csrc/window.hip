@@ -6,9 +6,9 @@
 // x 4 one 16-row MFMA fragment's.
 //
 // Full CROWN of 64 inputs of the 3x32x32 CNN (conv 16@3x3, 32@4x4/2, 32@3x3, 64@4x4/2, FC
-// 512, 10): 278 ms over whole layers, 47 ms with windows (one input: 4.93 and 1.20 ms).  The
-// windows' MFMA products run at 54 TFLOP/s: a tile is small, and 23 to 44 % of its pixels
-// pad the window to 4, 8 or 16 a side.
+// 512, 10): 278 ms over whole layers, 46 ms with windows on the FP32 kernels here, 34.8 ms
+// with the larger relaxing products on conv_split.hip's (one input: 4.93, 0.97, 0.85 ms).  23
+// to 44 % of a window's pixels pad it to 4, 8 or 16 a side.
 #include "conv_kernels.h"
 
 namespace bp {
