@@ -487,7 +487,7 @@ def other_configs(w_cnn, bb, stream):
         "inputs_per_s": n2 / (ms2 / 1e3), "ms_per_batch": ms2, "flop_per_input": f2,
         "tflops": f2 * n2 / (ms2 / 1e3) / 1e12,
         "frac_fp32_mfma": f2 * n2 / (ms2 / 1e3) / PEAK_FP32_MFMA,
-        "note": "padding taps excluded from the FLOP count"}
+        "note": "FLOP of the whole-layer passes, padding taps excluded; window passes do fewer"}
     # alpha-CROWN on the CNN: 64 inputs, 20 Adam steps, as one HIP graph
     lo, hi = bn2.crown_bounds(xl2, xh2)
     opt = N.AlphaBetaOptimizer(bn2, C2, lo, hi, xl2, xh2, steps=20, lr=0.1, alpha0=0.5,
