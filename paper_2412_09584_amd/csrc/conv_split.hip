@@ -28,7 +28,8 @@
 // Full CROWN of the 3x32x32 CNN (conv 16@3x3, 32@4x4/2, 32@3x3, 64@4x4/2, FC 512, 10), error
 // of all bounds against FP64: 1.6e-7 relative, with the FP32 kernels 1.7e-7.  64 inputs, FP32
 // kernels -> these: windows on the stride-2 layer 12.6 -> 9.2 ms, on the 3x3 layer 6.1 -> 4.1;
-// whole 3x3 and 64-channel layers 6.1 -> 4.5.
+// whole 3x3 and 64-channel layers 6.1 -> 4.5.  Nor do few blocks favour the FP32 kernels: whole
+// 3x3 layer, 18 images 21 -> 18 us, 144 images 24 -> 20, 576 images 39 -> 38.
 #include "conv_kernels.h"
 
 namespace bp {
@@ -292,9 +293,8 @@ bool fits(const GeomSet &gs, long n_img, bool window) {
     ConvTile ct{};
     size_t lds = 0;
     if (gs.n <= 0 || n_img <= 0 || !tile_split(gs, ct, lds, window)) return false;
-    // fewer blocks than CUs: the kernels that spread a product wider
     const long blocks = (n_img + ct.G - 1) / ct.G * ct.tiles_y * ((gs.g[0].N + SBN - 1) / SBN) * gs.n;
-    return blocks >= 256 && blocks <= 0x7fffffffL;
+    return blocks <= 0x7fffffffL;
 }
 
 }  // namespace
