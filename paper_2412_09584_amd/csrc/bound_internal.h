@@ -176,7 +176,16 @@ hipError_t gemm_fwd_cfg(const GeomSet &gs, const float *A, long n_img, const Fwd
 int gemm_candidates(const GeomSet &gs, int *cfgs, int cap);
 // dense.hip: wave-per-tile kernels for dense products with few tiles (configurations that
 // follow the GEMM's); dense_auto picks one, or -1 where the LDS-tiled GEMM serves better
-inline bool is_dense(const Geom &g) { return g.H == 1 && g.W == 1 && g.kh == 1 && g.kw == 1; }
+//
+// Dense means that row m of the product is img m and its columns are all of the result: one
+// geometry, one source pixel, one tap on it, one result pixel.  A convolution with one source
+// pixel and tap can fall short of that (a stride-2 2x2 layer onto one pixel has four phases,
+// a padded 1x1 layer several result pixels) and takes the implicit GEMM's gather.
+inline bool is_dense(const GeomSet &gs) {
+    const Geom &g = gs.g[0];
+    return gs.n == 1 && g.H == 1 && g.W == 1 && g.OH == 1 && g.OW == 1 && g.DH == 1 && g.DW == 1 &&
+           g.kh == 1 && g.kw == 1 && g.pad_y == 0 && g.pad_x == 0;
+}
 enum { DENSE_W32 = 11, DENSE_W16 = 12, DENSE_W16K4 = 13, DENSE_W16K16 = 14, DENSE_W16O = 15, DENSE_SPLIT = 16, DENSE_F32 = 17 };
 int dense_auto(const GeomSet &gs, long M, bool keep);
 hipError_t dense_relax(const GeomSet &gs, const float *A, long M, const RelaxParams &p, hipStream_t st, int cfg);

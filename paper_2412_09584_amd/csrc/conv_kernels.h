@@ -923,7 +923,7 @@ hipError_t try_direct(const GeomSet &gs, const float *X, long n_img, const Epi &
                       int want_cc, int mode, bool *used) {
     *used = false;
     const Geom &g = gs.g[0];
-    if (g.H == 1 && g.W == 1 && g.kh == 1 && g.kw == 1) return hipSuccess;  // dense: GEMM
+    if (g.H == 1 && g.W == 1 && g.kh == 1 && g.kw == 1) return hipSuccess;  // one pixel and tap: GEMM
     if (!same_shape(gs) || n_img <= 0) return hipSuccess;
     ConvTile ct{};
     if (!plan_tile(g, ct)) return hipSuccess;

@@ -184,7 +184,7 @@ hipError_t run(const GeomSet &gs, const float *A, long M, const Epi &epi, hipStr
 
 int dense_auto(const GeomSet &gs, long M, bool keep) {
     const Geom &g = gs.g[0];
-    if (!is_dense(g) || M <= 0) return -1;
+    if (!is_dense(gs) || M <= 0) return -1;
     const long big = (M + 127) / 128 * ((g.N + 127) / 128);       // tiles of the LDS-tiled GEMM
     // one tile per CU: below, the wave kernels are faster (160 tiles, K = 512: 95 -> 63 us; 3
     // tiles, K = 296: 75 -> 12 us), above they re-read A and B too often (384 tiles of K =

@@ -354,7 +354,7 @@ hipError_t launch_cfg(const GeomSet &gs, const float *A, long n_img, const Epi &
     const long tiles = ((Mmax + BM - 1) / BM) * ((g0.N + BN - 1) / BN) * gs.n;
     if (tiles > 0x7fffffffL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)tiles);   // tile order: xcd_tile
-    const bool dense = g0.H == 1 && g0.W == 1 && g0.kh == 1 && g0.kw == 1;
+    const bool dense = is_dense(gs);
     const bool vec = (g0.C % 4 == 0) && (g0.K % 4 == 0);
     for (int i = 0; i < gs.n; ++i) {
         if (!dense && gs.g[i].K > KDEC_MAX) return hipErrorInvalidValue;  // layer too wide

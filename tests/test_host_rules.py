@@ -1,0 +1,35 @@
+"""Host rules that choose a product's kernel, without a GPU: a small host program links the
+library and calls its rules on geometries as bound_init builds them.
+"""
+import os
+import subprocess
+
+import pytest
+
+from paper_2412_09584_amd import build as BUILD
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+SRC = os.path.join(HERE, "host_rules.cpp")
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    from paper_2412_09584_amd import binding as B
+    B.lib()                                              # built, or built now
+    exe = str(tmp_path_factory.mktemp("rules") / "host_rules")
+    lib = os.path.dirname(BUILD.OUT)
+    r = subprocess.run([BUILD.HIPCC, "--offload-host-only", "-O1", "-std=c++17", "-I", BUILD.CSRC,
+                        "-I", os.path.join(BUILD.ROOT, "include"), SRC, "-o", exe, "-L", lib, "-lbound",
+                        f"-Wl,-rpath,{lib}"], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+
+    def run(name):
+        r = subprocess.run([exe, name], capture_output=True, text=True)
+        assert r.returncode == 0, r.stdout + r.stderr
+    return run
+
+
+def test_dense_products_are_one_geometry_with_one_pixel_and_tap(rules):
+    """Only those may take the kernels whose row m is img m: a stride-2 layer onto one pixel has
+    several phases with one source pixel and tap, a padded 1x1 layer several result pixels."""
+    rules("dense")
