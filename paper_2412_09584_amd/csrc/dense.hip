@@ -189,7 +189,8 @@ int dense_auto(const GeomSet &gs, long M, bool keep) {
     // one tile per CU: below, the wave kernels are faster (160 tiles, K = 512: 95 -> 63 us; 3
     // tiles, K = 296: 75 -> 12 us), above they re-read A and B too often (384 tiles of K =
     // 296: 40 -> 50 us)
-    if (big >= 256) return keep ? (g.N >= 32 ? DENSE_F32 : -1) : DENSE_SPLIT;
+    // (a 1x1 convolution on one pixel has no bf16 weights)
+    if (big >= 256) return !keep && g.Bs ? DENSE_SPLIT : (g.N >= 32 ? DENSE_F32 : -1);
     const long small = (M + 15) / 16 * ((g.N + 15) / 16);
     // the general GEMM's default tiles are 32x32x2 from 32 columns on
     if (keep) return g.N < 32 ? DENSE_W16 : (small <= 4096 ? DENSE_W16O : DENSE_W32);

@@ -17,7 +17,7 @@ int gemm_candidates(const GeomSet &gs, int *cfgs, int cap) {
     }
     // the wave-per-tile kernels (they never repeat padding columns past a tile)
     for (int c = DENSE_W32; c <= DENSE_F32 && n < cap && is_dense(gs); ++c)
-        if (c != DENSE_W16K16 || g.K >= 256) cfgs[n++] = c;
+        if ((c != DENSE_W16K16 || g.K >= 256) && (c != DENSE_SPLIT || g.Bs)) cfgs[n++] = c;
     return n;
 }
 
@@ -69,7 +69,8 @@ hipError_t gemm_relax(const GeomSet &gs, const float *A, long n_img, const Relax
             if (used || e != hipSuccess) return e;                                           \
             const int d = plan.path == 0 ? dense_auto(gs, n_img, plan.keep) : -1;            \
             if (d >= 0) return DENSE(gs, A, n_img, p, st, d);                                \
-        } else if (plan.cfg >= DENSE_W32 && is_dense(gs)) {                                  \
+        } else if (plan.cfg >= DENSE_W32 && is_dense(gs) &&                                  \
+                   (plan.cfg != DENSE_SPLIT || gs.g[0].Bs)) {                                \
             return DENSE(gs, A, n_img, p, st, plan.cfg);                                     \
         }                                                                                    \
         return CFG(gs, A, n_img, p, st, plan.path == 2 ? plan.cfg : -1);                     \

@@ -69,8 +69,27 @@ static void dense() {
     }
 }
 
+// The bf16 tile needs the weights packed for it, which a convolution's dense products lack.
+static void split_weights() {
+    const unsigned short w = 0;
+    GeomSet gs = one(pixel(64, 128));
+    for (long m : {1L, 100000L}) {
+        check(dense_auto(gs, m, false) != DENSE_SPLIT, "chosen without weights");
+        gs.g[0].Bs = &w;
+        check((dense_auto(gs, m, false) == DENSE_SPLIT) == (m > 1), "chosen with weights");
+        gs.g[0].Bs = nullptr;
+    }
+    for (int c : listed(gs)) check(c != DENSE_SPLIT, "listed without weights");
+    check(tall_relax(gs, nullptr, 1, RelaxParams{}, nullptr, true) == hipErrorInvalidValue, "relaxing product");
+    check(tall_conc(gs, nullptr, 1, ConcParams{}, nullptr, true) == hipErrorInvalidValue, "concretising product");
+    gs.g[0].Bs = &w;
+    bool found = false;
+    for (int c : listed(gs)) found = found || c == DENSE_SPLIT;
+    check(found, "listed with weights");
+}
+
 int main(int argc, char **argv) {
-    const struct { const char *name; void (*f)(); } tests[] = {{"dense", dense}};
+    const struct { const char *name; void (*f)(); } tests[] = {{"dense", dense}, {"split_weights", split_weights}};
     for (auto &t : tests)
         if (argc == 2 && !std::strcmp(argv[1], t.name)) {
             t.f();

@@ -81,3 +81,38 @@ def test_one_pixel_convolutions(name, path):
         z = O.forward(net, x[i:i + 1].double().cpu().numpy())
         _close(slo[i], np.concatenate([v.reshape(-1) for v in z[:-1]]), "samples")
         _close(out[i], z[-1].reshape(-1), "outputs")
+
+
+def test_dense_convolution_without_bf16_weights():
+    """A 1x1 layer on one pixel from 256 tiles of 128 x 128 on, where Linear layers take the
+    bf16 tile: automatic, pinned (the plan falls back) and tuned."""
+    from paper_2412_09584_amd import binding as B
+    from paper_2412_09584_amd import net as N
+    rng = np.random.default_rng(195)
+    net = [W._conv(rng, (24, 1, 1), 300, 1, 1, 0), W._conv(rng, (300, 1, 1), 300, 1, 1, 0),
+           W._conv(rng, (300, 1, 1), 20, 1, 1, 0), W._linear(rng, 20, 4)]
+    n, R = 3000, 4
+    x_lo, x_hi = W.linf_box(W.uniform_inputs(n, 24, 196), 0.05)
+    C = np.random.default_rng(197).normal(0, 1, (n, R, 4)).astype(np.float32)
+    bn = N.BoundNet(net, n, n * 2 * R)          # 24000 rows x 300 columns: 564 tiles
+    small = [N.BoundNet(net, 1, 2 * 300).crown_bounds(x_lo[i:i + 1], x_hi[i:i + 1]) for i in range(n)]
+    lo, hi = (torch.cat([b[k] for b in small]) for k in (0, 1))
+    del small
+    rows = (0, 1, n - 1)
+    want = {}
+    for i in rows:
+        b = list(zip(O.per_layer(net, lo[i].double().cpu().numpy()), O.per_layer(net, hi[i].double().cpu().numpy())))
+        want[i] = O.spec_lower(net, 4, C[i], b, x_lo[i], x_hi[i])
+    for plan in ("auto", "pinned", "tuned"):
+        if plan == "pinned":
+            for k in (1, 2, 3):
+                for p in "RC":
+                    B.bound_set_plan(bn.handle, p, k, 2, 16, 0)
+        if plan == "tuned":
+            low, up = torch.empty(n, R, device="cuda"), torch.empty(n, R, device="cuda")
+            t = lambda a: torch.as_tensor(a, device="cuda")
+            B.bound_autotune(bn.handle, n, R, 4, spec=t(C), lo=lo, hi=hi, n_bounds=n, x_lo=t(x_lo), x_hi=t(x_hi),
+                             lower=low, upper=up, flags=B.BOUND_BOTH_SIDES)
+        low, _ = bn.spec_bounds(C, lo, hi, x_lo, x_hi)
+        for i in rows:
+            _close(low[i].double().cpu().numpy(), want[i], f"{plan}, instance {i}")

@@ -33,3 +33,9 @@ def test_dense_products_are_one_geometry_with_one_pixel_and_tap(rules):
     """Only those may take the kernels whose row m is img m: a stride-2 layer onto one pixel has
     several phases with one source pixel and tap, a padded 1x1 layer several result pixels."""
     rules("dense")
+
+
+def test_bf16_tile_needs_packed_weights(rules):
+    """A 1x1 convolution on one pixel is dense but has no bf16 weights: neither the automatic
+    rule nor the tuner's list may give it that tile, and its launcher refuses it."""
+    rules("split_weights")
