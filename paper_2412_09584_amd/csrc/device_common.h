@@ -379,6 +379,7 @@ __device__ inline void put_row_sums(const Epi &epi, long img, int dp, int n0, fl
 
 // Sum of r0 / r1 over the lanes that hold the same output row (they differ only in the
 // column bits of the lane id), then one sum pair per row from the column-0 lane.
+// img < 0: none; so for a wave whose columns all lie past the last one, which has no slot.
 template <int MF, class Epi>
 __device__ inline void reduce_row(const Epi &epi, float r0, float r1, int img, int dp, int n0,
                                   int lane) {
@@ -509,7 +510,7 @@ __device__ inline void tile_epilogue_impl(const Epi &epi, Acc (&acc)[FM][FN], co
                                          acc[i][j][vg * 4 + q], r0, r1);
                             }
                     }
-                    if (NR > 0) reduce_row<MF>(epi, r0, r1, img[q], dp[q], ncol[0], lane);
+                    if (NR > 0) reduce_row<MF>(epi, r0, r1, ncol[0] < N ? img[q] : -1, dp[q], ncol[0], lane);
                 }
             }
         }
@@ -556,7 +557,7 @@ __device__ inline void tile_epilogue_impl(const Epi &epi, Acc (&acc)[FM][FN], co
             if (NR > 0 && !FAST) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    reduce_row<MF>(epi, r0[q], r1[q], img[q], dp[q], ncol[0], lane);
+                    reduce_row<MF>(epi, r0[q], r1[q], ncol[0] < N ? img[q] : -1, dp[q], ncol[0], lane);
             }
         }
     }
