@@ -291,7 +291,7 @@ bound_status bound_adam(int64_t n, float *param, const float *grad, float *m, fl
  * is being captured.  The environment variable BOUND_DEBUG=1 sets it at bound_init. */
 /* BOUND_OPT_DETERMINISTIC: the row sums of the products (the bias and intercept terms
  * of Theorem 1, the concretised bound of Theorem 2 and the rounding-allowance
- * magnitudes) are formed without float atomics: every tile stores its partial sums in
+ * magnitudes) are formed without atomics: every tile stores its partial sums in
  * a slot of its own and the slots are added in a fixed order, so bound_backward's
  * results are bitwise reproducible run to run (the gradient already is); slower.  The
  * slots take max_rows x (output pixels x ceil(channels / 16), at most over the layers)

@@ -54,7 +54,7 @@ struct bound_net {
     long max_rows = 0, max_save_rows = 0, max_d = 0;
     std::vector<void *> allocs;
     float *buf[2] = {nullptr, nullptr};
-    float *acc_s = nullptr, *acc_mag = nullptr, *acc_low = nullptr;
+    double *acc_s = nullptr, *acc_mag = nullptr, *acc_low = nullptr;
     Relax *tab = nullptr;
     int32_t *slot = nullptr;         // compact save slots of the unstable neurons per bound row
     int32_t *slot_inv = nullptr;     // slot -> internal neuron index, per bound row
@@ -214,7 +214,7 @@ long det_slots(const bound_net *net, int m) {
 }
 
 // With BOUND_OPT_DETERMINISTIC: the zeroed slots of the product of layer m for n_img imgs
-// (det.part stays null otherwise: float atomics).
+// (det.part stays null otherwise: FP64 atomics).
 bound_status det_begin(bound_net *net, hipStream_t st, int m, long n_img, DetSums &det) {
     det = DetSums{};
     if (!(net->options & BOUND_OPT_DETERMINISTIC)) return BOUND_OK;
@@ -231,7 +231,8 @@ bound_status det_begin(bound_net *net, hipStream_t st, int m, long n_img, DetSum
 // BOUND_OPT_CHECK: count the NaN / Inf values of n floats at p (a product's output) and
 // fail with BOUND_E_NUMERIC naming `what` if there are any.  Synchronises the stream;
 // skipped while the stream is being captured.
-bound_status debug_check(bound_net *net, hipStream_t st, const float *p, long n, const std::string &what) {
+template <class T>
+bound_status debug_check(bound_net *net, hipStream_t st, const T *p, long n, const std::string &what) {
     if (!(net->options & BOUND_OPT_CHECK) || !p || n <= 0) return BOUND_OK;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return BOUND_OK;

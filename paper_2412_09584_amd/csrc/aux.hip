@@ -185,10 +185,11 @@ __global__ void k_alpha_split_zero(int nnz, int layer0, int layers, const LayerS
     galpha[(long)sp_inst[q] * ga_ld + L.off + (long)c * L.HW + p] = 0.f;
 }
 
-__global__ void k_count_nonfinite(const float *p, long n, int32_t *cnt) {
+template <class T>
+__global__ void k_count_nonfinite(const T *p, long n, int32_t *cnt) {
     int a = 0, b = 0;
     for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-        const float v = p[i];
+        const float v = (float)p[i];
         a += v != v;
         b += isinf(v);
     }
@@ -437,7 +438,7 @@ __global__ void k_prep_box(const BoxParams bx) {
 template <int TPI>
 __global__ __launch_bounds__(256) void k_init_spec(long img0, long n_img, int rows, int rpi, const float *spec,
                                                    long dk, int Ck, int HWk, const float *bias_k, float *lam,
-                                                   float *s, float *mag, float *low) {
+                                                   double *s, double *mag, double *low) {
     const long li = (long)blockIdx.x * (256 / TPI) + threadIdx.x / TPI;
     const int t0 = threadIdx.x & (TPI - 1);
     if (li >= n_img) return;
@@ -523,10 +524,10 @@ __global__ void k_init_identity(const IdentityParams p, long n_img) {
             p.s[li] = bk;
             p.low[li] = a;
         } else {
-            p.s[li] = bk + a;
+            p.s[li] = (double)bk + a;
             p.low[li] = 0.f;
         }
-        p.mag[li] = fabsf(bk) + b;
+        p.mag[li] = (double)fabsf(bk) + b;
     }
 }
 
@@ -623,13 +624,13 @@ __global__ __launch_bounds__(256) void k_init_dense(const IdentityParams p, cons
     if ((lane & (64 / ID_ROWS - 1)) != 0 || r0 + q >= p.dk) return;
     const float bk = p.bias_k[r0 + q];
     if (up + q >= 0 && up + q < n_img) {
-        p.s[up + q] = bk + a;
-        p.mag[up + q] = fabsf(bk) + b;
+        p.s[up + q] = (double)bk + a;
+        p.mag[up + q] = (double)fabsf(bk) + b;
         p.low[up + q] = 0.f;
     }
     if (both && dn + q >= 0 && dn + q < n_img) {
-        p.s[dn + q] = -bk + c;
-        p.mag[dn + q] = fabsf(bk) + d;
+        p.s[dn + q] = c - (double)bk;
+        p.mag[dn + q] = (double)fabsf(bk) + d;
         p.low[dn + q] = 0.f;
     }
 }
@@ -710,8 +711,8 @@ __global__ __launch_bounds__(256) void k_init_window(const IdentityParams p, con
     b = wave_sum(b);
     if (lane == 0) {
         const float bk = sg * p.bias_k[co];
-        p.s[li] = bk + a;
-        p.mag[li] = fabsf(bk) + b;
+        p.s[li] = (double)bk + a;
+        p.mag[li] = (double)fabsf(bk) + b;
         p.low[li] = 0.f;
     }
 }
@@ -772,8 +773,8 @@ __global__ void k_beta_sum(int nnz, int rows, const int32_t *off, const int32_t 
     bsum[e] = s;
 }
 
-__global__ void k_finalize(long img0, long n_img, int rows, int rpi, const float *s,
-                           const float *low, const float *mag, const int32_t *infeas, int slack,
+__global__ void k_finalize(long img0, long n_img, int rows, int rpi, const double *s,
+                           const double *low, const double *mag, const int32_t *infeas, int slack,
                            float *lower, float *upper, long ld, float *offset, float *offset_mag,
                            float *best, float *best_upper, int pC, int pHW) {
     const long li = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -785,11 +786,12 @@ __global__ void k_finalize(long img0, long n_img, int rows, int rpi, const float
         const int nr = rr < rows ? rr : rr - rows, pix = nr / pC;
         rr += (nr - pix * pC) * pHW + pix - nr;
     }
-    if (offset) offset[gimg] = s[li];
-    if (offset_mag) offset_mag[gimg] = mag[li];
+    if (offset) offset[gimg] = (float)s[li];
+    if (offset_mag) offset_mag[gimg] = (float)mag[li];
     if (!lower) return;
-    float v = s[li] + low[li];
-    if (slack) v -= KAPPA_U * mag[li];
+    double sum = s[li] + low[li];
+    if (slack) sum -= KAPPA_U * mag[li];
+    float v = (float)sum;
     if (infeas[inst]) v = INFINITY;
     if (rr < rows) {
         lower[inst * ld + rr] = v;
@@ -861,7 +863,7 @@ __global__ void k_beta_repeat(int nnz, int rows, const int32_t *sp_inst, const i
 // lower/mag[img] += sum_j lam c - |lam| r, sum_j |lam| (|c| + r) over one row of internal-order
 // coefficients, c / r the per-instance box (early stop over a pre-activation box).
 __global__ void k_box_conc(long img0, int rpi, long D, const float *lam, const float *cen,
-                           const float *rad, float *low, float *mag, float *save) {
+                           const float *rad, double *low, double *mag, float *save) {
     const long li = blockIdx.x;
     const long inst = (img0 + li) / rpi;
     const float *row = lam + li * D;
@@ -1156,20 +1158,27 @@ __global__ void k_pack_F(const float *W, int kind, int ci, int hwin, int kh, int
 
 }  // namespace
 
-hipError_t launch_count_nonfinite(const float *p, long n, int32_t *cnt, hipStream_t st) {
+template <class T>
+static hipError_t count_nonfinite(const T *p, long n, int32_t *cnt, hipStream_t st) {
     if (n <= 0) return hipSuccess;
     const long nb = blocks_for(n) < 4096 ? blocks_for(n) : 4096;
-    hipLaunchKernelGGL(k_count_nonfinite, dim3((unsigned)nb), dim3(TPB), 0, st, p, n, cnt);
+    hipLaunchKernelGGL(k_count_nonfinite<T>, dim3((unsigned)nb), dim3(TPB), 0, st, p, n, cnt);
     return hipGetLastError();
+}
+hipError_t launch_count_nonfinite(const float *p, long n, int32_t *cnt, hipStream_t st) {
+    return count_nonfinite(p, n, cnt, st);
+}
+hipError_t launch_count_nonfinite(const double *p, long n, int32_t *cnt, hipStream_t st) {
+    return count_nonfinite(p, n, cnt, st);
 }
 
 // One wave per img: lane l sums slots l, l + 64, ... in order, then a fixed xor tree.
-__global__ void k_det_reduce(long n_img, long nslot, const float *part, float *s, float *mag) {
+__global__ void k_det_reduce(long n_img, long nslot, const float *part, double *s, double *mag) {
     const long img = (long)blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64;
     const int lane = threadIdx.x & 63;
     if (img >= n_img) return;
     const float *p = part + img * nslot * 2;
-    float a = 0.f, b = 0.f;
+    double a = 0.0, b = 0.0;
     for (long k = lane; k < nslot; k += 64) {
         a += p[2 * k];
         b += p[2 * k + 1];
@@ -1185,7 +1194,7 @@ __global__ void k_det_reduce(long n_img, long nslot, const float *part, float *s
     }
 }
 
-hipError_t launch_det_reduce(long n_img, long nslot, const float *part, float *s, float *mag,
+hipError_t launch_det_reduce(long n_img, long nslot, const float *part, double *s, double *mag,
                              hipStream_t st) {
     if (n_img <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_det_reduce, dim3((unsigned)((n_img + 3) / 4)), dim3(256), 0, st, n_img,
@@ -1262,8 +1271,8 @@ hipError_t launch_prep_box(const BoxParams &box, hipStream_t st) {
 }
 
 hipError_t launch_init_spec(long img0, long n_img, int rows, int rpi, const float *spec, long dk,
-                            int Ck, int HWk, const float *bias_k, float *lam, float *s,
-                            float *mag, float *low, hipStream_t st) {
+                            int Ck, int HWk, const float *bias_k, float *lam, double *s,
+                            double *mag, double *low, hipStream_t st) {
     if (dk > 256)
         hipLaunchKernelGGL(k_init_spec<256>, dim3((unsigned)n_img), dim3(TPB), 0, st, img0, n_img, rows, rpi,
                            spec, dk, Ck, HWk, bias_k, lam, s, mag, low);
@@ -1322,8 +1331,8 @@ hipError_t launch_beta_sum(int nnz, int rows, const int32_t *off, const int32_t 
     return hipGetLastError();
 }
 
-hipError_t launch_finalize(long img0, long n_img, int rows, int rpi, const float *s,
-                           const float *low, const float *mag, const int32_t *infeas, bool slack,
+hipError_t launch_finalize(long img0, long n_img, int rows, int rpi, const double *s,
+                           const double *low, const double *mag, const int32_t *infeas, bool slack,
                            float *lower, float *upper, long ld, float *offset, float *offset_mag,
                            float *best, float *best_upper, hipStream_t st, int pC, int pHW) {
     hipLaunchKernelGGL(k_finalize, dim3(blocks_for(n_img)), dim3(TPB), 0, st, img0, n_img, rows,
@@ -1366,7 +1375,7 @@ hipError_t launch_prep_stop_box(int n_inst, const LayerShape &L, long n_relu, co
 }
 
 hipError_t launch_box_conc(long img0, long n_img, int rpi, long D, const float *lam, const float *cen,
-                           const float *rad, float *low, float *mag, float *save, hipStream_t st) {
+                           const float *rad, double *low, double *mag, float *save, hipStream_t st) {
     if (n_img <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_box_conc, dim3((unsigned)n_img), dim3(TPB), 0, st, img0, rpi, D, lam, cen,
                        rad, low, mag, save);

@@ -57,6 +57,12 @@ struct GeomSet {
 typedef float4 Relax;
 
 // ----- epilogue parameter blocks -----------------------------------------------------
+// A row's sums are accumulated in FP64: a tile adds its FP32 partial sums, and with an FP32
+// running sum each of these additions rounds at the size of the whole sum, the more often the
+// narrower the tiles are.  Error of the spec bounds against FP64 (root mean square, relative)
+// with FP32 sums over 64-column tiles / over 16- and 32-column tiles / with FP64 sums: one
+// 3x32x32 CNN input 2.8e-7 / 4.6e-7 / 4.0e-8, three inputs of an MLP 784-252-190-158-57-11
+// 1.0e-7 / 1.6e-7 / 5.1e-8, 256 of 784-256x6-10 1.1e-7 / 1.1e-7 / 3.7e-8.
 // Deterministic row sums: each tile's partial sums of a row go to their own slot
 // part[(img * nslot + dp * ncu + n0 / 16) * 2 + {0, 1}] (dp the destination pixel of the
 // tile's first row, n0 its first column, ncu = ceil(N / 16)) of a zeroed workspace, and
@@ -76,20 +82,20 @@ struct RelaxParams {       // G_m = Lambda_m W_m  ->  Lambda_{m-1} = relax(G_m)
     const float *bias;     // b_{m-1} per channel
     int chan;              // channels of layer m-1 (bias index = j % chan)
     long D;                // width of layer m-1
-    float *s, *mag;        // per-img offset accumulator and |term| accumulator
+    double *s, *mag;       // per-img offset accumulator and |term| accumulator
     long img0;             // global img index of local img 0
     int rpi;               // imgs per instance
     float rrpi;            // fl(1 / rpi)
     double rDd, rrpid;     // 1 / D and 1 / rpi in FP64, set with bsum
     const float *bsum;     // [nnz][rpi] split-multiplier term per first split entry and
                            // row, subtracted at the split neuron (nullable: no beta)
-    DetSums det;           // deterministic row sums (det.part null: float atomics)
+    DetSums det;           // deterministic row sums (det.part null: FP64 atomics)
 };
 
 struct ConcParams {        // G_1 = Lambda_1 W_1  ->  concretise over the box
     const float *cen, *rad;  // [n_inst][d0] internal order
     long D;                // d0
-    float *low, *mag;      // per-img accumulators
+    double *low, *mag;     // per-img accumulators
     float *save;           // G_1 kept (nullable)
     float *emit;           // coefficient output in C-major order (nullable)
     int chan, hw;          // input shape for the C-major index
@@ -260,10 +266,11 @@ __host__ __device__ inline int prep_tiles(const LayerShape &L) {
 hipError_t launch_fill(float *p, long n, float v, hipStream_t st);
 // deterministic row sums: s[img] += the slots' first values, mag[img] += their second
 // values, each summed in slot order (one wave per img, a fixed shuffle tree)
-hipError_t launch_det_reduce(long n_img, long nslot, const float *part, float *s, float *mag,
+hipError_t launch_det_reduce(long n_img, long nslot, const float *part, double *s, double *mag,
                              hipStream_t st);
 // cnt[0] += NaN count, cnt[1] += Inf count of p[0 .. n) (debug checks)
 hipError_t launch_count_nonfinite(const float *p, long n, int32_t *cnt, hipStream_t st);
+hipError_t launch_count_nonfinite(const double *p, long n, int32_t *cnt, hipStream_t st);   // as FP32
 // input boxes -> centre / radius in internal order (x_lo null: zeros); infeas (nullable):
 // cleared for n_inst instances
 struct BoxParams {
@@ -300,7 +307,7 @@ hipError_t launch_prep_stop_box(int n_inst, const LayerShape &L, long n_relu, co
                                 const float *hi, const int32_t *bound_of, int n_bounds, bool relu,
                                 float *cen, float *rad, hipStream_t st);
 hipError_t launch_box_conc(long img0, long n_img, int rpi, long D, const float *lam, const float *cen,
-                           const float *rad, float *low, float *mag, float *save, hipStream_t st);
+                           const float *rad, double *low, double *mag, float *save, hipStream_t st);
 hipError_t launch_adj_stop_linear(long n_img, int rows, long D, const float *lam, const float *g,
                                   const float *cen, const float *rad, const float *gl,
                                   const int32_t *infeas, float *sbar, const Relax *tab, long tab_ld,
@@ -311,7 +318,7 @@ hipError_t launch_beta_grad_stop(int nnz, int rows, int layer, long D, const int
                                  const float *sbar, float *gbeta, hipStream_t st);
 hipError_t launch_init_spec(long img0, long n_img, int rows, int rpi, const float *spec,
                             long dk, int Ck, int HWk, const float *bias_k, float *lam,
-                            float *s, float *mag, float *low, hipStream_t st);
+                            double *s, double *mag, double *low, hipStream_t st);
 
 struct IdentityParams {
     // target layer k
@@ -335,7 +342,7 @@ struct IdentityParams {
     const float *cen, *rad;
     float *emit;
     // accumulators
-    float *s, *mag, *low;
+    double *s, *mag, *low;
 };
 hipError_t launch_init_identity(const IdentityParams &p, long n_img, bool conc, hipStream_t st);
 // identity rows of a Linear target (relaxed), W its rows in internal order with stride ldw
@@ -355,8 +362,8 @@ hipError_t launch_conv1_bounds(const IdentityParams &p, int n_inst, bool slack, 
 hipError_t launch_beta_sum(int nnz, int rows, const int32_t *off, const int32_t *idx,
                            const int8_t *sign, const int32_t *sp_inst, const int32_t *sp_layer,
                            const int32_t *sp_dup, const float *beta, float *bsum, hipStream_t st);
-hipError_t launch_finalize(long img0, long n_img, int rows, int rpi, const float *s,
-                           const float *low, const float *mag, const int32_t *infeas,
+hipError_t launch_finalize(long img0, long n_img, int rows, int rpi, const double *s,
+                           const double *low, const double *mag, const int32_t *infeas,
                            bool slack, float *lower, float *upper, long ld, float *offset,
                            float *offset_mag, float *best, float *best_upper, hipStream_t st,
                            int pC = 0, int pHW = 0);   // pC: window pass, the target's channels

@@ -147,8 +147,8 @@ struct EpiRelax {
         return p.bsum[(long)q * p.rpi + r];
     }
     __device__ float colv(int n) const { return p.bias[n % p.chan]; }
-    __device__ float *red0() const { return p.s; }
-    __device__ float *red1() const { return p.mag; }
+    __device__ double *red0() const { return p.s; }
+    __device__ double *red1() const { return p.mag; }
     __device__ const DetSums *det() const { return &p.det; }
     __device__ Pre pre(const Row &rc, int dp, int n, int N) const { return ld(rc.tb, dp * N + n); }
     __device__ void pre2(const Row &, Pre &) const {}
@@ -192,8 +192,8 @@ struct EpiConc {
         return Row{r.cen, r.rad, r.save ? r.save + (long)k * p.D : nullptr, r.emit ? r.emit + (long)k * p.D : nullptr};
     }
     __device__ float colv(int) const { return 0.f; }
-    __device__ float *red0() const { return p.low; }
-    __device__ float *red1() const { return p.mag; }
+    __device__ double *red0() const { return p.low; }
+    __device__ double *red1() const { return p.mag; }
     __device__ const DetSums *det() const { return &p.det; }
     __device__ Pre pre(const Row &rc, int dp, int n, int N) const {
         return make_float2(ld(rc.cen, dp * N + n), ld(rc.rad, dp * N + n));
@@ -224,8 +224,8 @@ struct EpiAdj {
     __device__ bool one_instance(int, int) const { return false; }   // saved rows differ
     __device__ Row at(const Row &r, int) const { return r; }
     __device__ float colv(int n) const { return p.bias[n]; }
-    __device__ float *red0() const { return nullptr; }
-    __device__ float *red1() const { return nullptr; }
+    __device__ double *red0() const { return nullptr; }
+    __device__ double *red1() const { return nullptr; }
     __device__ const DetSums *det() const { return nullptr; }
     // G is saved at the unstable neurons only (slot w - 1), a load that depends on the
     // record: pre() fetches the record, pre2() the saved coefficient.  Elsewhere x = y
@@ -260,8 +260,8 @@ struct EpiFwd {
     __device__ bool one_instance(int, int) const { return true; }
     __device__ Row at(const Row &r, int k) const { return Row{r.out + (long)k * p.D}; }
     __device__ float colv(int n) const { return p.bias[n]; }
-    __device__ float *red0() const { return nullptr; }
-    __device__ float *red1() const { return nullptr; }
+    __device__ double *red0() const { return nullptr; }
+    __device__ double *red1() const { return nullptr; }
     __device__ const DetSums *det() const { return nullptr; }
     __device__ Pre pre(const Row &, int, int, int) const { return Pre{}; }
     __device__ void pre2(const Row &, Pre &) const {}
@@ -302,8 +302,8 @@ struct EpiRelaxWin {
         return Row{p.tab + o.inst * p.tab_ld, p.out + (long)img * p.D, o.y0, o.x0};
     }
     __device__ float colv(int n) const { return p.bias[n % p.chan]; }
-    __device__ float *red0() const { return p.s; }
-    __device__ float *red1() const { return p.mag; }
+    __device__ double *red0() const { return p.s; }
+    __device__ double *red1() const { return p.mag; }
     __device__ const DetSums *det() const { return nullptr; }
     __device__ Pre pre(const Row &rc, int dp, int n, int N) const {
         const int px = win_pixel(w, rc.y0, rc.x0, dp);
@@ -340,8 +340,8 @@ struct EpiConcWin {
         return Row{p.cen + o.inst * p.D, p.rad + o.inst * p.D, o.y0, o.x0};
     }
     __device__ float colv(int) const { return 0.f; }
-    __device__ float *red0() const { return p.low; }
-    __device__ float *red1() const { return p.mag; }
+    __device__ double *red0() const { return p.low; }
+    __device__ double *red1() const { return p.mag; }
     __device__ const DetSums *det() const { return nullptr; }
     __device__ Pre pre(const Row &rc, int dp, int n, int N) const {
         const int px = win_pixel(w, rc.y0, rc.x0, dp);
@@ -361,7 +361,7 @@ struct EpiConcWin {
     }
 };
 
-// One row sum pair of a tile: a float atomic per accumulator, or with deterministic sums
+// One row sum pair of a tile: an FP64 atomic per accumulator, or with deterministic sums
 // a store to the tile's own slot (dp: destination pixel of the tile's first row, n0: its
 // first column).
 template <class Epi>
@@ -372,8 +372,8 @@ __device__ inline void put_row_sums(const Epi &epi, long img, int dp, int n0, fl
         q[0] = r0;
         q[1] = r1;
     } else {
-        atomicAdd(epi.red0() + img, r0);
-        atomicAdd(epi.red1() + img, r1);
+        atomicAdd(epi.red0() + img, (double)r0);
+        atomicAdd(epi.red1() + img, (double)r1);
     }
 }
 
@@ -667,7 +667,7 @@ __device__ inline void tile_epilogue_win(const Epi &epi, Acc (&acc)[FM][FN], con
     int v;
     const float x = sum_rows<64, 2 * NI>(sums, lane, v);
     const long im = img0 + ((row0 + (v >> 1) * 16) >> lpx);
-    if ((lane & (64 / (2 * NI) - 1)) == 0 && im < n_img) atomicAdd((v & 1 ? epi.red1() : epi.red0()) + im, x);
+    if ((lane & (64 / (2 * NI) - 1)) == 0 && im < n_img) atomicAdd((v & 1 ? epi.red1() : epi.red0()) + im, (double)x);
 }
 
 // Epilogue of a wave that holds one MF x MF tile of a dense product (rows m0 .., M rows in
