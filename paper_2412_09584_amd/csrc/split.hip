@@ -5,16 +5,21 @@
 // of bf16 matrices accumulated in FP32; the three smallest (mid*lo, lo*mid, lo*lo, below
 // 2^-24 of a term) are left out.  v_mfma_f32_32x32x16_bf16 runs at 16 times the rate of
 // v_mfma_f32_32x32x2f32, so the six remaining ones cost 3/8 of the FP32 MFMAs, and unlike
-// those they leave the VALU free for the epilogue and the splitting.  Measured against FP64
-// on normal data with a log-normal scale, K = 16 .. 4096: error 0.68 .. 0.76 of the FP32
-// MFMA's (fewer roundings of the partial sums).
+// those they leave the VALU free for the epilogue and the splitting.
+//
+// An instruction aligns its terms with the sum it continues and cuts them off there, toward
+// minus infinity.  Continuing one sum over all of K would cut the small products at the size of
+// the whole sum: error 1.06 times the FP32 kernels'.  So a column's six products of 16 k start
+// a sum of their own, which one FP32 fused multiply-add takes into the column's: 0.39 times
+// (MLP 784-256x6-10, 16384 rows, coefficients against FP64 5.0e-7 FP32, 5.3e-7, now 2.0e-7).
 //
 // Tile: 256 threads = 4 waves of 32 rows x 32 FN columns.  The weights are split once at
 // bound_init, laid out in 32-wide k chunks ([n][chunk][part][32]), and reach LDS by DMA, two
 // buffers deep; their 16-byte k octets are stored in the order q ^ ((r >> 1) & 3) ^ ((r >> 3)
 // & 1) of row r, which spreads 16 consecutive rows over the banks.  A wave's own rows of A
 // go straight from global memory to registers, one chunk ahead, and are split there: no
-// other wave needs them.  One barrier per chunk.
+// other wave needs them.  One barrier per chunk.  Three waves a SIMD (168 registers) hide the
+// chains of products; with two, MLP 784-256x6-10, 256 inputs: 3.87 -> 4.27 ms.
 //
 // 131072 rows, K = 256: N = 784 with the box 0.59 -> 0.39 ms (135 TFLOP/s of FP32 products),
 // N = 256 with the relaxation 0.22 -> 0.12 ms.
@@ -42,7 +47,7 @@ constexpr int SK = 32;           // k per chunk
 constexpr int SBM = 128;         // rows per block
 
 // x = hi + mid + lo, eight values at a time
-__device__ inline void split8(const float (&x)[8], bf8 &hi, bf8 &mid, bf8 &lo) {
+__device__ inline void split8(const float *x, bf8 &hi, bf8 &mid, bf8 &lo) {
     u4 h, m, l;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -60,18 +65,18 @@ __device__ inline void split8(const float (&x)[8], bf8 &hi, bf8 &mid, bf8 &lo) {
     lo = __builtin_bit_cast(bf8, l);
 }
 
+// Sign of chunk c's weights in the 32 columns of tile y.
+__host__ __device__ inline bool chunk_sign(int c, int y) { return (__builtin_popcount(c) + y) & 1; }
+
 __device__ inline int swz(int r) { return ((r >> 1) & 3) ^ ((r >> 3) & 1); }
 __device__ inline int swz8(int r) { return (r ^ (r >> 3 & 1)) & 7; }
 
-// The bf16 MFMAs round their aligned terms toward minus infinity: sums over many columns of
-// one sign (a box's centre) see that as a bias, five times the FP32 MFMA's whole error.  Half
-// of the steps (the Thue-Morse sequence, which also cancels a trend along K) accumulate the
-// negated sum, which turns their bias round, and every other column tile starts with the
-// other sign.  Full CROWN of MLP 784-256x6-10, 256 inputs, error of the bounds against FP64:
-// FP32 MFMAs 1.25e-7, without the signs 6.9e-7, with them 1.0e-7 (16-256x3-1, 2048 boxes:
-// 8.1e-8 and 7.2e-8).
+// What the cut leaves of a sum's products is a bias; sums over many columns of one sign (a
+// box's centre) would see it.  Half of the chunks' weights (the Thue-Morse sequence, which also
+// cancels a trend along K; every other column tile starts with the other sign) are stored
+// negated and their sums subtracted, which turns the bias round.
 template <class Epi, int FN, bool SPLIT>
-__global__ __launch_bounds__(256) void k_dense_tall(const Geom g, const float *__restrict__ A,
+__global__ __launch_bounds__(256, SPLIT ? 3 : 1) void k_dense_tall(const Geom g, const float *__restrict__ A,
                                                     const long M, const Epi epi) {
     using MM = Mma<32>;
     constexpr int BN = 32 * FN, SLOTS = SPLIT ? 3 * BN * 4 : BN * 8, NS = (SLOTS + 255) / 256;
@@ -107,21 +112,18 @@ __global__ __launch_bounds__(256) void k_dense_tall(const Geom g, const float *_
     // this lane's row of A: k = 16 t + 8 h + 0 .. 7 of a chunk, t = 0, 1
     const long row = m0 + col;
     const float *a = A + (row < M ? row : M - 1) * (long)K + 8 * h;     // rows past M: dropped
-    float ra[16], rn[16];
-    auto loadA = [&](int c, float (&x)[16]) {
-        const int k0 = c * SK;
-        if (k0 + SK <= K) {
+    float ra[16], rn[SPLIT ? 1 : 16];
+    auto loadA = [&](int c, int t, float *x) {       // half t of chunk c
+        const int k0 = c * SK + 16 * t;
+        if ((c + 1) * SK <= K) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const f4u v = *(const f4u *)(a + k0 + (t >> 1) * 16 + (t & 1) * 4);
-                x[4 * t] = v[0]; x[4 * t + 1] = v[1]; x[4 * t + 2] = v[2]; x[4 * t + 3] = v[3];
+            for (int q = 0; q < 2; ++q) {
+                const f4u v = *(const f4u *)(a + k0 + 4 * q);
+                x[4 * q] = v[0]; x[4 * q + 1] = v[1]; x[4 * q + 2] = v[2]; x[4 * q + 3] = v[3];
             }
         } else {
 #pragma unroll
-            for (int t = 0; t < 16; ++t) {
-                const int k = k0 + (t >> 3) * 16 + (t & 7);
-                x[t] = k + 8 * h < K ? a[k] : 0.f;
-            }
+            for (int q = 0; q < 8; ++q) x[q] = k0 + q + 8 * h < K ? a[k0 + q] : 0.f;
         }
     };
     f32x16 acc[FN];
@@ -130,21 +132,73 @@ __global__ __launch_bounds__(256) void k_dense_tall(const Geom g, const float *_
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
 
-    auto sign_of = [&](int ks) { return (unsigned)(__builtin_popcount(ks) + ti.y) & 1u; };
     dma(0, 0);
-    loadA(0, ra);
+    loadA(0, 0, ra);
+    loadA(0, 1, ra + 8);
     for (int c = 0; c < nch; ++c) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();          // chunk c has landed, and every wave is done with c - 1
         if (c + 1 < nch) {
             dma(c + 1, (c + 1) & 1);
-            loadA(c + 1, rn);
+            if constexpr (!SPLIT) {
+                loadA(c + 1, 0, rn);
+                loadA(c + 1, 1, rn + 8);
+            }
         }
         const float *B = Bs[c & 1];
+        if constexpr (SPLIT) {
+            // two columns at a time, so that one's chain of products hides the other's latency
+            constexpr int JC = FN < 2 ? 1 : 2;
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            if constexpr (!SPLIT) {
-                // the order of the general GEMM's 32x32x2 tiles: k = s and 8 + s at step s
+            for (int t = 0; t < 2; ++t) {
+                bf8 ah, am, al;
+                split8(ra + 8 * t, ah, am, al);
+                if (t == 1) {
+                    // the next chunk takes these registers; not earlier, or the second half's
+                    // split would wait for it
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (c + 1 < nch) {
+                        loadA(c + 1, 0, ra);
+                        loadA(c + 1, 1, ra + 8);
+                    }
+                }
+#pragma unroll
+                for (int j0 = 0; j0 < FN; j0 += JC) {
+                    f32x16 s[JC];
+#pragma unroll
+                    for (int j = 0; j < JC; ++j)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) s[j][v] = 0.f;
+#pragma unroll
+                    for (int p = 2; p >= 0; --p) {
+                        bf8 b[JC];
+#pragma unroll
+                        for (int j = 0; j < JC; ++j) {
+                            const int r = (j0 + j) * 32 + col;
+                            b[j] = *(const bf8 *)(B + ((p * BN + r) * 4 + ((2 * t + h) ^ swz(r))) * 4);
+                        }
+                        auto mm = [&](const bf8 &x) {
+#pragma unroll
+                            for (int j = 0; j < JC; ++j)
+                                s[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, b[j], s[j], 0, 0, 0);
+                        };
+                        if (p == 0) mm(al);
+                        if (p <= 1) mm(am);
+                        mm(ah);
+                    }
+#pragma unroll
+                    for (int j = 0; j < JC; ++j) {
+                        const float sgn = chunk_sign(c, ti.y * FN + j0 + j) ? -1.f : 1.f;
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) acc[j0 + j][v] = fmaf(s[j][v], sgn, acc[j0 + j][v]);
+                        asm volatile("" : "+v"(acc[j0 + j]));   // here, not after all columns: registers
+                    }
+                }
+            }
+        } else {
+            // the order of the general GEMM's 32x32x2 tiles: k = s and 8 + s at step s
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
                 if (c * SK + 16 * t >= K) break;
                 f32x4v b[FN][2];
 #pragma unroll
@@ -158,49 +212,10 @@ __global__ __launch_bounds__(256) void k_dense_tall(const Geom g, const float *_
                 for (int k = 0; k < 8; ++k)
 #pragma unroll
                     for (int j = 0; j < FN; ++j) acc[j] = MM::mma(ra[8 * t + k], b[j][k >> 2][k & 3], acc[j]);
-                continue;
             }
-            const int ks = 2 * c + t;
-            const unsigned sg = sign_of(ks) << 31;
-            if (ks > 0 && sign_of(ks) != sign_of(ks - 1)) {
 #pragma unroll
-                for (int j = 0; j < FN; ++j) acc[j] = -acc[j];
-            }
-            float x[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) x[i] = __uint_as_float(__float_as_uint(ra[8 * t + i]) ^ sg);
-            bf8 ah, am, al;
-            split8(x, ah, am, al);
-            bf8 b[FN];
-            auto rd = [&](int p) {
-#pragma unroll
-                for (int j = 0; j < FN; ++j) {
-                    const int r = j * 32 + col;
-                    b[j] = *(const bf8 *)(B + ((p * BN + r) * 4 + ((2 * t + h) ^ swz(r))) * 4);
-                }
-            };
-            auto mm = [&](const bf8 &x) {
-#pragma unroll
-                for (int j = 0; j < FN; ++j)
-                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, b[j], acc[j], 0, 0, 0);
-            };
-            rd(2);
-            mm(ah);
-            rd(1);
-            mm(am);
-            mm(ah);
-            rd(0);
-            mm(al);
-            mm(am);
-            mm(ah);
+            for (int i = 0; i < 16; ++i) ra[i] = rn[i];
         }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) ra[i] = rn[i];
-    }
-
-    if (SPLIT && sign_of(2 * nch - 1)) {
-#pragma unroll
-        for (int j = 0; j < FN; ++j) acc[j] = -acc[j];
     }
 
     // ---------------------------------------------------------------- epilogue
@@ -274,7 +289,8 @@ __global__ void k_pack_split(const float *Bt, int Kp, int Kc, long total, unsign
     if (e >= total) return;
     const long n = e / (Kc * SK);
     const int k = (int)(e - n * Kc * SK), c = k / SK, i = k - c * SK;
-    const float x = k < Kp ? Bt[n * Kp + k] : 0.f;
+    float x = k < Kp ? Bt[n * Kp + k] : 0.f;
+    if (chunk_sign(c, (int)(n >> 5))) x = -x;
     const __bf16 hi = (__bf16)x;
     const float r = x - (float)hi;
     const __bf16 mid = (__bf16)r, lo = (__bf16)(r - (float)mid);
