@@ -253,7 +253,8 @@ std::string lbl(const char *f, int m) {
     return buf;
 }
 
-// The dense layer's packed weights once more, as three bf16 parts (split.hip).
+// The dense layer's packed weights once more, as three bf16 parts (split.hip): the backward
+// products', the forward and adjoint ones keep the FP32 order.
 bool split_weights(bound_net *net, Geom &g, int Np, hipStream_t st) {
     unsigned short *bs = nullptr;
     g.Kc = (int)((g.K + 31) / 32);
@@ -320,7 +321,6 @@ bound_status build_geoms(bound_net *net, hipStream_t st) {
                                  (int)NpF, bf, st));
             f.Bt = bf;
             set_recips(f);
-            if (!split_weights(net, f, (int)NpF, st)) return fail(BOUND_E_NOMEM, "weight packing");
             li.gF.g[0] = f; li.gF.n = 1;
         } else {
             // forward convolution (adjoint)

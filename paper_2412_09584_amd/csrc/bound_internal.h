@@ -203,7 +203,7 @@ hipError_t dense_fwd(const GeomSet &gs, const float *A, long M, const FwdParams 
 hipError_t tall_relax(const GeomSet &gs, const float *A, long M, const RelaxParams &p, hipStream_t st, bool split);
 hipError_t tall_conc(const GeomSet &gs, const float *A, long M, const ConcParams &p, hipStream_t st, bool split);
 hipError_t tall_adj(const GeomSet &gs, const float *A, long M, const AdjParams &p, hipStream_t st);
-hipError_t tall_fwd(const GeomSet &gs, const float *A, long M, const FwdParams &p, hipStream_t st, bool split);
+hipError_t tall_fwd(const GeomSet &gs, const float *A, long M, const FwdParams &p, hipStream_t st);
 hipError_t launch_pack_split(const float *Bt, int Np, int Kp, int Kc, unsigned short *out, hipStream_t st);
 // conv.hip: direct convolution (cc = 0: largest chunk that fits; mode 1 or 3: tiles staged
 // by LDS DMA, else through registers; mode 2 or 3: 16x16 MFMA tiles for 32 output

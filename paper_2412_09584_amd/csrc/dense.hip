@@ -206,12 +206,13 @@ hipError_t dense_conc(const GeomSet &gs, const float *A, long M, const ConcParam
     if (cfg >= DENSE_SPLIT) return tall_conc(gs, A, M, p, st, cfg == DENSE_SPLIT);
     return run(gs, A, M, EpiConc{p}, st, cfg);
 }
+// the adjoint and the forward pass keep the FP32 order (no bf16 weights are packed for them)
 hipError_t dense_adj(const GeomSet &gs, const float *A, long M, const AdjParams &p, hipStream_t st, int cfg) {
-    if (cfg >= DENSE_SPLIT) return tall_adj(gs, A, M, p, st);   // gradients keep the FP32 order
+    if (cfg >= DENSE_SPLIT) return tall_adj(gs, A, M, p, st);
     return run(gs, A, M, EpiAdj{p}, st, cfg);
 }
 hipError_t dense_fwd(const GeomSet &gs, const float *A, long M, const FwdParams &p, hipStream_t st, int cfg) {
-    if (cfg >= DENSE_SPLIT) return tall_fwd(gs, A, M, p, st, cfg == DENSE_SPLIT);
+    if (cfg >= DENSE_SPLIT) return tall_fwd(gs, A, M, p, st);
     return run(gs, A, M, EpiFwd{p}, st, cfg);
 }
 

@@ -332,8 +332,8 @@ hipError_t tall_conc(const GeomSet &gs, const float *A, long M, const ConcParams
 hipError_t tall_adj(const GeomSet &gs, const float *A, long M, const AdjParams &p, hipStream_t st) {
     return run<EpiAdj, false>(gs, A, M, EpiAdj{p}, st);
 }
-hipError_t tall_fwd(const GeomSet &gs, const float *A, long M, const FwdParams &p, hipStream_t st, bool split) {
-    return split ? run<EpiFwd, true>(gs, A, M, EpiFwd{p}, st) : run<EpiFwd, false>(gs, A, M, EpiFwd{p}, st);
+hipError_t tall_fwd(const GeomSet &gs, const float *A, long M, const FwdParams &p, hipStream_t st) {
+    return run<EpiFwd, false>(gs, A, M, EpiFwd{p}, st);
 }
 
 hipError_t launch_pack_split(const float *Bt, int Np, int Kp, int Kc, unsigned short *out, hipStream_t st) {
