@@ -281,10 +281,12 @@ bound_status bound_adam(int64_t n, float *param, const float *grad, float *m, fl
 
 /* Kernel selection: BOUND_OPT_GEMM_ONLY runs every product as an implicit GEMM (the
  * LDS-tiled direct-convolution kernels are otherwise used where the layer geometry fits
- * them).  BOUND_OPT_DIRECT_DMA makes the direct-convolution kernels of products that
- * bound_autotune has not planned stage their tiles by LDS DMA instead of through
- * registers.  All variants compute the same bound; the options exist to test and
- * compare them.  BOUND_OPT_CHECK (debugging): after every product of bound_backward and
+ * them).  BOUND_OPT_DIRECT_DMA makes products that bound_autotune has not planned take the
+ * direct-convolution kernels with their tiles staged by LDS DMA (by themselves they stage
+ * through registers where there are few blocks, and passes that save nothing may take other
+ * kernels).  All variants compute the same bound; the options exist to test and compare
+ * them.  While any option is set, full CROWN's passes over convolutional layers
+ * use whole layers instead of receptive-field windows, several times slower.  BOUND_OPT_CHECK (debugging): after every product of bound_backward and
  * bound_grad the library counts NaN and Inf values in the product's output (and in the
  * gradient it returns), waits for the count, and returns BOUND_E_NUMERIC naming the
  * product if there are any; the calls become synchronous.  Not applied while the stream

@@ -147,7 +147,8 @@ struct WinMap {
 // A plan picks the kernel of one product: path 0 = automatic (direct convolution when
 // the geometry fits, else the implicit GEMM with the default tile), 1 = direct
 // convolution with channel chunk cc (0 = largest that fits), 2 = implicit GEMM with tile
-// configuration cfg (see gemm_candidates).
+// configuration cfg (see gemm_candidates).  Path 0 with cfg 1 (BOUND_OPT_DIRECT_DMA): direct
+// convolutions as in path 1 with cfg 1, dense products automatic.
 struct Plan {
     int path = 0;
     int cfg = -1;

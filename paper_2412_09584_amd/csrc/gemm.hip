@@ -54,7 +54,7 @@ static hipError_t relax_general(const GeomSet &gs, const float *A, long n_img, c
                                 hipStream_t st, const Plan &plan);
 hipError_t gemm_relax(const GeomSet &gs, const float *A, long n_img, const RelaxParams &p,
                       hipStream_t st, const Plan &plan) {
-    if (plan.path == 0 && !plan.keep && !p.save && conv_split_fits(gs, n_img, false))
+    if (plan.path == 0 && plan.cfg != 1 && !plan.keep && !p.save && conv_split_fits(gs, n_img, false))
         return conv_split_relax(gs, A, n_img, p, st);
     return relax_general(gs, A, n_img, p, st, plan);
 }
@@ -65,7 +65,8 @@ hipError_t gemm_relax(const GeomSet &gs, const float *A, long n_img, const Relax
         if (plan.path != 2) {                                                                \
             bool used = false;                                                               \
             const hipError_t e = DIRECT(gs, A, n_img, p, st, plan.path == 1 ? plan.cc : 0,   \
-                                        plan.path == 1 ? plan.cfg : DIRECT_AUTO, &used);      \
+                                        plan.path == 1 || plan.cfg == 1 ? plan.cfg : DIRECT_AUTO, \
+                                        &used);                                              \
             if (used || e != hipSuccess) return e;                                           \
             const int d = plan.path == 0 ? dense_auto(gs, n_img, plan.keep) : -1;            \
             if (d >= 0) return DENSE(gs, A, n_img, p, st, d);                                \

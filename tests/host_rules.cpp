@@ -1,11 +1,132 @@
 // Checks of the library's host rules (see test_host_rules.py): exits with 1 and a message
-// where one does not hold.
+// where one does not hold.  The program defines the HIP runtime calls that the library makes,
+// so its passes run here without a GPU: allocations are host memory, and a launch is recorded
+// by its kernel's name and grid instead of run.
+#include "bound.h"
 #include "bound_internal.h"
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
+#include <cxxabi.h>
+#include <functional>
+#include <map>
+#include <string>
 #include <vector>
 
 using namespace bp;
+
+// ---- a HIP runtime that records launches --------------------------------------------
+struct Launch { std::string name; dim3 grid, block; };
+// filled by the library's initialisers, before this program's run
+static std::map<const void *, std::string> &kernels() {
+    static auto *m = new std::map<const void *, std::string>;
+    return *m;
+}
+static std::vector<Launch> launches;
+static std::function<float()> elapsed = [] { return 1.f; };   // of the launches since the last event
+static struct { dim3 grid, block; size_t lds; hipStream_t st; } config;
+
+extern "C" {
+void **__hipRegisterFatBinary(const void *) { static void *h; return &h; }
+void __hipUnregisterFatBinary(void **) {}
+void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
+void __hipRegisterFunction(void **, const void *host, char *, const char *name, unsigned, void *, void *, void *,
+                           void *, int *) {
+    int st = 0;
+    char *d = abi::__cxa_demangle(name, nullptr, nullptr, &st);
+    kernels()[host] = d ? d : name;
+    std::free(d);
+}
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t lds, hipStream_t st) {
+    config = {g, b, lds, st};
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *lds, hipStream_t *st) {
+    *g = config.grid; *b = config.block; *lds = config.lds; *st = config.st;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **, size_t, hipStream_t) {
+    launches.push_back({kernels()[f], g, b});
+    return hipSuccess;
+}
+hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipMalloc(void **p, size_t n) { *p = std::calloc(n, 1); return *p ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipFree(void *p) { std::free(p); return hipSuccess; }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) {
+    std::memcpy(d, s, n);
+    return hipSuccess;
+}
+hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) { std::memset(d, v, n); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) {
+    *s = hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t)std::malloc(1); return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { std::free((void *)e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = elapsed(); return hipSuccess; }
+}
+
+// launches whose kernel's name holds every one of `parts`
+static int count(std::initializer_list<const char *> parts) {
+    int n = 0;
+    for (const auto &l : launches) {
+        bool all = true;
+        for (const char *p : parts) all = all && l.name.find(p) != std::string::npos;
+        n += all;
+    }
+    return n;
+}
+
+// ---- networks and passes -------------------------------------------------------------
+static std::vector<float> memory(1 << 22);        // stands in for every tensor that no host code reads
+
+static bound_layer conv(int ci, int hw, int co, int k, int s, int p) {
+    const int o = (hw + 2 * p - k) / s + 1;
+    return bound_layer{BOUND_CONV2D, ci, hw, hw, co, o, o, k, k, s, p, memory.data(), memory.data()};
+}
+static bound_layer linear(int ci, int hw, int co) {
+    return bound_layer{BOUND_LINEAR, ci, hw, hw, co, 1, 1, 1, 1, 1, 0, memory.data(), memory.data()};
+}
+
+struct Net {
+    bound_net *h = nullptr;
+    std::vector<bound_layer> layers;
+    Net(std::vector<bound_layer> l, int inst, long rows, long save = 0) : layers(std::move(l)) {
+        if (bound_init(layers.data(), (int)layers.size(), inst, rows, save, nullptr, &h) != BOUND_OK) {
+            std::printf("bound_init: %s\n", bound_last_error());
+            std::exit(1);
+        }
+    }
+    ~Net() { bound_destroy(h); }
+    // rows [n, rows] of z_target (rows = 0: the identity) with `flags`; runs f on them
+    template <class F> void pass(int target, int n, int rows, int flags, F f) {
+        float *m = memory.data();
+        const bound_layer &T = layers[target - 1];
+        bound_pass p{};
+        bound_out o{};
+        p.n_inst = n;
+        p.rows = rows > 0 ? rows : T.out_c * T.out_h * T.out_w;
+        p.target = target;
+        p.n_bounds = n;
+        p.spec = rows > 0 ? m : nullptr;
+        p.lo = p.hi = p.x_lo = p.x_hi = m;
+        p.flags = flags;
+        o.lower = o.upper = m;
+        launches.clear();
+        const bound_status s = f(&p, &o);
+        if (s != BOUND_OK) {
+            std::printf("pass: %s\n", bound_last_error());
+            std::exit(1);
+        }
+    }
+    void backward(int target, int n, int rows, int flags) {
+        pass(target, n, rows, flags, [&](bound_pass *p, bound_out *o) { return bound_backward(h, p, o, nullptr); });
+    }
+};
 
 static int bad = 0;
 static void check(bool ok, const char *what, int i = 0) {
@@ -88,8 +209,22 @@ static void split_weights() {
     check(found, "listed with weights");
 }
 
+// BOUND_OPT_DIRECT_DMA: every direct convolution stages by LDS DMA (k_conv's last template
+// argument), also where few blocks would keep the registers, and none is replaced by another
+// kernel.
+static void direct_dma() {
+    Net net({conv(4, 8, 16, 3, 1, 1), conv(16, 8, 32, 3, 1, 1), conv(32, 8, 64, 3, 1, 1), linear(64, 8, 4)}, 2, 64, 64);
+    for (int flags : {0, (int)BOUND_SAVE_FOR_GRAD})
+        for (int on : {0, 1}) {
+            bound_set_options(net.h, on ? BOUND_OPT_DIRECT_DMA : 0);
+            net.backward(4, 2, 3, flags);
+            check(count({"k_conv<", "EpiRelax", "true>"}) == (on ? 2 : 0), "relaxing products by DMA", flags);
+            if (on) check(count({"k_conv_split"}) == 0, "another kernel", flags);
+        }
+}
+
 int main(int argc, char **argv) {
-    const struct { const char *name; void (*f)(); } tests[] = {{"dense", dense}, {"split_weights", split_weights}};
+    const struct { const char *name; void (*f)(); } tests[] = {{"dense", dense}, {"split_weights", split_weights}, {"direct_dma", direct_dma}};
     for (auto &t : tests)
         if (argc == 2 && !std::strcmp(argv[1], t.name)) {
             t.f();

@@ -1,5 +1,5 @@
 """Host rules that choose a product's kernel, without a GPU: a small host program links the
-library and calls its rules on geometries as bound_init builds them.
+library, stands in for the HIP runtime and looks at the kernels that its passes launch.
 """
 import os
 import subprocess
@@ -39,3 +39,9 @@ def test_bf16_tile_needs_packed_weights(rules):
     """A 1x1 convolution on one pixel is dense but has no bf16 weights: neither the automatic
     rule nor the tuner's list may give it that tile, and its launcher refuses it."""
     rules("split_weights")
+
+
+def test_direct_dma_option_chooses_the_staging(rules):
+    """BOUND_OPT_DIRECT_DMA stages the automatic direct convolutions by LDS DMA, as it is
+    declared, in saving and other passes."""
+    rules("direct_dma")
