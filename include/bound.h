@@ -306,8 +306,13 @@ bound_status bound_set_options(bound_net *net, int32_t options);
 /* Kernel autotuning: runs the given pass (and, if grad_lower is not NULL and the pass
  * has SAVE_FOR_GRAD, its gradient) once in tuning mode -- every valid kernel variant of
  * every product (direct-convolution channel chunk, implicit-GEMM tile shape) is timed
- * on the live data and the fastest is kept for that product on this handle -- then runs
- * the pass again normally, so `out` and the saved state are those of a normal pass.
+ * on the live data and the fastest is kept for that product on this handle, for passes of
+ * the same kind -- then runs the pass again normally, so `out` and the saved state are those
+ * of a normal pass.  There are two kinds: SAVE_FOR_GRAD passes (with the adjoint and sample
+ * rows), which choose among the FP32 kernels, and all others, which also choose among those
+ * on the bf16 matrix cores at FP32 precision.  Full CROWN's passes over convolutional layers
+ * run on receptive-field windows, which have no plans; here their whole-layer products are
+ * timed, for the passes that use those (a coefficient output, or any option set).
  * Synchronises the stream; must not be called while the stream is being captured.
  * bound_autotune_report copies the timing log (NUL-terminated, truncated to cap) and
  * returns its full length. */
@@ -320,7 +325,11 @@ int32_t bound_autotune_report(const bound_net *net, char *buf, int32_t cap);
  * 'A' (adjoint step) or 'F' (forward step of sample rows); layer is 1-based; path 1 =
  * direct convolution (cfg: -1 staging through registers, 1 by LDS DMA, 2 / 3 the same
  * with 16x16 MFMA tiles for 32 output channels; cc: channel chunk, 0 = largest that
- * fits), path 2 = implicit GEMM (cfg: tile shape 0..10; 9 and 10 stage dense products by LDS DMA; 11..15 one wave per tile for dense products, 15 in the order of 11; 16 the bf16 matrix cores at FP32 precision ('R' and 'C'), 17 FP32 MFMAs on the same tiles), path 0 = automatic.  A plan the layer cannot run falls back to the implicit GEMM at launch.
+ * fits), path 2 = implicit GEMM (cfg: tile shape 0..10; 9 and 10 stage dense products by
+ * LDS DMA; 11..15 one wave per tile for dense products, 15 in the order of 11; 16 the bf16
+ * matrix cores at FP32 precision ('R' and 'C'), 17 FP32 MFMAs on the same tiles), path 0 =
+ * automatic.  The plan holds for saving and other passes alike.  A plan the layer cannot
+ * run falls back to the implicit GEMM at launch; window passes have no plans.
  * Lets a run reuse the plans of an earlier tuned run (the timing log's chosen lines). */
 bound_status bound_set_plan(bound_net *net, char product, int32_t layer, int32_t path,
                             int32_t cfg, int32_t cc);

@@ -116,7 +116,7 @@ class BetaBatch:
         """plans: {'R2': 'direct cfg=1 cc=16 ...', ...} as chosen_plans() returns them."""
         for key, plan in plans.items():
             path, cfg, cc = plan.split()[:3]
-            B.bound_set_plan(self.bn.handle, key[0], int(key[1:]), 1 if path == "direct" else 2,
+            B.bound_set_plan(self.bn.handle, key[0], int(key[1:]), {"auto": 0, "direct": 1, "gemm": 2}[path],
                              int(cfg.split("=")[1]), int(cc.split("=")[1]))
 
     def optimizer(self, steps=None):

@@ -151,13 +151,19 @@ struct ProfScope {
     }
 };
 
+inline int pkey(char c, int m) { return ((int)c << 8) | m; }
+constexpr int PLAN_KEEP = 1 << 16;
+
 // Run one product with its plan.  In tuning mode, time every valid candidate on the
 // live inputs (3 launches each after one warm-up; the product is re-run, so the pass's
 // accumulators are scratch until the normal pass that follows tuning) and keep the
 // fastest.
+// Products of passes that save (keep) and of others have plans of their own: they choose
+// among different kernels.
 template <class F>
 bound_status run_product(bound_net *net, hipStream_t st, int key, const GeomSet &gs, F launch,
                          bool keep = false) {
+    key |= keep ? PLAN_KEEP : 0;
     if (!net->tuning) {
         Plan p;
         if (net->options & BOUND_OPT_GEMM_ONLY) {
@@ -174,7 +180,7 @@ bound_status run_product(bound_net *net, hipStream_t st, int key, const GeomSet 
         return BOUND_OK;
     }
     Plan cand[kMaxCandidates];
-    const int nc = plan_candidates(gs, cand, kMaxCandidates);
+    const int nc = plan_candidates(gs, keep, cand, kMaxCandidates);
     hipEvent_t a = net->event(), b = net->event();
     float best = INFINITY;
     Plan bestp;
@@ -188,8 +194,9 @@ bound_status run_product(bound_net *net, hipStream_t st, int key, const GeomSet 
         float ms = 0.f;
         HIPCHK(hipEventElapsedTime(&ms, a, b));
         ms /= 3.f;
-        std::snprintf(line, sizeof line, "%c%d %s cfg=%d cc=%d %.4f ms\n", (char)(key >> 8), key & 255,
-                      cand[c].path == 1 ? "direct" : "gemm", cand[c].cfg, cand[c].cc, ms);
+        std::snprintf(line, sizeof line, "%c%d %s cfg=%d cc=%d %.4f ms\n", (char)(key >> 8 & 255), key & 255,
+                      cand[c].path == 0 ? "auto" : (cand[c].path == 1 ? "direct" : "gemm"), cand[c].cfg,
+                      cand[c].cc, ms);
         net->tune_report += line;
         if (ms < best) {
             best = ms;
@@ -203,7 +210,6 @@ bound_status run_product(bound_net *net, hipStream_t st, int key, const GeomSet 
     return BOUND_OK;
 }
 
-inline int pkey(char c, int m) { return ((int)c << 8) | m; }
 
 // Row-sum slots per img of the relaxation / concretisation product of layer m: its
 // output pixels (width / N) times ceil(N / 16) column groups, N the product's columns.
@@ -1385,7 +1391,7 @@ bound_status bound_set_plan(bound_net *net, char product, int32_t layer, int32_t
     p.path = path;
     p.cfg = cfg;
     p.cc = cc;
-    net->plans[pkey(product, layer)] = p;
+    net->plans[pkey(product, layer)] = net->plans[pkey(product, layer) | PLAN_KEEP] = p;
     return BOUND_OK;
 }
 

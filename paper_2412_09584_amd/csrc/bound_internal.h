@@ -153,10 +153,12 @@ struct Plan {
     int path = 0;
     int cfg = -1;
     int cc = 0;
-    // automatic plans keep the order in which the general kernels add a row's terms: the
-    // saved coefficients' signs pick the branch of the adjoint, and some of them are within
-    // rounding of 0, so a SAVE_FOR_GRAD pass takes only kernels that give bitwise the same
-    // coefficients, and the adjoint, whose gradients move the next step's slopes, the same
+    // Plans keep the order in which the general kernels add a row's terms: the saved
+    // coefficients' signs pick the branch of the adjoint, and some of them are within rounding
+    // of 0, so an automatic SAVE_FOR_GRAD pass takes only kernels that give bitwise the same
+    // coefficients, and the adjoint, whose gradients move the next step's slopes, the same.  A
+    // tuned one takes the general FP32 kernels (whose tiles and channel chunks have orders of
+    // their own) and those that repeat such an order, never the bf16 matrix cores.
     bool keep = false;
 };
 constexpr int kMaxCandidates = 32;
@@ -169,8 +171,9 @@ hipError_t gemm_adj(const GeomSet &gs, const float *A, long n_img, const AdjPara
                     hipStream_t st, const Plan &plan);
 hipError_t gemm_fwd(const GeomSet &gs, const float *A, long n_img, const FwdParams &p,
                     hipStream_t st, const Plan &plan);
-// Valid plans for a product (direct variants first, then GEMM tiles); returns the count.
-int plan_candidates(const GeomSet &gs, Plan *out, int cap);
+// Valid plans for a product (direct variants first, then GEMM tiles, then, unless it keeps the
+// order, the automatic choice); returns the count.
+int plan_candidates(const GeomSet &gs, bool keep, Plan *out, int cap);
 // gemm.hip: implicit GEMM with an explicit tile configuration (cfg < 0: default)
 hipError_t gemm_relax_cfg(const GeomSet &gs, const float *A, long n_img, const RelaxParams &p,
                           hipStream_t st, int cfg);
@@ -180,7 +183,7 @@ hipError_t gemm_adj_cfg(const GeomSet &gs, const float *A, long n_img, const Adj
                         hipStream_t st, int cfg);
 hipError_t gemm_fwd_cfg(const GeomSet &gs, const float *A, long n_img, const FwdParams &p,
                         hipStream_t st, int cfg);
-int gemm_candidates(const GeomSet &gs, int *cfgs, int cap);
+int gemm_candidates(const GeomSet &gs, bool keep, int *cfgs, int cap);
 // dense.hip: wave-per-tile kernels for dense products with few tiles (configurations that
 // follow the GEMM's); dense_auto picks one, or -1 where the LDS-tiled GEMM serves better
 //

@@ -5,7 +5,13 @@
 
 namespace bp {
 
-int gemm_candidates(const GeomSet &gs, int *cfgs, int cap) {
+// whether a dense kernel adds in the order of the general GEMM's default tiles, which are
+// 32x32x2 from 32 columns on
+static bool keeps_order(int cfg, int N) {
+    return N < 32 ? cfg == DENSE_W16 : cfg == DENSE_W32 || cfg == DENSE_W16O || cfg == DENSE_F32;
+}
+
+int gemm_candidates(const GeomSet &gs, bool keep, int *cfgs, int cap) {
     // a tile wider than the padded N only repeats zero columns
     const int N = gs.g[0].N;
     int n = 0;
@@ -17,7 +23,8 @@ int gemm_candidates(const GeomSet &gs, int *cfgs, int cap) {
     }
     // the wave-per-tile kernels (they never repeat padding columns past a tile)
     for (int c = DENSE_W32; c <= DENSE_F32 && n < cap && is_dense(gs); ++c)
-        if ((c != DENSE_W16K16 || g.K >= 256) && (c != DENSE_SPLIT || g.Bs)) cfgs[n++] = c;
+        if ((c != DENSE_W16K16 || g.K >= 256) && (c != DENSE_SPLIT || g.Bs) && (!keep || keeps_order(c, N)))
+            cfgs[n++] = c;
     return n;
 }
 
@@ -29,7 +36,7 @@ hipError_t gemm_conc_cfg(const GeomSet &gs, const float *A, long n_img, const Co
                          hipStream_t st, int cfg) {
     return dispatch(gs, A, n_img, dev::EpiConc{p}, st, cfg);
 }
-int plan_candidates(const GeomSet &gs, Plan *out, int cap) {
+int plan_candidates(const GeomSet &gs, bool keep, Plan *out, int cap) {
     int n = 0;
     int cc[kMaxCandidates], mode[kMaxCandidates];
     const int nd = direct_candidates(gs, cc, mode, kMaxCandidates);
@@ -40,13 +47,14 @@ int plan_candidates(const GeomSet &gs, Plan *out, int cap) {
         ++n;
     }
     int cf[kMaxCandidates];
-    const int ng = gemm_candidates(gs, cf, kMaxCandidates);
+    const int ng = gemm_candidates(gs, keep, cf, kMaxCandidates);
     for (int i = 0; i < ng && n < cap; ++i) {
         out[n].path = 2;
         out[n].cfg = cf[i];
         out[n].cc = 0;
         ++n;
     }
+    if (!keep && n < cap) out[n++] = Plan{};       // conv_split.hip's kernels have no plan of their own
     return n;
 }
 

@@ -158,7 +158,7 @@ static GeomSet one(const Geom &g) {
 
 static std::vector<int> listed(const GeomSet &gs) {
     int c[kMaxCandidates];
-    const int n = gemm_candidates(gs, c, kMaxCandidates);
+    const int n = gemm_candidates(gs, false, c, kMaxCandidates);
     return std::vector<int>(c, c + n);
 }
 
@@ -223,8 +223,39 @@ static void direct_dma() {
         }
 }
 
+// The tuner, when one kernel would win every timing it takes part in: a saving pass and its
+// gradient never time the bf16 tile or the kernels that split K, and their plans do not govern
+// passes that save nothing, which may choose those and keep the automatic choice among theirs.
+static void tuning() {
+    const long n = 4096, R = 8;           // 256 tiles of 128 x 128
+    for (const char *best : {"k_dense_tall<bp::dev::EpiRelax, 4, true>", "k_conv_split", "16, 4, false>"}) {
+        Net net({conv(4, 8, 16, 3, 1, 1), conv(16, 8, 32, 3, 1, 1), conv(32, 8, 32, 3, 1, 1), linear(32, 8, 256),
+                 linear(256, 1, 64)}, (int)n, n * R, n * R);
+        elapsed = [&] { return launches.back().name.find(best) != std::string::npos ? .5f : 1.f; };
+        auto tune = [&](int flags) {
+            net.pass(5, n, R, flags, [&](bound_pass *p, bound_out *o) {
+                return bound_autotune(net.h, p, o, memory.data(), nullptr);
+            });
+        };
+        tune(BOUND_SAVE_FOR_GRAD);
+        check(count({best}) == 0, "timed for a saving pass");
+        net.backward(5, n, R, BOUND_SAVE_FOR_GRAD);
+        check(count({best}) == 0, "launched by a saving pass");
+        check(count({"k_conv<", "EpiRelax"}) + count({"k_gemm<", "EpiRelax"}) >= 2, "its convolutions");
+        net.backward(5, n, R, 0);
+        check(count({"k_conv_split"}) == 1 && count({"k_dense_tall", "true>"}) >= 1, "a saving pass's plans elsewhere");
+        tune(0);
+        check(count({best}) > 0, "not timed for a pass that saves nothing");
+        net.backward(5, n, R, 0);
+        check(count({best}) > 0, "not kept for a pass that saves nothing");
+        net.backward(5, n, R, BOUND_SAVE_FOR_GRAD);
+        check(count({best}) == 0, "its plans in a saving pass");
+        elapsed = [] { return 1.f; };
+    }
+}
+
 int main(int argc, char **argv) {
-    const struct { const char *name; void (*f)(); } tests[] = {{"dense", dense}, {"split_weights", split_weights}, {"direct_dma", direct_dma}};
+    const struct { const char *name; void (*f)(); } tests[] = {{"dense", dense}, {"split_weights", split_weights}, {"direct_dma", direct_dma}, {"tuning", tuning}};
     for (auto &t : tests)
         if (argc == 2 && !std::strcmp(argv[1], t.name)) {
             t.f();

@@ -42,3 +42,18 @@ def test_adjoint_is_not_timed_on_the_bf16_tile():
     for key, plans in lists.items():
         if key[0] == "A":
             assert ("gemm", 16) not in plans, key
+
+
+def test_tuned_passes_of_both_kinds():
+    """A tuned saving pass times no plan on the bf16 matrix cores; a tuned pass that saves
+    nothing does, and its bounds are those of the automatic plans (1e-5: other orders of the
+    same FP32 sums)."""
+    n, R = 3000, 6                                  # 18000 rows x 260: 423 tiles
+    bn, net, args, (x_lo, x_hi, C) = _handle((40, 260, 256, 6), n, R, True)
+    ref, _ = bn.spec_bounds(C, args["lo"], args["hi"], x_lo, x_hi, both=False)
+    saving = _tuned(bn, n, R, len(net), args, True)
+    assert all(("gemm", c) not in plans for plans in saving.values() for c in (13, 14, 16))
+    other = _tuned(bn, n, R, len(net), args, False)
+    assert ("gemm", 16) in other["R2"] and ("auto", -1) in other["R2"]
+    low, _ = bn.spec_bounds(C, args["lo"], args["hi"], x_lo, x_hi, both=False)
+    assert bool(((low - ref).abs() <= 1e-5 * ref.abs().clamp_min(1.0)).all())

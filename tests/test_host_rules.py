@@ -45,3 +45,9 @@ def test_direct_dma_option_chooses_the_staging(rules):
     """BOUND_OPT_DIRECT_DMA stages the automatic direct convolutions by LDS DMA, as it is
     declared, in saving and other passes."""
     rules("direct_dma")
+
+
+def test_tuned_saving_passes_keep_fp32_kernels(rules):
+    """Autotuning a SAVE_FOR_GRAD pass chooses among FP32 kernels that keep an order of the
+    general ones, and its plans are not those of passes that save nothing."""
+    rules("tuning")
