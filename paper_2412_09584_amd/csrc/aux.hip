@@ -1228,8 +1228,14 @@ hipError_t launch_prep_tables(const NetShapes &ns, int first, int used, int n_in
                            slot_count);
     long tiles = 0, tile_first = 0;
     for (int m = 0; m < used; ++m) (m < first ? tile_first : tiles) += prep_tiles(ns.l[m]);
-    const long n_tab = tiles * n_inst, n_box = (box.total + TPB - 1) / TPB;
-    if (n_tab + n_box > 0x7fffffffL) return hipErrorInvalidValue;
+    const long n_tab = tiles * n_inst;
+    long n_box = (box.total + TPB - 1) / TPB;
+    if (n_tab > 0x7fffffffL) return hipErrorInvalidValue;
+    if (n_tab + n_box >= (1L << 32) / TPB) {      // more than HIP launches at once: the box by itself
+        const hipError_t e = launch_prep_box(box, st);
+        if (e != hipSuccess) return e;
+        n_box = 0;
+    }
     const auto f = save ? k_prep_tables<true> : k_prep_tables<false>;
     hipLaunchKernelGGL(f, dim3((unsigned)(n_tab + n_box)), dim3(256), 0, st, ns.dev, ns.tile0, used, n_relu, lo, hi,
                        bound_of, alpha, tab, infeas, n_bounds, slot, per_inst ? 1 : 0, srow, (int)tiles,
@@ -1298,14 +1304,33 @@ hipError_t launch_init_dense(const IdentityParams &p, const float *W, int ldw, l
     return hipGetLastError();
 }
 
+// The bounds of z_1 take one launch for as many instances as 2^31 threads cover (HIP refuses
+// 2^32): launch(params, instances, outputs) for each such part.
+template <class F>
+static hipError_t in_launches(const IdentityParams &p, int n_inst, long threads, long ld, float *lower, float *upper,
+                              float *best, float *best_upper, F launch) {
+    const long per = threads < (1L << 31) ? (1L << 31) / threads : 1;
+    for (long i = 0; i < n_inst; i += per) {
+        IdentityParams q = p;
+        q.cen += i * p.din;
+        q.rad += i * p.din;
+        auto at = [&](float *x) { return x ? x + i * ld : nullptr; };
+        launch(q, (int)(n_inst - i < per ? n_inst - i : per), at(lower), at(upper), at(best), at(best_upper));
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 hipError_t launch_dense1_bounds(const IdentityParams &p, const float *W, int ldw, int n_inst, bool slack,
                                 float *lower, float *upper, long ld, float *best, float *best_upper,
                                 hipStream_t st) {
-    const long n_wave = (long)n_inst * ((p.dk + ID_ROWS - 1) / ID_ROWS);
-    if (n_wave > 0x7fffffffL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_dense1_bounds, dim3(blocks_for(n_wave, 4)), dim3(TPB), 0, st, p, W, ldw, n_wave,
-                       slack ? 1 : 0, lower, upper, ld, best, best_upper);
-    return hipGetLastError();
+    const long tiles = (p.dk + ID_ROWS - 1) / ID_ROWS;
+    return in_launches(p, n_inst, tiles * 64, ld, lower, upper, best, best_upper,
+                       [&](const IdentityParams &q, int n, float *lo, float *up, float *b, float *bu) {
+        hipLaunchKernelGGL(k_dense1_bounds, dim3(blocks_for(n * tiles, 4)), dim3(TPB), 0, st, q, W, ldw, n * tiles,
+                           slack ? 1 : 0, lo, up, ld, b, bu);
+    });
 }
 
 hipError_t launch_init_window(const IdentityParams &p, const WinMap &w, long n_img, hipStream_t st) {
@@ -1315,10 +1340,11 @@ hipError_t launch_init_window(const IdentityParams &p, const WinMap &w, long n_i
 
 hipError_t launch_conv1_bounds(const IdentityParams &p, int n_inst, bool slack, float *lower, float *upper,
                                long ld, float *best, float *best_upper, hipStream_t st) {
-    const long total = (long)n_inst * p.dk;
-    hipLaunchKernelGGL(k_conv1_bounds, dim3(blocks_for(total)), dim3(TPB), 0, st, p, total, slack ? 1 : 0,
-                       lower, upper, ld, best, best_upper);
-    return hipGetLastError();
+    return in_launches(p, n_inst, p.dk, ld, lower, upper, best, best_upper,
+                       [&](const IdentityParams &q, int n, float *lo, float *up, float *b, float *bu) {
+        hipLaunchKernelGGL(k_conv1_bounds, dim3(blocks_for(n * p.dk)), dim3(TPB), 0, st, q, n * p.dk, slack ? 1 : 0,
+                           lo, up, ld, b, bu);
+    });
 }
 
 hipError_t launch_beta_sum(int nnz, int rows, const int32_t *off, const int32_t *idx,

@@ -24,6 +24,7 @@ static std::map<const void *, std::string> &kernels() {
 }
 static std::vector<Launch> launches;
 static std::function<float()> elapsed = [] { return 1.f; };   // of the launches since the last event
+static hipError_t last = hipSuccess;
 static struct { dim3 grid, block; size_t lds; hipStream_t st; } config;
 
 extern "C" {
@@ -46,11 +47,16 @@ hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *lds, hipStream_t 
     return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **, size_t, hipStream_t) {
+    if ((unsigned long)g.x * b.x > 0xffffffffUL) return last = hipErrorInvalidConfiguration;   // as HIP does
     launches.push_back({kernels()[f], g, b});
     return hipSuccess;
 }
 hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetLastError() {
+    const hipError_t e = last;
+    last = hipSuccess;
+    return e;
+}
 hipError_t hipMalloc(void **p, size_t n) { *p = std::calloc(n, 1); return *p ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipFree(void *p) { std::free(p); return hipSuccess; }
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) {
@@ -254,8 +260,29 @@ static void tuning() {
     }
 }
 
+// Passes of more instances than one launch takes threads for: the box bounds of z_1 (z_1's
+// values go up to 2^32 and beyond, in chunks), and the tables with the box in one launch.
+static void large() {
+    Net fc({linear(4, 1, 8192)}, 65537, 1024);
+    fc.backward(1, 65537, 0, BOUND_BOTH_SIDES);
+    check(count({"k_dense1_bounds"}) >= 2, "dense");
+    Net cv({conv(1, 64, 16, 3, 1, 1)}, 65537, 1024);
+    cv.backward(1, 65537, 0, BOUND_BOTH_SIDES);
+    check(count({"k_conv1_bounds"}) >= 2, "conv");
+    const int n = 1 << 21;
+    Net deep({linear(1024, 1, 8), linear(8, 1, 8), linear(8, 1, 8), linear(8, 1, 8), linear(8, 1, 8), linear(8, 1, 2)},
+             n, 1024);
+    deep.backward(6, n, 1, 0);
+    check(count({"k_prep_tables"}) == 1 && count({"k_prep_box"}) == 1, "tables and box");
+    long rows = 0;      // every instance of the dense pass once: 4 waves a block, 1024 rows of 8 an instance
+    fc.backward(1, 65537, 0, BOUND_BOTH_SIDES);
+    for (auto &l : launches)
+        if (l.name.find("k_dense1_bounds") != std::string::npos) rows += (long)l.grid.x * 4 / 1024;
+    check(rows == 65537, "instances", (int)rows);
+}
+
 int main(int argc, char **argv) {
-    const struct { const char *name; void (*f)(); } tests[] = {{"dense", dense}, {"split_weights", split_weights}, {"direct_dma", direct_dma}, {"tuning", tuning}};
+    const struct { const char *name; void (*f)(); } tests[] = {{"dense", dense}, {"split_weights", split_weights}, {"direct_dma", direct_dma}, {"tuning", tuning}, {"large", large}};
     for (auto &t : tests)
         if (argc == 2 && !std::strcmp(argv[1], t.name)) {
             t.f();

@@ -51,3 +51,9 @@ def test_tuned_saving_passes_keep_fp32_kernels(rules):
     """Autotuning a SAVE_FOR_GRAD pass chooses among FP32 kernels that keep an order of the
     general ones, and its plans are not those of passes that save nothing."""
     rules("tuning")
+
+
+def test_passes_larger_than_a_launch(rules):
+    """HIP refuses launches of 2^32 threads and more: full CROWN's first pass and the tables'
+    launch, which used to work in chunks of the workspace or on their own, take any size still."""
+    rules("large")
