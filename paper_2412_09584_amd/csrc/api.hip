@@ -435,7 +435,7 @@ bool window_plan(const bound_net *net, int k, int rpi, WinPlan &wp) {
         store = A * s;
         P = P * s + L.pad;
         S *= s;
-        if (store > 512 || S > 512) return false;
+        if (store > 512 || S > 512 || !win_index_fits(L.in_h, L.in_w, store)) return false;
         put_map(m - 1);
         // phase ph of the window (wy % s) takes the weights packed for the layer's phase
         // with the same first tap, (p + pad) % s == ph

@@ -143,6 +143,13 @@ struct WinMap {
     float rDW, rC, rOw, rrpi;   // fl(1 / .) of DW, the target's channels, ow, rpi
 };
 
+// Whether the window epilogues' indices hold for a layer of H x W pixels and windows of `store`
+// a side: they form y * W + x by 24-bit multiplications, y and x up to a window outside the
+// layer on either side.
+inline bool win_index_fits(long H, long W, long store) {
+    return (H + 2 * store) * W + 2 * store < (1L << 23) && H + 2 * store < (1L << 23) && W < (1L << 23);
+}
+
 // ----- product launchers ---------------------------------------------------------
 // A plan picks the kernel of one product: path 0 = automatic (direct convolution when
 // the geometry fits, else the implicit GEMM with the default tile), 1 = direct

@@ -57,3 +57,9 @@ def test_passes_larger_than_a_launch(rules):
     """HIP refuses launches of 2^32 threads and more: full CROWN's first pass and the tables'
     launch, which used to work in chunks of the workspace or on their own, take any size still."""
     rules("large")
+
+
+def test_window_indices_stay_in_range(rules):
+    """The window epilogues multiply in 24 bits; passes over layers whose pixel indices exceed
+    that may not run on windows."""
+    rules("window_index")
