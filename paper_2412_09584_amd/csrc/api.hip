@@ -261,18 +261,18 @@ std::string lbl(const char *f, int m) {
 
 // The dense layer's packed weights once more, as three bf16 parts (split.hip): the backward
 // products', the forward and adjoint ones keep the FP32 order.
-bool split_weights(bound_net *net, Geom &g, int Np, hipStream_t st) {
+bool split_weights(bound_net *net, Geom &g, int Np, int32_t *flags, hipStream_t st) {
     unsigned short *bs = nullptr;
     g.Kc = (int)((g.K + 31) / 32);
     if (!net->alloc(&bs, (long)Np * g.Kc * 96)) return false;
     g.Bs = bs;
-    return launch_pack_split(g.Bt, Np, g.Kp, g.Kc, bs, st) == hipSuccess;
+    return launch_pack_split(g.Bt, Np, g.Kp, g.Kc, bs, flags, st) == hipSuccess;
 }
 
 // The layer's pairs of phases in windows (none unless it has four phases of one shape and 5 ..
 // 16 columns): phase (wy, 0) and (wy, 1) of a window take the weights packed for the layer's
 // phases with the same first taps, (p + pad) % 2.
-bool build_pairs(bound_net *net, LayerInfo &li, hipStream_t st) {
+bool build_pairs(bound_net *net, LayerInfo &li, int32_t *flags, hipStream_t st) {
     const bound_layer &L = li.L;
     if (L.stride != 2 || li.gT.n != 4 || L.in_c > 16 || L.in_c <= 4) return true;
     for (int i = 1; i < 4; ++i)
@@ -289,8 +289,9 @@ bool build_pairs(bound_net *net, LayerInfo &li, hipStream_t st) {
         const long n = conv_split_size(t);
         unsigned short *bs;
         if (n == 0) return true;
-        if (!net->alloc(&bs, n) || launch_pack_conv(t, &second, bs, st) != hipSuccess) return false;
+        if (!net->alloc(&bs, n) || launch_pack_conv(t, &second, bs, flags, st) != hipSuccess) return false;
         t.Bs = bs;
+        t.Bt2 = second.Bt;
         li.gW.g[y] = t;
     }
     li.gW.n = 2;
@@ -298,6 +299,9 @@ bool build_pairs(bound_net *net, LayerInfo &li, hipStream_t st) {
 }
 
 bound_status build_geoms(bound_net *net, hipStream_t st) {
+    int32_t *flags;                            // launch_pack_split's, per layer
+    if (!net->alloc(&flags, 3L * net->n_layers)) return fail(BOUND_E_NOMEM, "weight packing");
+    HIPCHK(launch_fill((float *)flags, 3L * net->n_layers, 0.f, st));     // 0.0f is all-zero bits
     for (int i = 0; i < net->n_layers; ++i) {
         LayerInfo &li = net->layers[i];
         const bound_layer &L = li.L;
@@ -313,7 +317,7 @@ bound_status build_geoms(bound_net *net, hipStream_t st) {
                                  0, 0, 1, 1, t.N, t.K, t.Kp, (int)NpT, bt, st));
             t.Bt = bt;
             set_recips(t);
-            if (!split_weights(net, t, (int)NpT, st)) return fail(BOUND_E_NOMEM, "weight packing");
+            if (!split_weights(net, t, (int)NpT, flags + 3 * i, st)) return fail(BOUND_E_NOMEM, "weight packing");
             li.gT.g[0] = t; li.gT.n = 1;
 
             Geom f{};
@@ -372,15 +376,24 @@ bound_status build_geoms(bound_net *net, hipStream_t st) {
                     if (const long n = conv_split_size(t)) {
                         unsigned short *bs;
                         if (!net->alloc(&bs, n)) return fail(BOUND_E_NOMEM, "weight packing");
-                        HIPCHK(launch_pack_conv(t, nullptr, bs, st));
+                        HIPCHK(launch_pack_conv(t, nullptr, bs, flags + 3 * i, st));
                         t.Bs = bs;
                     }
                     li.gT.g[np++] = t;
                 }
             }
             li.gT.n = np;
-            if (!build_pairs(net, li, st)) return fail(BOUND_E_NOMEM, "weight packing");
+            if (!build_pairs(net, li, flags + 3 * i, st)) return fail(BOUND_E_NOMEM, "weight packing");
         }
+    }
+    std::vector<int32_t> f(3 * net->n_layers);
+    HIPCHK(hipMemcpyAsync(f.data(), flags, sizeof(int32_t) * f.size(), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
+    for (int i = 0; i < net->n_layers; ++i) {
+        if (!f[3 * i] && (f[3 * i + 2] || !f[3 * i + 1])) continue;
+        LayerInfo &li = net->layers[i];
+        for (Geom &g : li.gT.g) g.Bs = nullptr;
+        li.gW.n = 0;
     }
     return BOUND_OK;
 }

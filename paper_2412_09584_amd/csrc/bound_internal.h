@@ -29,6 +29,7 @@ struct Geom {
     // convolutions as conv_split.hip packs them (null where it does not take them)
     const unsigned short *Bs;
     int Kc;                    // its 32-wide k chunks
+    const float *Bt2;          // a pair's second phase (conv_split.hip)
 };
 
 // Reciprocals of a geometry's divisors, taken once on the host (the same correctly
@@ -215,7 +216,14 @@ hipError_t tall_relax(const GeomSet &gs, const float *A, long M, const RelaxPara
 hipError_t tall_conc(const GeomSet &gs, const float *A, long M, const ConcParams &p, hipStream_t st, bool split);
 hipError_t tall_adj(const GeomSet &gs, const float *A, long M, const AdjParams &p, hipStream_t st);
 hipError_t tall_fwd(const GeomSet &gs, const float *A, long M, const FwdParams &p, hipStream_t st);
-hipError_t launch_pack_split(const float *Bt, int Np, int Kp, int Kc, unsigned short *out, hipStream_t st);
+// Three bf16 parts hold an FP32 value's 24 bits where no part leaves the range of normal bf16
+// values: from SPLIT_MAX on the first one rounds to infinity, below SPLIT_MIN the last ones are
+// flushed to 0.  Rows outside are formed again by FP32 instructions, and a layer of such
+// weights stays with the FP32 kernels: `flags` [3] gets 1 where there are weights past SPLIT_MAX,
+// non-zero ones below SPLIT_MIN, and others.
+constexpr unsigned SPLIT_MAX = 0x7f7f0000u, SPLIT_MIN = 0x0d800000u;   // bits of 3.39e38, 2^-100
+hipError_t launch_pack_split(const float *Bt, int Np, int Kp, int Kc, unsigned short *out, int32_t *flags,
+                             hipStream_t st);
 // conv.hip: direct convolution (cc = 0: largest chunk that fits; mode 1 or 3: tiles staged
 // by LDS DMA, else through registers; mode 2 or 3: 16x16 MFMA tiles for 32 output
 // channels); *used = false when the geometry does not fit
@@ -239,7 +247,7 @@ hipError_t conv_split_relax(const GeomSet &gs, const float *A, long n_img, const
 hipError_t conv_split_relax_win(const GeomSet &gs, bool pair, const float *A, long n_img, const RelaxParams &p,
                                 const WinMap &w, hipStream_t st);
 long conv_split_size(const Geom &g);
-hipError_t launch_pack_conv(const Geom &g, const Geom *pair, unsigned short *out, hipStream_t st);
+hipError_t launch_pack_conv(const Geom &g, const Geom *pair, unsigned short *out, int32_t *flags, hipStream_t st);
 // window.hip: the products of a window pass (direct convolution, DMA-staged); window_fits
 // tells whether the kernels cover a geometry (conc: the concretising step)
 bool window_fits(const GeomSet &gs, bool conc);

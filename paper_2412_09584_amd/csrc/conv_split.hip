@@ -21,6 +21,9 @@
 // the taps of both, a third of them with zero weights, took 3.8 ms where the FP32 kernel
 // takes 3.6, so such layers stay with that one.
 //
+// Infinite operands, and images whose parts leave bf16's range: see launch_pack_split.  Finding
+// them by their results takes a maximum per result (no time at 64 inputs of the CNN below).
+//
 // The bf16 instructions round toward minus infinity.  Odd steps' weights are stored negated
 // and go to accumulators of their own, which are subtracted at the end: their bias has the
 // other sign.
@@ -45,6 +48,8 @@ constexpr int PXB = 3 * 2 * CK + 16; // LDS bytes per pixel
 constexpr int SBN = 32;              // columns of a tile
 constexpr int SPLIT_IN4 = 7;         // float4s of the input tile per thread
 constexpr int SPLIT_W4 = 8;          // 16-byte slots of a chunk's weights per thread
+// bits of 2^-80: below it a result's operands (weights of up to 2^20) may lie below SPLIT_MIN
+constexpr unsigned RESULT_MIN = 0x17800000u;
 
 // LDS tile of a split product; false where the kernel does not take it.
 bool tile_split(const GeomSet &gs, ConvTile &ct, size_t &lds, bool window) {
@@ -211,6 +216,42 @@ __global__ __launch_bounds__(256, 2) void k_conv_split(const GeomSet gs, const C
 #pragma unroll
             for (int j = 0; j < FN; ++j) acc[i][j] -= neg[i][j];
 
+        // results that operands outside the range of the three parts may have formed (one that is
+        // not finite, or all so small that their operands' last parts were flushed): the wave's
+        // tile by FP32 instructions
+        float big = 0.f;
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int v = 0; v < MM::NACC; v += 2)   // NaN stays
+                big = __builtin_elementwise_maximum(__builtin_elementwise_maximum(big, fabsf(acc[i][0][v])),
+                                                    fabsf(acc[i][0][v + 1]));
+        const unsigned ub = __float_as_uint(big);
+        const bool tiny = ub < RESULT_MIN && __any(ub != 0) && !__any(ub >= RESULT_MIN);
+        if (__builtin_expect(__any(ub > 0x7f7fffffu) || tiny, 0)) {
+            const int n = n0 + MM::col(lane0), nr = PAIR ? n & 15 : n;
+            const float *w = (PAIR && n >= 16 ? g.Bt2 : g.Bt) + (long)(nr < N ? nr : 0) * g.Kp;
+#pragma unroll 1
+            for (int e = 0; e < FM * MM::NACC; ++e) {
+                const int lr = wv * 64 + e / MM::NACC * MF + MM::row(e % MM::NACC, lane0);
+                const int gi = qdiv(lr, ct.rTP), q = lr - gi * tile_px;
+                const int py = qdiv(q, g.rOW), px = q - py * g.OW;
+                float x = 0.f;
+                if (nr < N && img0 + gi < n_img)
+                    for (int ty = 0; ty < g.kh; ++ty)
+                        for (int tx = 0; tx < g.kw; ++tx) {
+                            const int y = oyb + py - g.pad_y + ty, xx = px - g.pad_x + tx;
+                            if ((unsigned)y >= (unsigned)g.H || (unsigned)xx >= (unsigned)g.W) continue;
+                            const float *p = X + (((img0 + gi) * g.H + y) * (long)g.W + xx) * g.C;
+                            for (int c = 0; c < g.C; ++c) x = fmaf(p[c], w[(ty * g.kw + tx) * g.C + c], x);
+                        }
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int v = 0; v < MM::NACC; ++v) acc[i][0][v] = e == i * MM::NACC + v ? x : acc[i][0][v];
+            }
+        }
+
         int lane = lane0;
         if (LOOP) asm volatile("" : "+v"(lane));            // row indices anew, as in k_conv
         int ncol[FN];
@@ -251,7 +292,7 @@ __global__ __launch_bounds__(256, 2) void k_conv_split(const GeomSet gs, const C
 // Weights [Np][Kp] of a product, or of a pair's two, -> [column tile][chunk][octet of 8
 // channels of a tap][part][32][8], negated in odd steps; zero past the columns.
 __global__ void k_pack_conv(const float *B0, const float *B1, int N, int Kp, int C, int T, long total,
-                            unsigned short *out) {
+                            unsigned short *out, int32_t *flags) {
     const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= total) return;
     const int nch = C / CK;
@@ -264,6 +305,7 @@ __global__ void k_pack_conv(const float *B0, const float *B1, int N, int Kp, int
     const int row = B1 ? n & 15 : y * SBN + n;
     const float *Bt = B1 && n >= 16 ? B1 : B0;
     float x = row < N ? Bt[(long)row * Kp + t * C + ch * CK + (oct & 1) * 8 + i] : 0.f;
+    flag_range(x, flags);
     if ((ch * T + t) & 1) x = -x;
     const __bf16 hi = (__bf16)x;
     const float r = x - (float)hi;
@@ -318,11 +360,12 @@ long conv_split_size(const Geom &g) {
     if (T == 0 || g.C % CK != 0 || g.stride != 1 || g.N <= 4 || (T == 1 && g.H == 1 && g.W == 1)) return 0;
     return (long)((g.N + SBN - 1) / SBN) * (g.C / CK) * T * 2 * 3 * SBN * 8;
 }
-hipError_t launch_pack_conv(const Geom &g, const Geom *pair, unsigned short *out, hipStream_t st) {
+hipError_t launch_pack_conv(const Geom &g, const Geom *pair, unsigned short *out, int32_t *flags, hipStream_t st) {
     const long total = conv_split_size(g) / 3;
     if (total > 0x7fffffffL) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_pack_conv, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, g.Bt,
-                       pair ? pair->Bt : nullptr, pair ? g.N / 2 : g.N, g.Kp, g.C, g.kh * g.kw, total, out);
+                       pair ? pair->Bt : nullptr, pair ? g.N / 2 : g.N, g.Kp, g.C, g.kh * g.kw, total, out,
+                       flags);
     return hipGetLastError();
 }
 

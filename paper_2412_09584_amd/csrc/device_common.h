@@ -97,6 +97,13 @@ template <class T> __device__ inline void st(T *base, int i, T v) {
     *(G *)((char *)base + (unsigned)i * (unsigned)sizeof(T)) = v;
 }
 
+// Packed weights' range (SPLIT_MAX, SPLIT_MIN): see launch_pack_split.
+__device__ inline void flag_range(float x, int32_t *flags) {
+    const unsigned u = __float_as_uint(x) & 0x7fffffffu;
+    const int i = u > SPLIT_MAX ? 0 : (u < SPLIT_MIN ? 1 : 2);
+    if (u != 0 && !flags[i]) flags[i] = 1;
+}
+
 // ---------------------------------------------------------------------- LDS DMA
 // dword 3 of a raw buffer resource (32-bit data format; no swizzle, no index stride)
 constexpr int BUF_FLAGS = 0x00020000;

@@ -131,6 +131,7 @@ __global__ __launch_bounds__(256, SPLIT ? 3 : 1) void k_dense_tall(const Geom g,
     for (int j = 0; j < FN; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+    float big = 0.f;             // largest magnitude of this lane's part of its row
 
     dma(0, 0);
     loadA(0, 0, ra);
@@ -153,6 +154,9 @@ __global__ __launch_bounds__(256, SPLIT ? 3 : 1) void k_dense_tall(const Geom g,
             for (int t = 0; t < 2; ++t) {
                 bf8 ah, am, al;
                 split8(ra + 8 * t, ah, am, al);
+#pragma unroll
+                for (int i = 0; i < 8; i += 2)
+                    big = fmaxf(fmaxf(big, fabsf(ra[8 * t + i])), fabsf(ra[8 * t + i + 1]));
                 if (t == 1) {
                     // the next chunk takes these registers; not earlier, or the second half's
                     // split would wait for it
@@ -215,6 +219,27 @@ __global__ __launch_bounds__(256, SPLIT ? 3 : 1) void k_dense_tall(const Geom g,
             }
 #pragma unroll
             for (int i = 0; i < 16; ++i) ra[i] = rn[i];
+        }
+    }
+
+    if constexpr (SPLIT) {
+        // a row that three bf16 parts do not hold: the wave's tile by FP32 instructions (looking
+        // for one: full CROWN of 16-256x3-1, 2048 boxes, 2.78 -> 2.83 ms)
+        const unsigned u = __float_as_uint(fmaxf(big, __shfl_xor(big, 32, 64)));
+        if (__builtin_expect(__any(u > SPLIT_MAX || (u != 0 && u < SPLIT_MIN)), 0)) {
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+            const float *b = g.Bt + (long)(n0 + col) * g.Kp + 8 * h;
+#pragma unroll 1
+            for (int k0 = 0; k0 < K; k0 += 16)
+#pragma unroll 1
+                for (int k = k0; k < k0 + 8; ++k) {
+                    const float x = k + 8 * h < K ? a[k] : 0.f;
+#pragma unroll
+                    for (int j = 0; j < FN; ++j) acc[j] = MM::mma(x, b[(long)j * 32 * g.Kp + k], acc[j]);
+                }
         }
     }
 
@@ -284,12 +309,13 @@ __global__ __launch_bounds__(256, SPLIT ? 3 : 1) void k_dense_tall(const Geom g,
 }
 
 // Bt [Np][Kp] FP32 -> [Np][Kc][3][32] bf16 (zero past K, as Bt's padding is)
-__global__ void k_pack_split(const float *Bt, int Kp, int Kc, long total, unsigned short *out) {
+__global__ void k_pack_split(const float *Bt, int Kp, int Kc, long total, unsigned short *out, int32_t *flags) {
     const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= total) return;
     const long n = e / (Kc * SK);
     const int k = (int)(e - n * Kc * SK), c = k / SK, i = k - c * SK;
     float x = k < Kp ? Bt[n * Kp + k] : 0.f;
+    flag_range(x, flags);
     if (chunk_sign(c, (int)(n >> 5))) x = -x;
     const __bf16 hi = (__bf16)x;
     const float r = x - (float)hi;
@@ -336,9 +362,11 @@ hipError_t tall_fwd(const GeomSet &gs, const float *A, long M, const FwdParams &
     return run<EpiFwd, false>(gs, A, M, EpiFwd{p}, st);
 }
 
-hipError_t launch_pack_split(const float *Bt, int Np, int Kp, int Kc, unsigned short *out, hipStream_t st) {
+hipError_t launch_pack_split(const float *Bt, int Np, int Kp, int Kc, unsigned short *out, int32_t *flags,
+                             hipStream_t st) {
     const long total = (long)Np * Kc * SK;
-    hipLaunchKernelGGL(k_pack_split, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, Bt, Kp, Kc, total, out);
+    hipLaunchKernelGGL(k_pack_split, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, Bt, Kp, Kc, total, out,
+                       flags);
     return hipGetLastError();
 }
 
