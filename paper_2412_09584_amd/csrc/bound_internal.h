@@ -204,6 +204,9 @@ inline bool is_dense(const GeomSet &gs) {
     return gs.n == 1 && g.H == 1 && g.W == 1 && g.OH == 1 && g.OW == 1 && g.DH == 1 && g.DW == 1 &&
            g.kh == 1 && g.kw == 1 && g.pad_y == 0 && g.pad_x == 0;
 }
+// Whether 128 packed rows of K weights (6 bytes each on the bf16 tile) lie within the 32-bit byte
+// offsets of the LDS DMA
+inline bool dma_fits(const Geom &g) { return 128L * 6 * (g.K + 32L) < (1L << 31); }
 enum { DENSE_W32 = 11, DENSE_W16 = 12, DENSE_W16K4 = 13, DENSE_W16K16 = 14, DENSE_W16O = 15, DENSE_SPLIT = 16, DENSE_F32 = 17 };
 int dense_auto(const GeomSet &gs, long M, bool keep);
 hipError_t dense_relax(const GeomSet &gs, const float *A, long M, const RelaxParams &p, hipStream_t st, int cfg);

@@ -190,6 +190,7 @@ int dense_auto(const GeomSet &gs, long M, bool keep) {
     // tiles, K = 296: 75 -> 12 us), above they re-read A and B too often (384 tiles of K =
     // 296: 40 -> 50 us)
     // (a 1x1 convolution on one pixel has no bf16 weights)
+    if (big >= 256 && !dma_fits(g)) return -1;
     if (big >= 256) return !keep && g.Bs ? DENSE_SPLIT : (g.N >= 32 ? DENSE_F32 : -1);
     const long small = (M + 15) / 16 * ((g.N + 15) / 16);
     // the general GEMM's default tiles are 32x32x2 from 32 columns on

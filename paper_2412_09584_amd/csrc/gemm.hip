@@ -16,14 +16,15 @@ int gemm_candidates(const GeomSet &gs, bool keep, int *cfgs, int cap) {
     const int N = gs.g[0].N;
     int n = 0;
     const Geom &g = gs.g[0];
-    const bool dma = is_dense(gs) && g.C % 4 == 0 && g.K % BK == 0;
+    const bool dma = is_dense(gs) && g.C % 4 == 0 && g.K % BK == 0 && dma_fits(g);
     for (int c = 0; c < kGemmCfgs && n < cap; ++c) {
         if (c >= 9 && !dma) continue;
         if (kCfgBN[c] <= 16 * ((N + 15) / 16) || c == default_cfg(N)) cfgs[n++] = c;
     }
     // the wave-per-tile kernels (they never repeat padding columns past a tile)
     for (int c = DENSE_W32; c <= DENSE_F32 && n < cap && is_dense(gs); ++c)
-        if ((c != DENSE_W16K16 || g.K >= 256) && (c != DENSE_SPLIT || g.Bs) && (!keep || keeps_order(c, N)))
+        if ((c != DENSE_W16K16 || g.K >= 256) && (c != DENSE_SPLIT || g.Bs) && (c < DENSE_SPLIT || dma_fits(g)) &&
+            (!keep || keeps_order(c, N)))
             cfgs[n++] = c;
     return n;
 }
@@ -79,7 +80,8 @@ hipError_t gemm_relax(const GeomSet &gs, const float *A, long n_img, const Relax
             const int d = plan.path == 0 ? dense_auto(gs, n_img, plan.keep) : -1;            \
             if (d >= 0) return DENSE(gs, A, n_img, p, st, d);                                \
         } else if (plan.cfg >= DENSE_W32 && is_dense(gs) &&                                  \
-                   (plan.cfg != DENSE_SPLIT || gs.g[0].Bs)) {                                \
+                   (plan.cfg != DENSE_SPLIT || gs.g[0].Bs) &&                                \
+                   (plan.cfg < DENSE_SPLIT || dma_fits(gs.g[0]))) {                          \
             return DENSE(gs, A, n_img, p, st, plan.cfg);                                     \
         }                                                                                    \
         return CFG(gs, A, n_img, p, st, plan.path == 2 ? plan.cfg : -1);                     \

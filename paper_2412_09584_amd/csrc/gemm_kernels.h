@@ -362,7 +362,7 @@ hipError_t launch_cfg(const GeomSet &gs, const float *A, long n_img, const Epi &
     }
     bool k16 = true;
     for (int i = 0; i < gs.n; ++i) k16 = k16 && gs.g[i].K % BK == 0;
-    if (DMAG && dense && vec && k16)
+    if (DMAG && dense && vec && k16 && dma_fits(g0))
         hipLaunchKernelGGL((k_gemm<Epi, MF, BM, BN, WGM, WGN, true, true, DMAG>), grid, dim3(256), 0, st, gs, A, n_img, epi);
     else if (dense && vec)
         hipLaunchKernelGGL((k_gemm<Epi, MF, BM, BN, WGM, WGN, true, true>), grid, dim3(256), 0, st, gs, A, n_img, epi);

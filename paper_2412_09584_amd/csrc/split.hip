@@ -337,7 +337,7 @@ hipError_t launch(const Geom &g, const float *A, long M, const Epi &epi, hipStre
 template <class Epi, bool SPLIT>
 hipError_t run(const GeomSet &gs, const float *A, long M, const Epi &epi, hipStream_t st) {
     const Geom &g = gs.g[0];
-    if (!is_dense(gs) || (SPLIT && !g.Bs)) return hipErrorInvalidValue;   // no packed weights to read
+    if (!is_dense(gs) || (SPLIT && !g.Bs) || !dma_fits(g)) return hipErrorInvalidValue;   // no weights it can read
     const int rem = g.N % 128;
     if (g.N <= 32) return launch<Epi, 1, SPLIT>(g, A, M, epi, st);
     // 64 columns where 128 would pad half a tile, or leave the chip's last round nearly empty

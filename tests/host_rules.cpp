@@ -209,6 +209,12 @@ static void split_weights() {
     for (int c : listed(gs)) check(c != DENSE_SPLIT, "listed without weights");
     check(tall_relax(gs, nullptr, 1, RelaxParams{}, nullptr, true) == hipErrorInvalidValue, "relaxing product");
     check(tall_conc(gs, nullptr, 1, ConcParams{}, nullptr, true) == hipErrorInvalidValue, "concretising product");
+    // nor may 128 rows of them pass the DMA's 32-bit offsets
+    GeomSet wide = one(pixel(3000000, 4096));
+    wide.g[0].Bs = &w;
+    for (bool keep : {false, true}) check(dense_auto(wide, 4096, keep) < 0, "chosen for too wide rows");
+    for (int c : listed(wide)) check(c != 9 && c != 10 && c < DENSE_SPLIT, "listed for too wide rows", c);
+    check(tall_relax(wide, nullptr, 4096, RelaxParams{}, nullptr, false) == hipErrorInvalidValue, "too wide rows");
     gs.g[0].Bs = &w;
     bool found = false;
     for (int c : listed(gs)) found = found || c == DENSE_SPLIT;
