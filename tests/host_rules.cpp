@@ -315,8 +315,33 @@ static void window_index() {
     }
 }
 
+// What the passes of test_gpu_window_loops.py reach: blocks of several groups with a ragged end,
+// and windows of 16 pixels a side.
+static void window_loops() {
+    Net net({conv(3, 32, 16, 3, 1, 1), conv(16, 32, 32, 4, 2, 1), conv(32, 16, 32, 3, 1, 1), conv(32, 16, 64, 4, 2, 1),
+             linear(64, 8, 2)}, 5, 81901);
+    auto grid = [](const char *kernel, const char *epi) {
+        for (auto &l : launches)
+            if (l.name.find(kernel) != std::string::npos && l.name.find(epi) != std::string::npos) return (long)l.grid.x;
+        return 0L;
+    };
+    net.backward(3, 5, 0, BOUND_BOTH_SIDES);
+    // 5119 groups of 16 images, two pairs of phases, two groups a block: 2560 blocks a pair
+    check(grid("k_conv_split", "EpiRelaxWin, true>") == 2560 * 2, "pairs", (int)grid("k_conv_split", "EpiRelaxWin, true>"));
+    net.backward(4, 5, 0, BOUND_BOTH_SIDES);
+    // 40960 rows in groups of 4 images: 10240 tiles, two a block
+    check(grid("k_conv_split", "EpiRelaxWin, false>") == 5120, "single phases",
+          (int)grid("k_conv_split", "EpiRelaxWin, false>"));
+    Net wide({conv(3, 20, 32, 3, 1, 1), conv(32, 20, 32, 3, 1, 1), conv(32, 20, 32, 3, 1, 1), conv(32, 20, 32, 3, 1, 1),
+              conv(32, 20, 32, 3, 1, 1), linear(32, 20, 2)}, 1, 25600);
+    wide.backward(5, 1, 0, BOUND_BOTH_SIDES);
+    // 25600 rows: 256 pixels a window are a tile of one image, six of them a block
+    check(count({"k_init_window"}) == 1 && launches[launches.size() - 3].grid.x == (25600 + 5) / 6, "16 a side",
+          (int)launches[launches.size() - 3].grid.x);
+}
+
 int main(int argc, char **argv) {
-    const struct { const char *name; void (*f)(); } tests[] = {{"dense", dense}, {"split_weights", split_weights}, {"direct_dma", direct_dma}, {"tuning", tuning}, {"large", large}, {"window_index", window_index}};
+    const struct { const char *name; void (*f)(); } tests[] = {{"dense", dense}, {"split_weights", split_weights}, {"direct_dma", direct_dma}, {"tuning", tuning}, {"large", large}, {"window_index", window_index}, {"window_loops", window_loops}};
     for (auto &t : tests)
         if (argc == 2 && !std::strcmp(argv[1], t.name)) {
             t.f();

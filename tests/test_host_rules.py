@@ -63,3 +63,8 @@ def test_window_indices_stay_in_range(rules):
     """The window epilogues multiply in 24 bits; passes over layers whose pixel indices exceed
     that may not run on windows."""
     rules("window_index")
+
+
+def test_large_window_passes_reach_their_configurations(rules):
+    """The GPU test of large window passes runs blocks of several groups and 16-pixel windows."""
+    rules("window_loops")
