@@ -2,7 +2,7 @@
 // split clamping, box centre / radius, start of a backward pass, split-multiplier
 // injection and gradient, final assembly of the bound, the adjoint's start, the
 // standalone box concretisation (Theorem 2), Adam, and weight packing.
-#include "bound_internal.h"
+#include "device_common.h"
 
 namespace bp {
 namespace {
@@ -538,30 +538,6 @@ __global__ void k_init_identity(const IdentityParams p, long n_img) {
     }
 }
 
-// Sums over a wave of the NV (a power of two) values of every lane: each step halves the
-// values a lane carries.  Returns the sum of value `r`, held by 64 / NV lanes.
-template <int NV> __device__ inline float sum_lanes(float (&v)[NV], int lane, int &r) {
-    r = 0;
-    int n = NV;
-#pragma unroll
-    for (int mk = 32; mk > 0; mk >>= 1) {
-        if (n > 1) {
-            n >>= 1;
-            const bool up = (lane & mk) != 0;
-            r += up ? n : 0;
-#pragma unroll
-            for (int k = 0; k < NV / 2; ++k)
-                if (k < n) {
-                    const float mine = up ? v[k + n] : v[k], other = up ? v[k] : v[k + n];
-                    v[k] = mine + __shfl_xor(other, mk, 64);
-                }
-        } else {
-            v[0] += __shfl_xor(v[0], mk, 64);
-        }
-    }
-    return v[0];
-}
-
 // Identity rows of a Linear target: one wave takes ID_ROWS neurons of one instance, both
 // sides, and walks their columns 64 at a time, so a column's record (or box) is loaded once
 // for all of them and the sums of all rows are reduced together.  W: the layer's rows in
@@ -626,8 +602,8 @@ __global__ __launch_bounds__(256) void k_init_dense(const IdentityParams p, cons
         }
     }
     int q;
-    const float a = sum_lanes<ID_ROWS>(sp, lane, q), b = sum_lanes<ID_ROWS>(mp, lane, q);
-    const float c = sum_lanes<ID_ROWS>(sn, lane, q), d = sum_lanes<ID_ROWS>(mn, lane, q);
+    const float a = dev::sum_rows<64, ID_ROWS>(sp, lane, q), b = dev::sum_rows<64, ID_ROWS>(mp, lane, q);
+    const float c = dev::sum_rows<64, ID_ROWS>(sn, lane, q), d = dev::sum_rows<64, ID_ROWS>(mn, lane, q);
     if ((lane & (64 / ID_ROWS - 1)) != 0 || r0 + q >= p.dk) return;
     const float bk = p.bias_k[r0 + q];
     if (up + q >= 0 && up + q < n_img) {
@@ -670,8 +646,8 @@ __global__ __launch_bounds__(256) void k_dense1_bounds(const IdentityParams p, c
         }
     }
     int q;
-    const float a = sum_lanes<ID_ROWS>(gc, lane, q), b = sum_lanes<ID_ROWS>(gr, lane, q);
-    const float m = sum_lanes<ID_ROWS>(gm, lane, q);
+    const float a = dev::sum_rows<64, ID_ROWS>(gc, lane, q), b = dev::sum_rows<64, ID_ROWS>(gr, lane, q);
+    const float m = dev::sum_rows<64, ID_ROWS>(gm, lane, q);
     if ((lane & (64 / ID_ROWS - 1)) != 0 || r0 + q >= p.dk) return;
     const float bk = p.bias_k[r0 + q], sl = slack ? KAPPA_U * (fabsf(bk) + m) : 0.f;
     const float lo = bk + (a - b) - sl, hi = bk + (a + b) + sl;

@@ -38,9 +38,6 @@
 namespace bp {
 namespace {
 
-typedef float f2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef unsigned u2 __attribute__((ext_vector_type(2)));
 
 constexpr int CK = 16;               // channels per chunk
@@ -76,14 +73,11 @@ __device__ inline void split4(const float4 v, u2 &hi, u2 &mid, u2 &lo) {
     const float x[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const float a = x[2 * i], b = x[2 * i + 1];
-        const unsigned hp = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){a, b}, bf2));
-        const float ra = a - __uint_as_float(hp << 16), rb = b - __uint_as_float(hp & 0xffff0000u);
-        const unsigned mp = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){ra, rb}, bf2));
-        const float qa = ra - __uint_as_float(mp << 16), qb = rb - __uint_as_float(mp & 0xffff0000u);
+        unsigned hp, mp, lp;
+        split_pair(x[2 * i], x[2 * i + 1], hp, mp, lp);
         hi[i] = hp;
         mid[i] = mp;
-        lo[i] = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){qa, qb}, bf2));
+        lo[i] = lp;
     }
 }
 
@@ -307,13 +301,8 @@ __global__ void k_pack_conv(const float *B0, const float *B1, int N, int Kp, int
     float x = row < N ? Bt[(long)row * Kp + t * C + ch * CK + (oct & 1) * 8 + i] : 0.f;
     flag_range(x, flags);
     if ((ch * T + t) & 1) x = -x;
-    const __bf16 hi = (__bf16)x;
-    const float r = x - (float)hi;
-    const __bf16 mid = (__bf16)r, lo = (__bf16)(r - (float)mid);
     unsigned short *o = out + ((((long)y * nch + ch) * (2 * T) + oct) * 3 * SBN + n) * 8 + i;
-    o[0] = __builtin_bit_cast(unsigned short, hi);
-    o[SBN * 8] = __builtin_bit_cast(unsigned short, mid);
-    o[2 * SBN * 8] = __builtin_bit_cast(unsigned short, lo);
+    split_one(x, o[0], o[SBN * 8], o[2 * SBN * 8]);
 }
 
 template <class Epi, bool PAIR>

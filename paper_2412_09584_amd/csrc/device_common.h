@@ -97,6 +97,28 @@ template <class T> __device__ inline void st(T *base, int i, T v) {
     *(G *)((char *)base + (unsigned)i * (unsigned)sizeof(T)) = v;
 }
 
+// ---------------------------------------------------------------------- bf16 parts
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+
+// An FP32 value as three bf16 values, each the rounded remainder of the one before: of a pair,
+// packed, and of one (weights, on packing).
+__device__ inline void split_pair(float a, float b, unsigned &hi, unsigned &mid, unsigned &lo) {
+    hi = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){a, b}, bf2));
+    const float ra = a - __uint_as_float(hi << 16), rb = b - __uint_as_float(hi & 0xffff0000u);
+    mid = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){ra, rb}, bf2));
+    const float qa = ra - __uint_as_float(mid << 16), qb = rb - __uint_as_float(mid & 0xffff0000u);
+    lo = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){qa, qb}, bf2));
+}
+__device__ inline void split_one(float x, unsigned short &hi, unsigned short &mid, unsigned short &lo) {
+    const __bf16 h = (__bf16)x;
+    const float r = x - (float)h;
+    const __bf16 m = (__bf16)r, l = (__bf16)(r - (float)m);
+    hi = __builtin_bit_cast(unsigned short, h);
+    mid = __builtin_bit_cast(unsigned short, m);
+    lo = __builtin_bit_cast(unsigned short, l);
+}
 // Packed weights' range (SPLIT_MAX, SPLIT_MIN): see launch_pack_split.
 __device__ inline void flag_range(float x, int32_t *flags) {
     const unsigned u = __float_as_uint(x) & 0x7fffffffu;
@@ -312,11 +334,6 @@ struct EpiRelaxWin {
     __device__ double *red0() const { return p.s; }
     __device__ double *red1() const { return p.mag; }
     __device__ const DetSums *det() const { return nullptr; }
-    __device__ Pre pre(const Row &rc, int dp, int n, int N) const {
-        const int px = win_pixel(w, rc.y0, rc.x0, dp);
-        return px >= 0 && n < N ? ld(rc.tb, px * N + n) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    __device__ void pre2(const Row &, Pre &) const {}
     __device__ void post(const Pre &t, const Row &rc, int, int, int j, float bcol, float g,
                          float &r0, float &r1) const {
         const float lam = g >= 0.f ? g * t.x : g * t.y;

@@ -38,9 +38,6 @@ namespace {
 using namespace dev;
 
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // rows of any width
-typedef float f2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef unsigned u4 __attribute__((ext_vector_type(4)));
 
 constexpr int SK = 32;           // k per chunk
@@ -51,14 +48,11 @@ __device__ inline void split8(const float *x, bf8 &hi, bf8 &mid, bf8 &lo) {
     u4 h, m, l;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const float a = x[2 * i], b = x[2 * i + 1];
-        const unsigned hp = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){a, b}, bf2));
-        const float ra = a - __uint_as_float(hp << 16), rb = b - __uint_as_float(hp & 0xffff0000u);
-        const unsigned mp = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){ra, rb}, bf2));
-        const float qa = ra - __uint_as_float(mp << 16), qb = rb - __uint_as_float(mp & 0xffff0000u);
+        unsigned hp, mp, lp;
+        split_pair(x[2 * i], x[2 * i + 1], hp, mp, lp);
         h[i] = hp;
         m[i] = mp;
-        l[i] = __builtin_bit_cast(unsigned, __builtin_convertvector((f2){qa, qb}, bf2));
+        l[i] = lp;
     }
     hi = __builtin_bit_cast(bf8, h);
     mid = __builtin_bit_cast(bf8, m);
@@ -317,13 +311,8 @@ __global__ void k_pack_split(const float *Bt, int Kp, int Kc, long total, unsign
     float x = k < Kp ? Bt[n * Kp + k] : 0.f;
     flag_range(x, flags);
     if (chunk_sign(c, (int)(n >> 5))) x = -x;
-    const __bf16 hi = (__bf16)x;
-    const float r = x - (float)hi;
-    const __bf16 mid = (__bf16)r, lo = (__bf16)(r - (float)mid);
     unsigned short *o = out + ((n * Kc + c) * 3) * SK + i;
-    o[0] = __builtin_bit_cast(unsigned short, hi);
-    o[SK] = __builtin_bit_cast(unsigned short, mid);
-    o[2 * SK] = __builtin_bit_cast(unsigned short, lo);
+    split_one(x, o[0], o[SK], o[2 * SK]);
 }
 
 template <class Epi, int FN, bool SPLIT>
