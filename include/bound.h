@@ -285,8 +285,9 @@ bound_status bound_adam(int64_t n, float *param, const float *grad, float *m, fl
  * direct-convolution kernels with their tiles staged by LDS DMA (by themselves they stage
  * through registers where there are few blocks, and passes that save nothing may take other
  * kernels).  All variants compute the same bound; the options exist to test and compare
- * them.  While any option is set, full CROWN's passes over convolutional layers
- * use whole layers instead of receptive-field windows, several times slower.  BOUND_OPT_CHECK (debugging): after every product of bound_backward and
+ * them.  While any option but BOUND_OPT_CHECK is set, full CROWN's passes over
+ * convolutional layers use whole layers instead of receptive-field windows, several times
+ * slower.  BOUND_OPT_CHECK (debugging): after every product of bound_backward and
  * bound_grad the library counts NaN and Inf values in the product's output (and in the
  * gradient it returns), waits for the count, and returns BOUND_E_NUMERIC naming the
  * product if there are any; the calls become synchronous.  Not applied while the stream
@@ -312,7 +313,7 @@ bound_status bound_set_options(bound_net *net, int32_t options);
  * rows), which choose among the FP32 kernels, and all others, which also choose among those
  * on the bf16 matrix cores at FP32 precision.  Full CROWN's passes over convolutional layers
  * run on receptive-field windows, which have no plans; here their whole-layer products are
- * timed, for the passes that use those (a coefficient output, or any option set).
+ * timed, for the passes that use those (a coefficient output, or an option but BOUND_OPT_CHECK set).
  * Synchronises the stream; must not be called while the stream is being captured.
  * bound_autotune_report copies the timing log (NUL-terminated, truncated to cap) and
  * returns its full length. */

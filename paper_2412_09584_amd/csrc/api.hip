@@ -546,6 +546,8 @@ bound_status window_pass(bound_net *net, const bound_pass *P, const bound_out *o
             ProfScope ps(net, st, lbl("init_window_L%d", k));
             HIPCHK(launch_init_window(ip, wp.map[k - 1], n_img, st));
         }
+        bound_status bs = debug_check(net, st, cur, n_img * wp.elems[k - 1], lbl("init_window_L%d", k));
+        if (bs != BOUND_OK) return bs;
         for (int m = k - 1; m >= 2; --m) {
             RelaxParams rp{};
             rp.out = nxt;
@@ -556,9 +558,13 @@ bound_status window_pass(bound_net *net, const bound_pass *P, const bound_out *o
             rp.D = wp.elems[m - 1];
             rp.s = net->acc_s;
             rp.mag = net->acc_mag;
-            ProfScope ps(net, st, lbl("win_relax_L%d", m));
-            HIPCHK(window_relax(wp.gs[m], wp.gp[m], cur, n_img, rp, wp.map[m - 1], st));
+            {
+                ProfScope ps(net, st, lbl("win_relax_L%d", m));
+                HIPCHK(window_relax(wp.gs[m], wp.gp[m], cur, n_img, rp, wp.map[m - 1], st));
+            }
             std::swap(cur, nxt);
+            bs = debug_check(net, st, cur, n_img * wp.elems[m - 1], lbl("win_relax_L%d", m));
+            if (bs != BOUND_OK) return bs;
         }
         ConcParams cp{};
         cp.cen = net->cen;
@@ -570,6 +576,8 @@ bound_status window_pass(bound_net *net, const bound_pass *P, const bound_out *o
             ProfScope ps(net, st, "win_conc");
             HIPCHK(window_conc(wp.gs[1], cur, n_img, cp, wp.map[0], st));
         }
+        bs = debug_check(net, st, net->acc_low, n_img, "win_conc");
+        if (bs != BOUND_OK) return bs;
         ProfScope pf(net, st, "finalize");
         HIPCHK(launch_finalize(img0, n_img, P->rows, rpi, net->acc_s, net->acc_low, net->acc_mag, net->infeas,
                                slack, out->lower, both ? out->upper : nullptr, ld, nullptr, nullptr, out->best,
@@ -845,11 +853,11 @@ bound_status bound_backward(bound_net *net, const bound_pass *P, const bound_out
     }
 
     // Full CROWN's passes: z_1 straight from the box, a convolutional layer's rows on windows
-    // instead of whole layers.  Early
-    // stops, split multipliers, coefficient output and the options (tests and
-    // comparisons of the whole-layer kernels) keep the general path.
+    // instead of whole layers.  Early stops, split multipliers, coefficient output and the
+    // options that choose kernels or their sums keep the general path.
     const bool keep = save;   // see Plan
-    const bool winok = ident && conc && sl == 0 && !inject && net->options == 0 && !net->tuning;
+    const bool winok =
+        ident && conc && sl == 0 && !inject && (net->options & ~BOUND_OPT_CHECK) == 0 && !net->tuning;
     if (winok && k == 1) {
         IdentityParams ip = identity_params(net, k, rpi, 0);
         const Geom &wf = net->layers[0].gF.g[0];

@@ -340,8 +340,18 @@ static void window_loops() {
           (int)launches[launches.size() - 3].grid.x);
 }
 
+// BOUND_OPT_CHECK checks the window kernels that full CROWN runs without it: the first windows,
+// every product and the concretised sums.
+static void debug_windows() {
+    Net net({conv(4, 16, 16, 3, 1, 1), conv(16, 16, 16, 3, 1, 1), conv(16, 16, 16, 3, 1, 1), linear(16, 16, 2)}, 1, 8192);
+    bound_set_options(net.h, BOUND_OPT_CHECK);
+    net.backward(3, 1, 0, BOUND_BOTH_SIDES);
+    check(count({"k_init_window"}) == 1 && count({"EpiRelaxWin"}) == 1 && count({"EpiConcWin"}) == 1, "windows");
+    check(count({"k_count_nonfinite"}) == 3, "checks", count({"k_count_nonfinite"}));
+}
+
 int main(int argc, char **argv) {
-    const struct { const char *name; void (*f)(); } tests[] = {{"dense", dense}, {"split_weights", split_weights}, {"direct_dma", direct_dma}, {"tuning", tuning}, {"large", large}, {"window_index", window_index}, {"window_loops", window_loops}};
+    const struct { const char *name; void (*f)(); } tests[] = {{"dense", dense}, {"split_weights", split_weights}, {"direct_dma", direct_dma}, {"tuning", tuning}, {"large", large}, {"window_index", window_index}, {"window_loops", window_loops}, {"debug_windows", debug_windows}};
     for (auto &t : tests)
         if (argc == 2 && !std::strcmp(argv[1], t.name)) {
             t.f();

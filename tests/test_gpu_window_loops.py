@@ -48,3 +48,18 @@ def test_large_window_passes(name):
             out.append((low, up))
         for a, b in zip(*out):
             assert bool(((a - b).abs() <= 5e-6 * b.abs().clamp_min(1.0)).all()), f"target {k}"
+
+
+def test_debug_check_names_the_window_product():
+    from paper_2412_09584_amd import binding as B
+    from paper_2412_09584_amd import net as N
+    rng = np.random.default_rng(283)
+    net = [W._conv(rng, (3, 16, 16), 16, 3, 1, 1), W._conv(rng, (16, 16, 16), 16, 3, 1, 1), W._linear(rng, 4096, 2)]
+    x_lo, x_hi = W.linf_box(W.uniform_inputs(1, 768, 284), 0.01)
+    bn = N.BoundNet(net, 1, 8192)
+    B.bound_set_options(bn.handle, B.BOUND_OPT_CHECK)
+    bn.crown_bounds(x_lo, x_hi)
+    x_lo[0, 5] = np.nan
+    with pytest.raises(B.BoundError) as e:
+        bn.crown_bounds(x_lo, x_hi)
+    assert e.value.status == B.BOUND_E_NUMERIC and "L2" in str(e.value)   # z_1's NaN bounds reach its records

@@ -68,3 +68,8 @@ def test_window_indices_stay_in_range(rules):
 def test_large_window_passes_reach_their_configurations(rules):
     """The GPU test of large window passes runs blocks of several groups and 16-pixel windows."""
     rules("window_loops")
+
+
+def test_debug_checks_cover_windows(rules):
+    """BOUND_OPT_CHECK looks at the products that run without it, window passes included."""
+    rules("debug_windows")
