@@ -424,8 +424,8 @@ __global__ __launch_bounds__(TPB) void k_prune_scatter(int n, const float *f_lo,
 // lane has 16-bit counters of its own: the leading byte of FP32 keys takes few values, and a
 // shared bin would serialise the wave.  Pick-out of 1024 from 60000, split, best and pruner:
 // 223 -> 148 us (keys in memory and one histogram: 200 us).  Larger sets and picks keep the
-// device-wide sort.
-constexpr int ONE_T = 1024, ONE_PER = 64, ONE_MAX = ONE_T * ONE_PER, ONE_SORT = 4096;
+// device-wide sort: see pick_one_fits.
+constexpr int ONE_T = 1024, ONE_PER = 64, ONE_MAX = ONE_T * ONE_PER, ONE_SORT = 2048;
 
 // order-preserving bits of a comparison key
 __device__ inline unsigned order_bits(float x) {
@@ -719,6 +719,18 @@ hipError_t select_flagged(bound_bab *b, int n, int32_t *out, int32_t *n_out, hip
 }
 
 }  // namespace
+
+// One block or the device-wide sort (which takes a dozen launches, but is bound by no single
+// unit).  us, device-wide / one block, eta = 0.75 and 1: 60000 subdomains, 1024 picks 205 / 134;
+// 8192, 2048 90 / 54 and 44 / 35; 8192, 6000 90 / 100; 8193, 5461 90 / 101 -- a phase of more than
+// 2048 picks sorts in LDS behind a barrier a stride.  Few or very many subdomains leave less to
+// gain: 4096, 3072 63 / 70; 32769, 3072 149 / 158.  With all picked the device-wide path has no
+// rest to list (1000, 1000 30 / 38), and with phase 1 alone it has one sort: 32768, 2048 54 / 45,
+// 32769, 2048 55 / 78.
+bool pick_one_fits(int n_dom, int n, int n1) {
+    return n_dom <= ONE_MAX && n < n_dom && n1 <= ONE_SORT && n - n1 <= ONE_SORT &&
+           (n <= ONE_SORT || (n_dom > 4096 && n_dom <= 32768)) && (n_dom <= 32768 || n > n1);
+}
 }  // namespace bp
 
 using bp::set_error;
@@ -775,7 +787,7 @@ bound_status bound_bab_pick_out(bound_bab *b, int32_t n_dom, const float *f_lo, 
     hipStream_t st = (hipStream_t)stream;
     const int n = n_pick < n_dom ? n_pick : n_dom;
     const int n1 = (int)std::floor((double)eta * (double)n);
-    if (n_dom <= bp::ONE_MAX && n1 <= bp::ONE_SORT && n - n1 <= bp::ONE_SORT) {
+    if (bp::pick_one_fits(n_dom, n, n1)) {
         const auto f = n_dom <= 8 * bp::ONE_T    ? bp::k_pick_one<8>
                        : n_dom <= 32 * bp::ONE_T ? bp::k_pick_one<32>
                                                  : bp::k_pick_one<bp::ONE_PER>;

@@ -420,6 +420,9 @@ hipError_t launch_concretize(int n_inst, int rows, long d0, const float *coeff,
                              const float *offset, const float *offset_mag, const float *x_lo,
                              const float *x_hi, bool slack, float *lower, hipStream_t st);
 
+// bab.hip: whether one block picks n of n_dom subdomains, n1 of them in phase 1
+bool pick_one_fits(int n_dom, int n, int n1);
+
 // Packing helpers (aux.hip)
 hipError_t launch_pack_T(const float *W, int kind, int ci, int hi_, int wi, int co, int ho,
                          int wo, int kh, int kw, int stride, int pad, int py, int px, int ky0,

@@ -350,8 +350,19 @@ static void debug_windows() {
     check(count({"k_count_nonfinite"}) == 3, "checks", count({"k_count_nonfinite"}));
 }
 
+// One block picks only where that was measured faster than the device-wide sort.
+static void picks() {
+    struct { int n_dom, n, n1; bool one; } t[] = {
+        {300, 64, 48, true}, {1000, 700, 700, true}, {2048, 1500, 1125, true}, {4096, 2048, 1024, true},
+        {60000, 1024, 768, true}, {8192, 2048, 2048, true}, {8192, 4096, 2048, true}, {32768, 2048, 2048, true},
+        {65536, 2048, 1536, true}, {1000, 1000, 750, false}, {4096, 3072, 1536, false}, {8192, 6000, 3000, false},
+        {8193, 5461, 4095, false}, {12000, 3072, 3072, false}, {32769, 2048, 2048, false}, {32769, 3072, 1536, false},
+        {45000, 64, 64, false}, {65537, 64, 48, false}};
+    for (auto &q : t) check(pick_one_fits(q.n_dom, q.n, q.n1) == q.one, "one block", q.n_dom);
+}
+
 int main(int argc, char **argv) {
-    const struct { const char *name; void (*f)(); } tests[] = {{"dense", dense}, {"split_weights", split_weights}, {"direct_dma", direct_dma}, {"tuning", tuning}, {"large", large}, {"window_index", window_index}, {"window_loops", window_loops}, {"debug_windows", debug_windows}};
+    const struct { const char *name; void (*f)(); } tests[] = {{"dense", dense}, {"split_weights", split_weights}, {"direct_dma", direct_dma}, {"tuning", tuning}, {"large", large}, {"window_index", window_index}, {"window_loops", window_loops}, {"debug_windows", debug_windows}, {"picks", picks}};
     for (auto &t : tests)
         if (argc == 2 && !std::strcmp(argv[1], t.name)) {
             t.f();

@@ -73,3 +73,8 @@ def test_large_window_passes_reach_their_configurations(rules):
 def test_debug_checks_cover_windows(rules):
     """BOUND_OPT_CHECK looks at the products that run without it, window passes included."""
     rules("debug_windows")
+
+
+def test_one_block_picks_where_it_is_faster(rules):
+    """Pick-outs that the device-wide sort does in less time keep it."""
+    rules("picks")
