@@ -182,21 +182,35 @@ hipError_t run(const GeomSet &gs, const float *A, long M, const Epi &epi, hipStr
 
 }  // namespace
 
+// The lines were drawn by relaxing products of K x N = 10 x 512 .. 4096 x 512 and 64 .. 36864
+// rows (us, one side / the other):
+//  - one 128 x 128 tile per CU: below, the wave kernels are faster than the LDS-tiled GEMM (4096 x
+//    512, 4608 rows: 360 W32, 364 GEMM; 256 x 256, 4608: 29, 57), above they re-read A and B too
+//    often (296 x 296, 16384: 50, 40).
+//  - up to K = 128 a tile is loads and epilogue: 32 x 32 from 96 of them on (64 x 64: 576 rows 11
+//    on both, 4608 rows 11, 16 x 16 21; 100 x 100: 576 rows 14, 12; 16384 rows 22, 32).
+//  - longer chains: four waves share one of 16 x 16 while tiles are few (4096 x 512: 576 rows,
+//    1152 tiles, 86, 32 x 32 123; 1152 rows, 2304 tiles, 148, 125; 512 x 4096, 200 rows, 3328
+//    tiles, 54, 27); sixteen waves were slower from the first tile on (4096 x 512, 1 row: 19 by
+//    four, 22).  Where a quarter of the 32-wide tiles' columns or more would be padding, 16 x 16
+//    stay: 1000 x 40, 9216 rows 31 shared by four, 44; past 2048 tiles one wave each (16384 rows
+//    42, shared 51).
+//  - products that keep the general order: see the head of the file (W32 from 4096 tiles on:
+//    576 rows of 512 x 4096 62, 16 x 16 87).
 int dense_auto(const GeomSet &gs, long M, bool keep) {
     const Geom &g = gs.g[0];
     if (!is_dense(gs) || M <= 0) return -1;
     const long big = (M + 127) / 128 * ((g.N + 127) / 128);       // tiles of the LDS-tiled GEMM
-    // one tile per CU: below, the wave kernels are faster (160 tiles, K = 512: 95 -> 63 us; 3
-    // tiles, K = 296: 75 -> 12 us), above they re-read A and B too often (384 tiles of K =
-    // 296: 40 -> 50 us)
     // (a 1x1 convolution on one pixel has no bf16 weights)
     if (big >= 256 && !dma_fits(g)) return -1;
     if (big >= 256) return !keep && g.Bs ? DENSE_SPLIT : (g.N >= 32 ? DENSE_F32 : -1);
-    const long small = (M + 15) / 16 * ((g.N + 15) / 16);
+    const long small = (M + 15) / 16 * ((g.N + 15) / 16), n32 = (g.N + 31) / 32;
     // the general GEMM's default tiles are 32x32x2 from 32 columns on
     if (keep) return g.N < 32 ? DENSE_W16 : (small <= 4096 ? DENSE_W16O : DENSE_W32);
-    if (g.K >= 1024 && small <= 512) return DENSE_W16K16;
-    return g.K > 128 && small <= 1024 ? DENSE_W16K4 : DENSE_W16;
+    if (g.K <= 128) return (M + 31) / 32 * n32 >= 96 ? DENSE_W32 : DENSE_W16;
+    const bool padded = n32 * 128 > 5L * g.N;
+    if (small > 1152 && !padded) return DENSE_W32;
+    return small <= 2048 ? DENSE_W16K4 : DENSE_W16;
 }
 
 hipError_t dense_relax(const GeomSet &gs, const float *A, long M, const RelaxParams &p, hipStream_t st, int cfg) {

@@ -361,8 +361,24 @@ static void picks() {
     for (auto &q : t) check(pick_one_fits(q.n_dom, q.n, q.n1) == q.one, "one block", q.n_dom);
 }
 
+// The dense kernels' lines, on either side.
+static void dense_lines() {
+    struct { int K, N; long M; int cfg; } t[] = {
+        {64, 64, 576, DENSE_W16}, {64, 64, 1536, DENSE_W32}, {64, 16, 4608, DENSE_W32}, {10, 512, 200, DENSE_W32},
+        {4096, 512, 1, DENSE_W16K4}, {4096, 512, 576, DENSE_W16K4}, {4096, 512, 1152, DENSE_W32},
+        {4096, 512, 4608, DENSE_W32}, {2048, 2048, 1152, DENSE_W32}, {512, 4096, 200, DENSE_W32},
+        {1000, 40, 9216, DENSE_W16K4}, {1000, 40, 16384, DENSE_W16}, {1000, 16, 9216, DENSE_W16K4},
+        {256, 256, 16384, DENSE_SPLIT}};
+    const unsigned short w = 0;
+    for (auto &q : t) {
+        GeomSet gs = one(pixel(q.K, q.N));
+        gs.g[0].Bs = &w;
+        check(dense_auto(gs, q.M, false) == q.cfg, "dense kernel", dense_auto(gs, q.M, false));
+    }
+}
+
 int main(int argc, char **argv) {
-    const struct { const char *name; void (*f)(); } tests[] = {{"dense", dense}, {"split_weights", split_weights}, {"direct_dma", direct_dma}, {"tuning", tuning}, {"large", large}, {"window_index", window_index}, {"window_loops", window_loops}, {"debug_windows", debug_windows}, {"picks", picks}};
+    const struct { const char *name; void (*f)(); } tests[] = {{"dense", dense}, {"split_weights", split_weights}, {"direct_dma", direct_dma}, {"tuning", tuning}, {"large", large}, {"window_index", window_index}, {"window_loops", window_loops}, {"debug_windows", debug_windows}, {"picks", picks}, {"dense_lines", dense_lines}};
     for (auto &t : tests)
         if (argc == 2 && !std::strcmp(argv[1], t.name)) {
             t.f();

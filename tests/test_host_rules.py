@@ -78,3 +78,8 @@ def test_debug_checks_cover_windows(rules):
 def test_one_block_picks_where_it_is_faster(rules):
     """Pick-outs that the device-wide sort does in less time keep it."""
     rules("picks")
+
+
+def test_dense_kernels_by_measured_lines(rules):
+    """Dense products of passes that save nothing: the kernel on either side of each line."""
+    rules("dense_lines")
