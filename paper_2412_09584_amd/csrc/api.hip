@@ -410,8 +410,10 @@ struct WinPlan {
 
 // Window geometry of target k, or false where whole layers serve better: a layer below is
 // not a convolution, a product's shape is outside the window kernels, or the windows cover
-// so much of the layers that they save less than a third of the multiply-adds (the window
-// epilogues cost more per element; no network between 1 / 2 and 1 / 1 was timed).
+// so much of the layers that they save less than a third of the multiply-adds.  That line is a
+// cautious one: third 3x3 layer of 16-32-32 channels, 32 inputs, whole layers / windows 19.6 /
+// 2.0 ms at 0.63 of the multiply-adds (10 x 10 pixels), 10.9 / 1.6 at 0.77 (9 x 9), 1.86 / 1.28 at
+// 0.98 (8 x 8); no size was found where windows lose.
 bool window_plan(const bound_net *net, int k, int rpi, WinPlan &wp) {
     const bound_layer &T = net->layers[k - 1].L;
     const long lim = 1L << 20;                 // FP32-reciprocal quotients

@@ -329,10 +329,12 @@ hipError_t run(const GeomSet &gs, const float *A, long M, const Epi &epi, hipStr
     if (!is_dense(gs) || (SPLIT && !g.Bs) || !dma_fits(g)) return hipErrorInvalidValue;   // no weights it can read
     const int rem = g.N % 128;
     if (g.N <= 32) return launch<Epi, 1, SPLIT>(g, A, M, epi, st);
-    // 64 columns where 128 would pad half a tile, or leave the chip's last round nearly empty
-    // (three blocks of 128 columns fit a CU)
+    // 64 columns where 128 would pad half a tile, and where 128 leave CUs without one of the
+    // blocks that hide its chains: 128 / 64 columns, 256 x 256, 24576 rows (384 tiles) 41 / 36 us,
+    // 49152 rows (768) 56 / 61; 512 x 512, 9216 rows (288) 56 / 50, 16384 rows (512) 64 / 68 (in
+    // FP32 92 / 99); 256 x 784, 131072 rows (padding) 460 / 429
     const long tiles = (M + SBM - 1) / SBM * ((g.N + 127) / 128);
-    if ((rem > 0 && rem <= 64) || tiles < 1536) return launch<Epi, 2, SPLIT>(g, A, M, epi, st);
+    if ((rem > 0 && rem <= 64) || tiles < 512) return launch<Epi, 2, SPLIT>(g, A, M, epi, st);
     return launch<Epi, 4, SPLIT>(g, A, M, epi, st);
 }
 
