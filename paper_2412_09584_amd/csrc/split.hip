@@ -106,18 +106,21 @@ __global__ __launch_bounds__(256, SPLIT ? 3 : 1) void k_dense_tall(const Geom g,
     // this lane's row of A: k = 16 t + 8 h + 0 .. 7 of a chunk, t = 0, 1
     const long row = m0 + col;
     const float *a = A + (row < M ? row : M - 1) * (long)K + 8 * h;     // rows past M: dropped
-    float ra[16], rn[SPLIT ? 1 : 16];
-    auto loadA = [&](int c, int t, float *x) {       // half t of chunk c
-        const int k0 = c * SK + 16 * t;
-        if ((c + 1) * SK <= K) {
+    float ra[16], rn[16];
+    auto loadA = [&](int c, float (&x)[16]) {
+        const int k0 = c * SK;
+        if (k0 + SK <= K) {
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const f4u v = *(const f4u *)(a + k0 + 4 * q);
-                x[4 * q] = v[0]; x[4 * q + 1] = v[1]; x[4 * q + 2] = v[2]; x[4 * q + 3] = v[3];
+            for (int t = 0; t < 4; ++t) {
+                const f4u v = *(const f4u *)(a + k0 + (t >> 1) * 16 + (t & 1) * 4);
+                x[4 * t] = v[0]; x[4 * t + 1] = v[1]; x[4 * t + 2] = v[2]; x[4 * t + 3] = v[3];
             }
         } else {
 #pragma unroll
-            for (int q = 0; q < 8; ++q) x[q] = k0 + q + 8 * h < K ? a[k0 + q] : 0.f;
+            for (int t = 0; t < 16; ++t) {
+                const int k = k0 + (t >> 3) * 16 + (t & 7);
+                x[t] = k + 8 * h < K ? a[k] : 0.f;
+            }
         }
     };
     f32x16 acc[FN];
@@ -128,17 +131,13 @@ __global__ __launch_bounds__(256, SPLIT ? 3 : 1) void k_dense_tall(const Geom g,
     float big = 0.f;             // largest magnitude of this lane's part of its row
 
     dma(0, 0);
-    loadA(0, 0, ra);
-    loadA(0, 1, ra + 8);
+    loadA(0, ra);
     for (int c = 0; c < nch; ++c) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();          // chunk c has landed, and every wave is done with c - 1
         if (c + 1 < nch) {
             dma(c + 1, (c + 1) & 1);
-            if constexpr (!SPLIT) {
-                loadA(c + 1, 0, rn);
-                loadA(c + 1, 1, rn + 8);
-            }
+            if constexpr (!SPLIT) loadA(c + 1, rn);
         }
         const float *B = Bs[c & 1];
         if constexpr (SPLIT) {
@@ -155,10 +154,7 @@ __global__ __launch_bounds__(256, SPLIT ? 3 : 1) void k_dense_tall(const Geom g,
                     // the next chunk takes these registers; not earlier, or the second half's
                     // split would wait for it
                     __builtin_amdgcn_sched_barrier(0);
-                    if (c + 1 < nch) {
-                        loadA(c + 1, 0, ra);
-                        loadA(c + 1, 1, ra + 8);
-                    }
+                    if (c + 1 < nch) loadA(c + 1, ra);
                 }
 #pragma unroll
                 for (int j0 = 0; j0 < FN; j0 += JC) {
