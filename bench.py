@@ -309,7 +309,7 @@ def recompute_compare(bb, stream, steps=5):
 
 
 def deterministic_compare(bb, stream, steps=5):
-    """One optimisation step of the batch with the row sums formed without float atomics
+    """One optimisation step of the batch with the row sums formed without atomics
     (BOUND_OPT_DETERMINISTIC): time per step, and whether two passes from the same state
     give bitwise the same bounds (with and without the mode)."""
     import torch

@@ -28,9 +28,9 @@
 // and go to accumulators of their own, which are subtracted at the end: their bias has the
 // other sign.
 //
-// Full CROWN of the 3x32x32 CNN (conv 16@3x3, 32@4x4/2, 32@3x3, 64@4x4/2, FC 512, 10), error
-// of all bounds against FP64: 1.6e-7 relative, with the FP32 kernels 1.7e-7.  64 inputs, FP32
-// kernels -> these: windows on the stride-2 layer 12.6 -> 9.2 ms, on the 3x3 layer 6.1 -> 4.1;
+// The 3x32x32 CNN (conv 16@3x3, 32@4x4/2, 32@3x3, 64@4x4/2, FC 512, 10), error against FP64:
+// coefficients of 576 spec rows 4.7e-7, with the FP32 kernels 5.1e-7; full CROWN's intermediate
+// bounds 1.5e-7, with FP32 kernels on whole layers 1.6e-7.  64 inputs, FP32 kernels -> these: windows on the stride-2 layer 12.6 -> 9.2 ms, on the 3x3 layer 6.1 -> 4.1;
 // whole 3x3 and 64-channel layers 6.1 -> 4.5.  Nor do few blocks favour the FP32 kernels: whole
 // 3x3 layer, 18 images 21 -> 18 us, 144 images 24 -> 20, 576 images 39 -> 38.
 #include "conv_kernels.h"
